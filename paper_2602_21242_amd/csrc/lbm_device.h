@@ -128,6 +128,10 @@ struct Coef {
   T a0;           // theta (1 - 3 theta)
   T b0;           // 2 theta (1 - theta)
   T c3;           // 1 - 3 theta
+  T th;           // theta
+  T c2, qc2;      // 1 - 2 theta, (1 - 2 theta)/4
+  T e0, tt2;      // theta (1 - theta), 2 theta^2
+  T omb_invth2;   // (1 - 1/tau)/theta^2
 };
 
 // Moments recorded per node and step for the adjoint: rho, u_x, u_y, N_xx, N_xy.
@@ -374,166 +378,133 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
 // m = (rho, j_x, j_y, D, P_xy) (and, for LBGK, directly), so dJ/df = M^T dJ/dm. With the
 // populations indexed by (c_x, c_y) the equilibrium and the OReg population are sums of
 // products of a function of c_x and one of c_y (eq:guidedEq, eq:oreg), so every sum over i
-// of fbs_i times such a product is a 3 x 3 bilinear form x^T F y; dJ/d(rho, u, N) is a few
-// of those, and the corrections Psi (linear in f^OReg through psi and the prefactor) only
-// reweight F. Checked against the complex-step derivative of the literal collision.
+// of fbs_i times such a product is a bilinear form x^T F y.
+//
+// The forms are evaluated in the basis of even and odd parts. A vector v over c = -1, 0, 1 has
+// z = v_0, q = (v_+ + v_-)/2 - v_0 and d = v_+ - v_-, and x . v = x^(0) z + x^(2) q + x^(1) d/2
+// with the moments x^(k) = sum_c c^k x_c. The per-axis factors have short moments:
+//   A0 = Phi(c, u)        (1, u, theta + u^2)            derivative (0, 1, 2u)
+//   A1 = Phi (c - u)      (0, theta, a12)                           (0, 0, 1 - theta - 3u^2)
+//   A2 = Phi (c - u)^2    (theta, a21, a22)                         (0, 1 - 2 theta - 3u^2, 2 da)
+// (in the order 0, 1, 2), a12 = u (1 - theta - u^2), a21 = u (1 - 2 theta - u^2),
+// a22 = theta - u a12, da = u (2u^2 - 1 + theta), so that the nine transformed values of F meet
+// few nonzero coefficients. The form of N_xx, A2 B0 - A0 B2, has the coefficients e_x on (q, z),
+// -e_y on (z, q), e = theta (1 - theta) + u^2 (u^2 - 1), and K on the four with q or d on both
+// axes. The corrections only reweight F: psi takes the (d, z) and (z, d) parts out of the OReg
+// population's weights (partial and complete model), and the prefactor moves Q from (q, z) to
+// (z, q). Checked against the complex-step derivative of the literal collision. Every fused
+// product is written out, so that all reverse kernels agree bit for bit.
 template <class T, int MODEL>
 __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], const Coef<T>& k, T fbar[Q]) {
+#pragma clang fp contract(off)
   const T rho = rec[0], ux = rec[1], uy = rec[2], Nxx = rec[3], Nxy = rec[4];
-  const T ux2 = ux * ux, uy2 = uy * uy;
-  // Per-axis vectors over c = -1, 0, +1 (index c + 1): the GEq factors A0 = Phi(c, u_x) and
-  // their u-derivatives dA0, and for the OReg population A1 = A0 C, A2 = A0 C^2 with
-  // C = c - u_x, and their u_x-derivatives (dC/du_x = -1); B* likewise in y.
-  T A0[3], A1[3], A2[3], dA0[3], dA1[3], dA2[3];
-  T B0[3], B1[3], B2[3], dB0[3], dB1[3], dB2[3];
-  A0[0] = k.r1 + T(0.5) * (ux2 - ux), A0[1] = k.r0 - ux2, A0[2] = k.r1 + T(0.5) * (ux2 + ux);
-  B0[0] = k.r1 + T(0.5) * (uy2 - uy), B0[1] = k.r0 - uy2, B0[2] = k.r1 + T(0.5) * (uy2 + uy);
-  dA0[0] = ux - T(0.5), dA0[1] = T(-2) * ux, dA0[2] = ux + T(0.5);
-  dB0[0] = uy - T(0.5), dB0[1] = T(-2) * uy, dB0[2] = uy + T(0.5);
-  // F[a][b]: the reverse-streamed adjoint populations arranged by (c_x, c_y).
-  T F[3][3];
-#pragma unroll
-  for (int i = 0; i < Q; ++i) F[cx(i) + 1][cy(i) + 1] = fbs[i];
-  auto matvec = [](const T M[3][3], const T v[3], T out[3]) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) out[a] = M[a][0] * v[0] + M[a][1] * v[1] + M[a][2] * v[2];
-  };
-  auto dot = [](const T x[3], const T y[3]) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
-  // Terms whose coefficient is a lattice constant of 0 are left out (a product with a zero
-  // constant stays in the code, since 0 * x is NaN for infinite x: 29 of the 365 vector
-  // instructions of the FP32 complete model), the others are summed in the order of the full
-  // sums: for finite values the complete and uncorrected models give the full sums' results
-  // bit for bit; LBGK and the partial model differ within rounding (2.5e-7 in FP32), where
-  // the compiler now fuses other products.
-
-  T uxb, uyb;
-  if (MODEL != M_BGK) {
-    // Weights of the OReg population f^OReg_i = P_i t_i in the output: omb fbs, plus, for the
-    // corrected models, the chain through Psi, which depends on f^OReg via psi = sum c f^OReg
-    // and (complete model) the prefactor, a moment of f^OReg.
-    T W[3][3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) W[a][b] = k.omb * F[a][b];
-    T uxc, uyc;  // the complete model's direct u-dependence of the stress error
-    if (MODEL == M_PARTIAL || MODEL == M_COMPLETE) {
-      // Psi bar = omb fbs; psi bar_x = (Psib_3 - Psib_1)/2, psi bar_y = (Psib_4 - Psib_2)/2.
-      const T psxb = T(0.5) * (W[0][1] - W[2][1]);
-      const T psyb = T(0.5) * (W[1][0] - W[1][2]);
-      if (MODEL == M_COMPLETE) {
-        // Prefactor from its closed form (the moment of f^OReg), stress-error weights and
-        // their direct u-dependence; the prefactor's own dependence on f^OReg enters W.
-        const T pf = -k.inv4th2 * (Nxx * k.inv2th2) * (k.b0 + ux2 * (ux2 - T(1)) + uy2 * (uy2 - T(1)));
-        const T ax = k.a0 + ux2 * (ux2 - T(1));
-        const T ay = k.a0 + uy2 * (uy2 - T(1));
-        const T bxy = ux * uy * (ux2 - uy2);
-        const T sb = (W[2][2] + W[0][2]) + (W[0][0] + W[2][0]);
-        const T Ptyyb = T(0.5) * (W[2][1] + W[0][1]) - T(0.25) * sb;
-        const T Ptxxb = T(0.5) * (W[1][2] + W[1][0]) - T(0.25) * sb;
-        const T Ptxyb = T(0.25) * ((W[0][2] + W[2][0]) - (W[2][2] + W[0][0]));
-        const T pfb = -Ptxxb * ax + Ptyyb * ay + Ptxyb * bxy;
-        const T axb = -Ptxxb * pf, ayb = Ptyyb * pf, bb = Ptxyb * pf;
-        uxc = axb * (T(4) * ux2 - T(2)) * ux + bb * uy * (T(3) * ux2 - uy2);
-        uyc = ayb * (T(4) * uy2 - T(2)) * uy + bb * ux * (ux2 - T(3) * uy2);
-        const T q = k.inv4th2 * pfb;
-        W[2][1] -= q;  // populations 1 and 3
-        W[0][1] -= q;
-        W[1][2] += q;  // populations 2 and 4
-        W[1][0] += q;
-      }
-      // W_ab += c_a psi bar_x + c_b psi bar_y with c = a - 1 (edges one term, corners the sum).
-      W[2][1] += psxb;
-      W[0][1] += -psxb;
-      W[1][2] += psyb;
-      W[1][0] += -psyb;
-      W[2][2] += psxb + psyb;
-      W[0][0] += -psxb - psyb;
-      W[2][0] += psxb - psyb;
-      W[0][2] += -psxb + psyb;
-    }
-    // f^OReg_ab = [(A2_a B0_b - A0_a B2_b) N_xx + 2 A1_a B1_b N_xy] / (2 theta^2).
-    const T Cx[3] = {T(-1) - ux, -ux, T(1) - ux};
-    const T Cy[3] = {T(-1) - uy, -uy, T(1) - uy};
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      A1[c] = A0[c] * Cx[c];
-      A2[c] = A1[c] * Cx[c];
-      const T tx = dA0[c] * Cx[c];
-      dA1[c] = tx - A0[c];
-      dA2[c] = tx * Cx[c] - T(2) * A1[c];
-      B1[c] = B0[c] * Cy[c];
-      B2[c] = B1[c] * Cy[c];
-      const T ty = dB0[c] * Cy[c];
-      dB1[c] = ty - B0[c];
-      dB2[c] = ty * Cy[c] - T(2) * B1[c];
-    }
-    T WB0[3], WB1[3], WB2[3], WdB0[3], WdB1[3], WdB2[3];
-    matvec(W, B0, WB0);
-    matvec(W, B1, WB1);
-    matvec(W, B2, WB2);
-    matvec(W, dB0, WdB0);
-    matvec(W, dB1, WdB1);
-    matvec(W, dB2, WdB2);
-    const T kx = Nxx * k.inv2th2, ky = Nxy * (T(2) * k.inv2th2);
-    const T Nxxb = k.inv2th2 * (dot(A2, WB0) - dot(A0, WB2));
-    const T Nxyb = (T(2) * k.inv2th2) * dot(A1, WB1);
-    const T uxo = kx * (dot(dA2, WB0) - dot(dA0, WB2)) + ky * dot(dA1, WB1);
-    const T uyo = kx * (dot(A2, WdB0) - dot(A0, WdB2)) + ky * dot(A1, WdB1);
-    if (MODEL == M_COMPLETE) {
-      uxb = uxc + uxo;
-      uyb = uyc + uyo;
-    } else {
-      uxb = uxo;
-      uyb = uyo;
-    }
-    const T Db = T(0.5) * Nxxb;
-    const T Pxyb = Nxyb;
-    // Equilibrium part rho A0_a B0_b (shifted by a constant).
-    T FB0[3], FdB0[3];
-    matvec(F, B0, FB0);
-    matvec(F, dB0, FdB0);
-    T rhob = dot(A0, FB0);
-    uxb += rho * dot(dA0, FB0);
-    uyb += rho * dot(A0, FdB0);
-    // Chain (rho, u, N) -> (rho, j, D, Pxy).
-    rhob += T(-0.5) * Nxxb * (ux2 - uy2) - Nxyb * ux * uy;
-    uxb += -Nxxb * rho * ux - Nxyb * rho * uy;
-    uyb += Nxxb * rho * uy - Nxyb * rho * ux;
-    const T rinv = recip(rho);
-    const T jxb = uxb * rinv, jyb = uyb * rinv;
-    rhob -= (uxb * ux + uyb * uy) * rinv;
-    // fbar_i = rhob + c_ix jxb + c_iy jyb + (c_ix^2 - c_iy^2) Db + c_ix c_iy Pxyb, nonzero
-    // terms in this order.
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      T t = rhob;
-      if (cx(i) != 0) t = t + (cx(i) > 0 ? jxb : -jxb);
-      if (cy(i) != 0) t = t + (cy(i) > 0 ? jyb : -jyb);
-      if (cx(i) * cx(i) != cy(i) * cy(i)) t = t + (cx(i) * cx(i) > cy(i) * cy(i) ? Db : -Db);
-      if (cx(i) * cy(i) != 0) t = t + (cx(i) * cy(i) > 0 ? Pxyb : -Pxyb);
-      fbar[i] = t;
-    }
-  } else {
-    // LBGK: the equilibrium part rho A0_a B0_b weighted 1 - omb, and omb fbs directly.
-    const T es = T(1) - k.omb;
-    T FB0[3], FdB0[3];
-    matvec(F, B0, FB0);
-    matvec(F, dB0, FdB0);
-    T rhob = es * dot(A0, FB0);
-    uxb = es * rho * dot(dA0, FB0);
-    uyb = es * rho * dot(A0, FdB0);
-    const T rinv = recip(rho);
-    const T jxb = uxb * rinv, jyb = uyb * rinv;
-    rhob -= (uxb * ux + uyb * uy) * rinv;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      T t = fmad(k.omb, fbs[i], rhob);
-      if (cx(i) != 0) t = t + (cx(i) > 0 ? jxb : -jxb);
-      if (cy(i) != 0) t = t + (cy(i) > 0 ? jyb : -jyb);
-      fbar[i] = t;
-    }
+  const T x2 = ux * ux, y2 = uy * uy;
+  const T hux = T(0.5) * ux, huy = T(0.5) * uy;
+  // F over (c_x, c_y): first along x for each c_y, then along y.
+  const T h = T(0.5);
+  const T sm = fbs[8] + fbs[7], s0 = fbs[1] + fbs[3], sp = fbs[5] + fbs[6];
+  const T qm = fmad(h, sm, -fbs[4]), q0 = fmad(h, s0, -fbs[0]), qp = fmad(h, sp, -fbs[2]);
+  const T dm = fbs[8] - fbs[7], d0 = fbs[1] - fbs[3], dp = fbs[5] - fbs[6];
+  const T Fzz = fbs[0], Fzq = fmad(h, fbs[2] + fbs[4], -fbs[0]), Fzd = fbs[2] - fbs[4];
+  const T Fqz = q0, Fqq = fmad(h, qp + qm, -q0), Fqd = qp - qm;
+  const T Fdz = d0, Fdq = fmad(h, dp + dm, -d0), Fdd = dp - dm;
+  // Equilibrium part rho A0 B0 (shifted by a constant): value e0, twice the derivatives ex2, ey2.
+  const T tx = k.th + x2, ty = k.th + y2;
+  const T vz = fmad(huy, Fzd, fmad(ty, Fzq, Fzz));
+  const T vq = fmad(huy, Fqd, fmad(ty, Fqq, Fqz));
+  const T vd = fmad(huy, Fdd, fmad(ty, Fdq, Fdz));
+  const T fx = T(4) * ux, fy = T(4) * uy;
+  const T e0 = fmad(hux, vd, fmad(tx, vq, vz));
+  const T ex2 = fmad(fx, vq, vd);
+  const T ey2 = fmad(hux, fmad(fy, Fdq, Fdd), fmad(tx, fmad(fy, Fqq, Fqd), fmad(fy, Fzq, Fzd)));
+  const T rinv = recip(rho);
+  if (MODEL == M_BGK) {
+    // The equilibrium weighted 1 - omb = 1/tau, and omb fbs directly. dJ/dj = dJ/du / rho.
+    const T es = T(1) - k.omb, hes = h * es;
+    const T jxb = hes * ex2, jyb = hes * ey2;
+    const T rb = fmad(-jyb, uy, fmad(-jxb, ux, es * e0));
+    const T rp = rb + jxb, rm = rb - jxb;
+    fbar[0] = fmad(k.omb, fbs[0], rb);
+    fbar[1] = fmad(k.omb, fbs[1], rp);
+    fbar[2] = fmad(k.omb, fbs[2], rb + jyb);
+    fbar[3] = fmad(k.omb, fbs[3], rm);
+    fbar[4] = fmad(k.omb, fbs[4], rb - jyb);
+    fbar[5] = fmad(k.omb, fbs[5], rp + jyb);
+    fbar[6] = fmad(k.omb, fbs[6], rm + jyb);
+    fbar[7] = fmad(k.omb, fbs[7], rm - jyb);
+    fbar[8] = fmad(k.omb, fbs[8], rp - jyb);
+    return;
   }
+  // Per-axis moments (halved where they meet a d part).
+  const T a12 = ux * (k.r0 - x2), b12 = uy * (k.r0 - y2);
+  const T a22 = fmad(-ux, a12, k.th), b22 = fmad(-uy, b12, k.th);
+  const T ha21 = hux * (k.c2 - x2), hb21 = huy * (k.c2 - y2);
+  const T da = ux * fmad(T(2), x2, -k.r0), db = uy * fmad(T(2), y2, -k.r0);
+  const T qda = fmad(T(-0.75), x2, k.qc2), qdb = fmad(T(-0.75), y2, k.qc2);  // (1 - 2 theta - 3u^2)/4
+  const T ex = k.e0 + fmad(x2, x2, -x2), ey = k.e0 + fmad(y2, y2, -y2);
+  const T dex = ux * fmad(T(2), x2, T(-1)), dey = uy * fmad(T(2), y2, T(-1));  // half the derivatives of e
+  const T dy2 = y2 - x2;
+  const T Kdd = hux * huy * dy2;
+  const T Kddx = T(0.25) * huy * fmad(T(-3), x2, y2), Kddy = T(0.25) * hux * fmad(T(3), y2, -x2);
+  // Weights of the OReg population, in units of omb: F with the corrections' chain.
+  T Wqz = Fqz, Wzq = Fzq;
+  const T kx = Nxx * k.omb_inv2th2;
+  T uxc = T(0), uyc = T(0);  // the complete model's direct u-dependence of the stress error, halved
+  if (MODEL == M_COMPLETE) {
+    const T pxx = Fqq + Fqz, pyy = Fqq + Fzq;
+    const T pf = -k.inv4th2 * (kx * (ex + ey));
+    uxc = pf * fmad(Fdd, Kddx, pxx * dex);
+    uyc = pf * fmad(Fdd, Kddy, -(pyy * dey));
+    const T Qw = k.inv4th2 * fmad(Fdd, Kdd, fmad(pxx, ex - k.tt2, -(pyy * (ey - k.tt2))));
+    Wqz = Wqz - Qw;
+    Wzq = Wzq + Qw;
+  }
+  // N_xx: the form S and half its u-derivatives.
+  T S = fmad(ex, Wqz, -(ey * Wzq));
+  S = fmad(fmad(a22, ty, -(tx * b22)), Fqq, S);
+  S = fmad(fmad(a22, huy, -(tx * hb21)), Fqd, S);
+  S = fmad(fmad(ha21, ty, -(hux * b22)), Fdq, S);
+  S = fmad(Kdd, Fdd, S);
+  T Sx = fmad(dex, Wqz, Kddx * Fdd);
+  Sx = fmad(fmad(da, ty, -(ux * b22)), Fqq, Sx);
+  Sx = fmad(fmad(da, huy, -(ux * hb21)), Fqd, Sx);
+  Sx = fmad(fmad(qda, ty, T(-0.25) * b22), Fdq, Sx);
+  T Sy = fmad(-dey, Wzq, Kddy * Fdd);
+  Sy = fmad(fmad(a22, uy, -(tx * db)), Fqq, Sy);
+  Sy = fmad(fmad(T(0.25), a22, -(tx * qdb)), Fqd, Sy);
+  Sy = fmad(fmad(ha21, uy, -(hux * db)), Fdq, Sy);
+  if (MODEL == M_UC) {
+    S = fmad(hux * (k.c3 - x2), Fdz, fmad(-huy * (k.c3 - y2), Fzd, S));
+    Sx = fmad(T(0.25) * fmad(T(-3), x2, k.c3), Fdz, Sx);
+    Sy = fmad(T(-0.25) * fmad(T(-3), y2, k.c3), Fzd, Sy);
+  }
+  // N_xy: theta/2 = r1.
+  const T g1 = fmad(k.r1, Fqd, b12 * Fqq), g2 = fmad(k.r1, Fdd, b12 * Fdq), g3 = fmad(k.r1, Fdq, a12 * Fqq);
+  const T ky = Nxy * k.omb_inv2th2;
+  const T Nxxb = k.omb_inv2th2 * S;
+  const T Nxyb = k.omb_invth2 * fmad(a12, g1, k.r1 * g2);
+  // Half of dJ/du through the populations, then the chain (rho, u, N) -> (rho, j, D, P_xy).
+  const T hrho = h * rho;
+  const T hux_b = fmad(ky * fmad(T(-3), x2, k.r0), g1, fmad(kx, Sx, uxc));
+  const T huy_b = fmad(ky * fmad(T(-3), y2, k.r0), g3, fmad(kx, Sy, uyc));
+  const T uxb = fmad(hrho, ex2, T(2) * hux_b), uyb = fmad(hrho, ey2, T(2) * huy_b);
+  const T jxb = fmad(uxb, rinv, -fmad(Nxxb, ux, Nxyb * uy));
+  const T jyb = fmad(uyb, rinv, fmad(Nxxb, uy, -(Nxyb * ux)));
+  const T Db = h * Nxxb;
+  // dJ/drho = e0 - Nxxb (ux^2 - uy^2)/2 - Nxyb ux uy - (dJ/dj) . u
+  T rb = fmad(Db, dy2, e0);
+  rb = fmad(-Nxyb * ux, uy, rb);
+  rb = fmad(-jyb, uy, fmad(-jxb, ux, rb));
+  const T rx = rb + Db, ry = rb - Db, yp = rb + jyb, ym = rb - jyb, xp = jxb + Nxyb, xm = jxb - Nxyb;
+  fbar[0] = rb;
+  fbar[1] = rx + jxb;
+  fbar[2] = ry + jyb;
+  fbar[3] = rx - jxb;
+  fbar[4] = ry - jyb;
+  fbar[5] = yp + xp;
+  fbar[6] = yp - xp;
+  fbar[7] = ym - xm;
+  fbar[8] = ym + xm;
 }
 
 }  // namespace lbm

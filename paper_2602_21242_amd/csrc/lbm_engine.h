@@ -99,6 +99,12 @@ inline Coef<T> make_coef(const RunDesc& d) {
   k.a0 = T(th * (1.0 - 3.0 * th));
   k.b0 = T(2.0 * th * (1.0 - th));
   k.c3 = T(1.0 - 3.0 * th);
+  k.th = T(th);
+  k.c2 = T(1.0 - 2.0 * th);
+  k.qc2 = T(0.25 * (1.0 - 2.0 * th));
+  k.e0 = T(th * (1.0 - th));
+  k.tt2 = T(2.0 * th * th);
+  k.omb_invth2 = T((1.0 - 1.0 / d.tau) / (th * th));
   return k;
 }
 
