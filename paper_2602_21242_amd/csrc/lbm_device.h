@@ -129,9 +129,9 @@ struct Coef {
   T b0;           // 2 theta (1 - theta)
   T c3;           // 1 - 3 theta
   T th;           // theta
-  T c2, qc2;      // 1 - 2 theta, (1 - 2 theta)/4
+  T c2, hc2;      // 1 - 2 theta, (1 - 2 theta)/2
   T e0, tt2;      // theta (1 - theta), 2 theta^2
-  T omb_invth2;   // (1 - 1/tau)/theta^2
+  T omb_inv4th2;  // (1 - 1/tau)/(4 theta^2)
 };
 
 // Moments recorded per node and step for the adjoint: rho, u_x, u_y, N_xx, N_xy.
@@ -381,7 +381,7 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
 // of fbs_i times such a product is a bilinear form x^T F y.
 //
 // The forms are evaluated in the basis of even and odd parts. A vector v over c = -1, 0, 1 has
-// z = v_0, q = (v_+ + v_-)/2 - v_0 and d = v_+ - v_-, and x . v = x^(0) z + x^(2) q + x^(1) d/2
+// z = v_0, q = v_+ + v_- - 2 v_0 and d = v_+ - v_-, and x . v = x^(0) z + x^(2) q/2 + x^(1) d/2
 // with the moments x^(k) = sum_c c^k x_c. The per-axis factors have short moments:
 //   A0 = Phi(c, u)        (1, u, theta + u^2)            derivative (0, 1, 2u)
 //   A1 = Phi (c - u)      (0, theta, a12)                           (0, 0, 1 - theta - 3u^2)
@@ -392,66 +392,74 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
 // -e_y on (z, q), e = theta (1 - theta) + u^2 (u^2 - 1), and K on the four with q or d on both
 // axes. The corrections only reweight F: psi takes the (d, z) and (z, d) parts out of the OReg
 // population's weights (partial and complete model), and the prefactor moves Q from (q, z) to
-// (z, q). Checked against the complex-step derivative of the literal collision. Every fused
-// product is written out, so that all reverse kernels agree bit for bit.
+// (z, q). Checked against the complex-step derivative of the literal collision. About 190 vector
+// instructions for the FP32 complete model, against 325 for the same forms summed over c. Every
+// fused product is written out, so that all reverse kernels agree bit for bit.
+//
+// Where fbar* varies little over the nine populations, as in a smooth flow, all but (z, z) are
+// small: they are formed from differences to v_0, and every output is fbs_0 plus a sum of small
+// terms, rounded once, since errors of one sign over smooth regions add up over the steps.
+// Enstrophy gradient of the 16384 x 4096 shear layer along the perturbation, FP32 against FP64
+// central differences: 2.8e-6 after 500 steps and 9.7e-5 after 3000 (sums over c: 4.1e-6 and
+// 8.6e-5; equally exact arrangements of this code between 1.0e-4 and 1.1e-4, one with sums of
+// the full values 1.7e-4): at 3000 steps it is the FP32 trajectory that is off.
 template <class T, int MODEL>
 __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], const Coef<T>& k, T fbar[Q]) {
 #pragma clang fp contract(off)
   const T rho = rec[0], ux = rec[1], uy = rec[2], Nxx = rec[3], Nxy = rec[4];
   const T x2 = ux * ux, y2 = uy * uy;
-  const T hux = T(0.5) * ux, huy = T(0.5) * uy;
+  const T h = T(0.5), hux = h * ux, huy = h * uy;
   // F over (c_x, c_y): first along x for each c_y, then along y.
-  const T h = T(0.5);
-  const T sm = fbs[8] + fbs[7], s0 = fbs[1] + fbs[3], sp = fbs[5] + fbs[6];
-  const T qm = fmad(h, sm, -fbs[4]), q0 = fmad(h, s0, -fbs[0]), qp = fmad(h, sp, -fbs[2]);
-  const T dm = fbs[8] - fbs[7], d0 = fbs[1] - fbs[3], dp = fbs[5] - fbs[6];
-  const T Fzz = fbs[0], Fzq = fmad(h, fbs[2] + fbs[4], -fbs[0]), Fzd = fbs[2] - fbs[4];
-  const T Fqz = q0, Fqq = fmad(h, qp + qm, -q0), Fqd = qp - qm;
-  const T Fdz = d0, Fdq = fmad(h, dp + dm, -d0), Fdd = dp - dm;
-  // Equilibrium part rho A0 B0 (shifted by a constant): value e0, twice the derivatives ex2, ey2.
-  const T tx = k.th + x2, ty = k.th + y2;
-  const T vz = fmad(huy, Fzd, fmad(ty, Fzq, Fzz));
-  const T vq = fmad(huy, Fqd, fmad(ty, Fqq, Fqz));
-  const T vd = fmad(huy, Fdd, fmad(ty, Fdq, Fdz));
-  const T fx = T(4) * ux, fy = T(4) * uy;
-  const T e0 = fmad(hux, vd, fmad(tx, vq, vz));
+  const T z0 = fbs[0], zp = fbs[2], zm = fbs[4];
+  const T p0 = fbs[1] - z0, m0 = fbs[3] - z0, pp = fbs[5] - zp, mp = fbs[6] - zp, pm = fbs[8] - zm, mm = fbs[7] - zm;
+  const T q0 = p0 + m0, qp = pp + mp, qm = pm + mm, d0 = p0 - m0, dp = pp - mp, dm = pm - mm;
+  const T zu = zp - z0, zl = zm - z0;
+  const T Fzq = zu + zl, Fzd = zu - zl;
+  const T Fqz = q0, Fqq = fmad(T(-2), q0, qp + qm), Fqd = qp - qm;
+  const T Fdz = d0, Fdq = fmad(T(-2), d0, dp + dm), Fdd = dp - dm;
+  // Equilibrium part rho A0 B0 (shifted by a constant): value fbs_0 + e0, twice the derivatives ex2, ey2.
+  const T htx = h * (k.th + x2), hty = h * (k.th + y2);
+  const T vq = fmad(huy, Fqd, fmad(hty, Fqq, Fqz));
+  const T vd = fmad(huy, Fdd, fmad(hty, Fdq, Fdz));
+  const T fx = T(2) * ux, fy = T(2) * uy;
+  const T e0 = fmad(hux, vd, fmad(htx, vq, fmad(huy, Fzd, hty * Fzq)));
   const T ex2 = fmad(fx, vq, vd);
-  const T ey2 = fmad(hux, fmad(fy, Fdq, Fdd), fmad(tx, fmad(fy, Fqq, Fqd), fmad(fy, Fzq, Fzd)));
-  const T rinv = recip(rho);
+  const T ey2 = fmad(hux, fmad(fy, Fdq, Fdd), fmad(htx, fmad(fy, Fqq, Fqd), fmad(fy, Fzq, Fzd)));
   if (MODEL == M_BGK) {
-    // The equilibrium weighted 1 - omb = 1/tau, and omb fbs directly. dJ/dj = dJ/du / rho.
+    // The equilibrium weighted 1 - omb = 1/tau, and omb fbs directly: fbs_i = fbs_0 + (fbs_i -
+    // fbs_0). dJ/dj = dJ/du / rho.
     const T es = T(1) - k.omb, hes = h * es;
     const T jxb = hes * ex2, jyb = hes * ey2;
-    const T rb = fmad(-jyb, uy, fmad(-jxb, ux, es * e0));
-    const T rp = rb + jxb, rm = rb - jxb;
-    fbar[0] = fmad(k.omb, fbs[0], rb);
-    fbar[1] = fmad(k.omb, fbs[1], rp);
-    fbar[2] = fmad(k.omb, fbs[2], rb + jyb);
-    fbar[3] = fmad(k.omb, fbs[3], rm);
-    fbar[4] = fmad(k.omb, fbs[4], rb - jyb);
-    fbar[5] = fmad(k.omb, fbs[5], rp + jyb);
-    fbar[6] = fmad(k.omb, fbs[6], rm + jyb);
-    fbar[7] = fmad(k.omb, fbs[7], rm - jyb);
-    fbar[8] = fmad(k.omb, fbs[8], rp - jyb);
+    const T t = fmad(-jyb, uy, fmad(-jxb, ux, es * e0));
+    const T tp = t + jxb, tm = t - jxb;
+    fbar[0] = z0 + t;
+    fbar[1] = z0 + fmad(k.omb, p0, tp);
+    fbar[2] = z0 + fmad(k.omb, zu, t + jyb);
+    fbar[3] = z0 + fmad(k.omb, m0, tm);
+    fbar[4] = z0 + fmad(k.omb, zl, t - jyb);
+    fbar[5] = z0 + fmad(k.omb, fbs[5] - z0, tp + jyb);
+    fbar[6] = z0 + fmad(k.omb, fbs[6] - z0, tm + jyb);
+    fbar[7] = z0 + fmad(k.omb, fbs[7] - z0, tm - jyb);
+    fbar[8] = z0 + fmad(k.omb, fbs[8] - z0, tp - jyb);
     return;
   }
-  // Per-axis moments (halved where they meet a d part).
+  // Per-axis moments.
   const T a12 = ux * (k.r0 - x2), b12 = uy * (k.r0 - y2);
   const T a22 = fmad(-ux, a12, k.th), b22 = fmad(-uy, b12, k.th);
-  const T ha21 = hux * (k.c2 - x2), hb21 = huy * (k.c2 - y2);
+  const T a21 = ux * (k.c2 - x2), b21 = uy * (k.c2 - y2);
   const T da = ux * fmad(T(2), x2, -k.r0), db = uy * fmad(T(2), y2, -k.r0);
-  const T qda = fmad(T(-0.75), x2, k.qc2), qdb = fmad(T(-0.75), y2, k.qc2);  // (1 - 2 theta - 3u^2)/4
+  const T hda = fmad(T(-1.5), x2, k.hc2), hdb = fmad(T(-1.5), y2, k.hc2);  // (1 - 2 theta - 3u^2)/2
   const T ex = k.e0 + fmad(x2, x2, -x2), ey = k.e0 + fmad(y2, y2, -y2);
   const T dex = ux * fmad(T(2), x2, T(-1)), dey = uy * fmad(T(2), y2, T(-1));  // half the derivatives of e
   const T dy2 = y2 - x2;
-  const T Kdd = hux * huy * dy2;
-  const T Kddx = T(0.25) * huy * fmad(T(-3), x2, y2), Kddy = T(0.25) * hux * fmad(T(3), y2, -x2);
+  const T Kdd = ux * huy * dy2;
+  const T Kddx = h * huy * fmad(T(-3), x2, y2), Kddy = h * hux * fmad(T(3), y2, -x2);
   // Weights of the OReg population, in units of omb: F with the corrections' chain.
   T Wqz = Fqz, Wzq = Fzq;
   const T kx = Nxx * k.omb_inv2th2;
-  T uxc = T(0), uyc = T(0);  // the complete model's direct u-dependence of the stress error, halved
+  T uxc = T(0), uyc = T(0);  // the complete model's direct u-dependence of the stress error
   if (MODEL == M_COMPLETE) {
-    const T pxx = Fqq + Fqz, pyy = Fqq + Fzq;
+    const T pxx = fmad(h, Fqq, Fqz), pyy = fmad(h, Fqq, Fzq);
     const T pf = -k.inv4th2 * (kx * (ex + ey));
     uxc = pf * fmad(Fdd, Kddx, pxx * dex);
     uyc = pf * fmad(Fdd, Kddy, -(pyy * dey));
@@ -459,52 +467,51 @@ __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], c
     Wqz = Wqz - Qw;
     Wzq = Wzq + Qw;
   }
-  // N_xx: the form S and half its u-derivatives.
+  // N_xx: twice the form, S, and its u-derivatives over two.
   T S = fmad(ex, Wqz, -(ey * Wzq));
-  S = fmad(fmad(a22, ty, -(tx * b22)), Fqq, S);
-  S = fmad(fmad(a22, huy, -(tx * hb21)), Fqd, S);
-  S = fmad(fmad(ha21, ty, -(hux * b22)), Fdq, S);
+  S = fmad(fmad(a22, hty, -(htx * b22)), Fqq, S);
+  S = fmad(fmad(a22, huy, -(htx * b21)), Fqd, S);
+  S = fmad(fmad(a21, hty, -(hux * b22)), Fdq, S);
   S = fmad(Kdd, Fdd, S);
   T Sx = fmad(dex, Wqz, Kddx * Fdd);
-  Sx = fmad(fmad(da, ty, -(ux * b22)), Fqq, Sx);
-  Sx = fmad(fmad(da, huy, -(ux * hb21)), Fqd, Sx);
-  Sx = fmad(fmad(qda, ty, T(-0.25) * b22), Fdq, Sx);
+  Sx = fmad(fmad(da, hty, -(hux * b22)), Fqq, Sx);
+  Sx = fmad(fmad(da, huy, -(hux * b21)), Fqd, Sx);
+  Sx = fmad(fmad(hda, hty, T(-0.25) * b22), Fdq, Sx);
   T Sy = fmad(-dey, Wzq, Kddy * Fdd);
-  Sy = fmad(fmad(a22, uy, -(tx * db)), Fqq, Sy);
-  Sy = fmad(fmad(T(0.25), a22, -(tx * qdb)), Fqd, Sy);
-  Sy = fmad(fmad(ha21, uy, -(hux * db)), Fdq, Sy);
+  Sy = fmad(fmad(a22, huy, -(htx * db)), Fqq, Sy);
+  Sy = fmad(fmad(T(0.25), a22, -(htx * hdb)), Fqd, Sy);
+  Sy = fmad(fmad(a21, huy, -(hux * db)), Fdq, Sy);
   if (MODEL == M_UC) {
-    S = fmad(hux * (k.c3 - x2), Fdz, fmad(-huy * (k.c3 - y2), Fzd, S));
-    Sx = fmad(T(0.25) * fmad(T(-3), x2, k.c3), Fdz, Sx);
-    Sy = fmad(T(-0.25) * fmad(T(-3), y2, k.c3), Fzd, Sy);
+    S = fmad(ux * (k.c3 - x2), Fdz, fmad(-uy * (k.c3 - y2), Fzd, S));
+    Sx = fmad(h * fmad(T(-3), x2, k.c3), Fdz, Sx);
+    Sy = fmad(-h * fmad(T(-3), y2, k.c3), Fzd, Sy);
   }
-  // N_xy: theta/2 = r1.
-  const T g1 = fmad(k.r1, Fqd, b12 * Fqq), g2 = fmad(k.r1, Fdd, b12 * Fdq), g3 = fmad(k.r1, Fdq, a12 * Fqq);
-  const T ky = Nxy * k.omb_inv2th2;
-  const T Nxxb = k.omb_inv2th2 * S;
-  const T Nxyb = k.omb_invth2 * fmad(a12, g1, k.r1 * g2);
-  // Half of dJ/du through the populations, then the chain (rho, u, N) -> (rho, j, D, P_xy).
-  const T hrho = h * rho;
-  const T hux_b = fmad(ky * fmad(T(-3), x2, k.r0), g1, fmad(kx, Sx, uxc));
-  const T huy_b = fmad(ky * fmad(T(-3), y2, k.r0), g3, fmad(kx, Sy, uyc));
-  const T uxb = fmad(hrho, ex2, T(2) * hux_b), uyb = fmad(hrho, ey2, T(2) * huy_b);
+  // N_xy.
+  const T g1 = fmad(k.th, Fqd, b12 * Fqq), g2 = fmad(k.th, Fdd, b12 * Fdq), g3 = fmad(k.th, Fdq, a12 * Fqq);
+  const T ky = Nxy * k.omb_inv4th2;
+  const T Nxxb = k.omb_inv4th2 * S;
+  const T Nxyb = k.omb_inv4th2 * fmad(a12, g1, k.th * g2);
+  // dJ/du through N, then the chain (rho, u, N) -> (rho, j, D, P_xy).
+  const T rinv = recip(rho), hrho = h * rho;
+  const T uxb = fmad(hrho, ex2, fmad(ky * fmad(T(-3), x2, k.r0), g1, fmad(kx, Sx, uxc)));
+  const T uyb = fmad(hrho, ey2, fmad(ky * fmad(T(-3), y2, k.r0), g3, fmad(kx, Sy, uyc)));
   const T jxb = fmad(uxb, rinv, -fmad(Nxxb, ux, Nxyb * uy));
   const T jyb = fmad(uyb, rinv, fmad(Nxxb, uy, -(Nxyb * ux)));
   const T Db = h * Nxxb;
-  // dJ/drho = e0 - Nxxb (ux^2 - uy^2)/2 - Nxyb ux uy - (dJ/dj) . u
-  T rb = fmad(Db, dy2, e0);
-  rb = fmad(-Nxyb * ux, uy, rb);
-  rb = fmad(-jyb, uy, fmad(-jxb, ux, rb));
-  const T rx = rb + Db, ry = rb - Db, yp = rb + jyb, ym = rb - jyb, xp = jxb + Nxyb, xm = jxb - Nxyb;
-  fbar[0] = rb;
-  fbar[1] = rx + jxb;
-  fbar[2] = ry + jyb;
-  fbar[3] = rx - jxb;
-  fbar[4] = ry - jyb;
-  fbar[5] = yp + xp;
-  fbar[6] = yp - xp;
-  fbar[7] = ym - xm;
-  fbar[8] = ym + xm;
+  // dJ/drho = fbs_0 + e0 - Nxxb (ux^2 - uy^2)/2 - Nxyb ux uy - (dJ/dj) . u
+  T t = fmad(Db, dy2, e0);
+  t = fmad(-Nxyb * ux, uy, t);
+  t = fmad(-jyb, uy, fmad(-jxb, ux, t));
+  const T tx = t + Db, ty = t - Db, tp = t + jyb, tm = t - jyb, xp = jxb + Nxyb, xm = jxb - Nxyb;
+  fbar[0] = z0 + t;
+  fbar[1] = z0 + (tx + jxb);
+  fbar[2] = z0 + (ty + jyb);
+  fbar[3] = z0 + (tx - jxb);
+  fbar[4] = z0 + (ty - jyb);
+  fbar[5] = z0 + (tp + xp);
+  fbar[6] = z0 + (tp - xp);
+  fbar[7] = z0 + (tm - xm);
+  fbar[8] = z0 + (tm + xm);
 }
 
 }  // namespace lbm

@@ -99,12 +99,14 @@ inline Coef<T> make_coef(const RunDesc& d) {
   k.a0 = T(th * (1.0 - 3.0 * th));
   k.b0 = T(2.0 * th * (1.0 - th));
   k.c3 = T(1.0 - 3.0 * th);
-  k.th = T(th);
-  k.c2 = T(1.0 - 2.0 * th);
-  k.qc2 = T(0.25 * (1.0 - 2.0 * th));
-  k.e0 = T(th * (1.0 - th));
-  k.tt2 = T(2.0 * th * th);
-  k.omb_invth2 = T((1.0 - 1.0 / d.tau) / (th * th));
+  // The VJP's theta is that of the rest factors the collision uses, 2 r1 = 1 - r0.
+  const double te = 2.0 * double(k.r1);
+  k.th = T(te);
+  k.c2 = T(1.0 - 2.0 * te);
+  k.hc2 = T(0.5 * (1.0 - 2.0 * te));
+  k.e0 = T(te * (1.0 - te));
+  k.tt2 = T(2.0 * te * te);
+  k.omb_inv4th2 = T((1.0 - 1.0 / d.tau) / (4.0 * th * th));
   return k;
 }
 
