@@ -96,8 +96,10 @@ typedef struct {
                             record_steps x 5 x sizeof(compute type) bytes per node) recomputes
                             nothing */
   int64_t record_steps;  /* 0: no adjoint; N > 0: checkpoint the first N steps for lbm_adjoint */
-  int32_t two_step;      /* two steps per launch (see lbm_steps_per_launch): 0 where the grid is
-                            large enough for it to pay, 1 wherever the layout allows, -1 never */
+  int32_t two_step;      /* A-B: several steps per kernel launch. 0: as many as are fastest for the
+                            grid, type and model; 1: the kernel that marches up the rows wherever
+                            lbm_steps_per_launch documents 2, else as 0; -1: one step per launch.
+                            AA: two reverse steps per launch of the adjoint, by the same values */
   int32_t walls;         /* 0: doubly periodic. 1: the columns x = 0 and x = nx - 1 are solid
                             nodes with fullway bounce-back (the isothermal shocktube, Sec. 5):
                             instead of colliding, a wall node sends each population back the way
@@ -192,14 +194,15 @@ lbm_status lbm_adjoint_populations(lbm_ctx* ctx, const void* d_fbarN, void* d_fb
 /* Completed time steps n, or -1 for a NULL context. */
 int64_t lbm_time(const lbm_ctx* ctx);
 
-/* Time steps one kernel launch of lbm_step advances for this context: 2 where the two-step
- * LDS-staged kernel applies, else 1 (-1 for a NULL context). It applies to the A-B pattern
- * (every storage type and model), no walls, nx a multiple of 512, more than 2^15 storage
- * positions and two_step >= 0; with two_step = 0 also only where the grid gives at least
- * three quarters of the device's compute units a block of 2 or more rows x 512 columns
- * (roughly (nx/512) floor(ny/2) >= 3 CUs/4), below which the single-step kernel is faster.
- * A pair of steps never passes over a checkpoint time of a recorded run. Results do not
- * depend on it: two steps in one launch are bit-identical to two single steps. */
+/* 2 on grids of at least two steps per kernel launch in pairs of rows, else 1 (-1 for a NULL
+ * context): the A-B pattern (every storage type and model), no walls, nx a multiple of 512, more
+ * than 2^15 storage positions and two_step >= 0; with two_step = 0 also only where the grid gives
+ * at least three quarters of the device's compute units a block of 2 or more rows x 512 columns
+ * (roughly (nx/512) floor(ny/2) >= 3 CUs/4). It classifies the grid and is not the length of a
+ * launch: with two_step >= 0 lbm_step takes 2 to 4 steps per launch on large A-B grids, more on
+ * small ones, up to all of a call's (at most 4096) on boxes that one block holds. A launch never
+ * passes over a checkpoint time of a recorded run. Results do not depend on it: several steps in
+ * one launch are bit-identical to single steps. */
 int32_t lbm_steps_per_launch(const lbm_ctx* ctx);
 
 const char* lbm_status_string(lbm_status s);

@@ -140,9 +140,9 @@ struct DeviceGuard {
 
 }  // namespace
 
-// Launch-bound grids: lbm_step replays a HIP graph of kGraphSteps step launches (an even
-// count, so the A-B buffer index and the AA phase parity return to their start values)
-// instead of launching every step from the host. Measured on MI355X: host-side launches
+// Launch-bound grids without a kernel of several steps (AA, two_step = -1): lbm_step replays a
+// HIP graph of kGraphSteps step launches (an even count, so the A-B buffer index and the AA phase
+// parity return to their start values) instead of launching every step from the host. Measured on MI355X: host-side launches
 // cost 3.3 us per step, graph replays 0.8 us; per-step time at 64^2 and 128^2 drops from
 // 3.3-3.5 to 2.5-3.1 us (the GPU's own dispatch of dependent kernels remains), at 256^2 it
 // no longer improves (FP64 got slower), so graphs are used up to 2^15 storage positions.
@@ -221,67 +221,51 @@ lbm_status check_ctx(const lbm_ctx* c) {
   return LBM_OK;
 }
 
-lbm_status step_from(lbm_ctx* c, const void* src, void* rec);
 lbm_status reduce_totals(lbm_ctx* c, double* partial, double* result, double out[3]);
 
-// One time step of the current pattern; rec != nullptr also writes the moment record. A
-// state held in a checkpoint slot is stepped out of place into population buffer 0.
-lbm_status do_step(lbm_ctx* c, void* rec) {
-  if (c->state_slot >= 0) return step_from(c, c->state(), rec);
+// ns steps in one launch from the current state into dst; rec (or null) receives the moment
+// records of the steps, one slot after the other. Out of place, except AA's own buffer (ns = 1).
+lbm_status launch_steps(lbm_ctx* c, int64_t ns, void* dst, void* rec) {
   return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
     using E = decltype(eng);
+    using T = typename E::T;
     hipError_t e;
-    if (c->p.pattern == LBM_AB) {
-      e = E::step(c->d, lbm::PH_AB, c->ws + c->plan.pop_off[c->cur], c->ws + c->plan.pop_off[1 - c->cur], rec,
-                  c->stream);
-      if (e == hipSuccess) c->cur ^= 1;
-    } else {
-      const int ph = (c->time & 1) ? lbm::PH_AA_ODD : lbm::PH_AA_EVEN;
-      e = E::step(c->d, ph, c->ws + c->plan.pop_off[0], c->ws + c->plan.pop_off[0], rec, c->stream);
-    }
-    if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("step kernel launch: ") + hipGetErrorString(e));
-    ++c->time;
-    return LBM_OK;
-  });
-}
-
-// Two A-B steps in one launch (the LDS-staged kernel) from src into population buffer dst,
-// which then holds the state; rec1/rec2 (or null) receive both steps' moment records.
-lbm_status do_step2(lbm_ctx* c, const void* src, int dst, void* rec1, void* rec2) {
-  return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
-    using E = decltype(eng);
-    const hipError_t e = E::step2(c->d, src, c->ws + c->plan.pop_off[dst], rec1, rec2, c->stream);
-    if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("two-step kernel launch: ") + hipGetErrorString(e));
-    c->cur = dst;
-    c->state_slot = -1;
-    c->time += 2;
-    return LBM_OK;
-  });
-}
-
-// One step (npair = 1) or an A-B pair (npair = 2) from the current state into checkpoint
-// slot k, which then holds the state. Out of place, so valid for both AA phases as well.
-lbm_status step_into_ckpt(lbm_ctx* c, int npair, int64_t k) {
-  return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
-    using E = decltype(eng);
-    hipError_t e;
-    if (npair == 2) {
-      e = E::step2(c->d, c->state(), c->ckpt(k), nullptr, nullptr, c->stream);
-    } else {
+    if (ns == 1) {
       const int ph = c->p.pattern == LBM_AB ? lbm::PH_AB : ((c->time & 1) ? lbm::PH_AA_ODD : lbm::PH_AA_EVEN);
-      e = E::step(c->d, ph, c->state(), c->ckpt(k), nullptr, c->stream);
+      e = E::step(c->d, ph, c->state(), dst, rec, c->stream);
+    } else {
+      const int64_t slot = int64_t(c->plan.rec_slot_bytes / sizeof(T));
+      e = c->d.tile.steps > 0 ? E::tile(c->d, int(ns), c->state(), dst, static_cast<T*>(rec), slot, c->stream)
+                              : E::march(c->d, int(ns), c->state(), dst, static_cast<T*>(rec), slot, c->stream);
     }
     if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("step kernel launch: ") + hipGetErrorString(e));
-    c->state_slot = k;
-    c->cur = 0;
-    c->time += npair;
     return LBM_OK;
   });
+}
+
+// ns steps into a population buffer, which then holds the state: the other one (A-B), AA's own,
+// or buffer 0 from a checkpoint slot.
+lbm_status do_steps(lbm_ctx* c, int64_t ns, void* rec) {
+  const int b = c->state_slot < 0 && c->p.pattern == LBM_AB ? 1 - c->cur : 0;
+  const lbm_status s = launch_steps(c, ns, c->ws + c->plan.pop_off[b], rec);
+  if (s != LBM_OK) return s;
+  c->cur = b;
+  c->state_slot = -1;
+  c->time += ns;
+  return LBM_OK;
+}
+
+// ns steps into checkpoint slot k, which then holds the state (the next step reads it there).
+lbm_status steps_into_ckpt(lbm_ctx* c, int64_t ns, int64_t k, void* rec) {
+  const lbm_status s = launch_steps(c, ns, c->ckpt(k), rec);
+  if (s != LBM_OK) return s;
+  c->state_slot = k;
+  c->cur = 0;
+  c->time += ns;
+  return LBM_OK;
 }
 
 bool is_small(const lbm_ctx* c) { return int64_t(c->d.pitch) * c->d.ny <= kGraphMaxPositions; }
-
-bool fused_ok(const lbm_ctx* c) { return c->d.fuse_rb > 0; }
 
 // The executable graph of kGraphSteps steps from the current buffer index (A-B) or phase
 // parity (AA). It is recorded by running the ordinary step launches against the private
@@ -297,7 +281,7 @@ lbm_status step_graph(lbm_ctx* c, hipGraphExec_t* out) {
     HIP_TRY(hipStreamBeginCapture(c->capture, hipStreamCaptureModeRelaxed));
     c->stream = c->capture;
     lbm_status s = LBM_OK;
-    for (int k = 0; k < kGraphSteps && s == LBM_OK; ++k) s = do_step(c, nullptr);
+    for (int k = 0; k < kGraphSteps && s == LBM_OK; ++k) s = do_steps(c, 1, nullptr);
     c->stream = user;
     c->time = t0;
     c->cur = cur0;
@@ -318,39 +302,17 @@ lbm_status step_graph(lbm_ctx* c, hipGraphExec_t* out) {
   return LBM_OK;
 }
 
-// One step whose input is another buffer (a checkpoint slot), written to population buffer
-// 0, which then holds the state. Valid for A-B and out of place for both AA phases: every
-// node writes all nine of its output locations.
-lbm_status step_from(lbm_ctx* c, const void* src, void* rec) {
-  return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
-    using E = decltype(eng);
-    const int ph = c->p.pattern == LBM_AB ? lbm::PH_AB : ((c->time & 1) ? lbm::PH_AA_ODD : lbm::PH_AA_EVEN);
-    const hipError_t e = E::step(c->d, ph, src, c->ws + c->plan.pop_off[0], rec, c->stream);
-    if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("step kernel launch: ") + hipGetErrorString(e));
-    c->cur = 0;
-    c->state_slot = -1;
-    ++c->time;
-    return LBM_OK;
-  });
-}
-
-lbm_status restore(lbm_ctx* c, int64_t slot, int64_t t) {
-  HIP_TRY(hipMemcpyAsync(c->ws + c->plan.pop_off[0], c->ckpt(slot), c->plan.pop_bytes, hipMemcpyDeviceToDevice, c->stream));
-  c->cur = 0;
-  c->state_slot = -1;
-  c->time = t;
-  return LBM_OK;
-}
-
 // Reverse sweep over the recorded run: on entry fbar(0) holds dJ/df^N; on exit fbar(*out_b)
 // holds dJ/df^0. Segment k (steps [k s, min((k+1) s, N))) is recomputed from its checkpoint
-// while recording moments (two steps per launch where the two-step kernel applies; the
-// first launch reads the checkpoint slot directly, so no copy restores it), then traversed
-// backwards with the adjoint kernel. The last segment's moments are usually still in the
+// while recording moments (several steps per launch where the run's plan says so; the first
+// launch reads the checkpoint slot directly, so no copy restores it), then traversed
+// backwards with the adjoint kernels. The last segment's moments are usually still in the
 // slots from the forward run, which recorded them; with a single segment (stride >= N)
-// nothing is recomputed at all.
+// nothing is recomputed at all. The state at N is in checkpoint slot nck, where the forward run
+// left it, and is the current state again at the end.
 lbm_status sweep(lbm_ctx* c, int* out_b) {
   const int64_t N = c->p.record_steps, s = c->plan.stride;
+  const lbm::RunDesc& d = c->d;
   int b = 0;
   for (int64_t k = c->plan.nck - 1; k >= 0; --k) {
     const int64_t t0 = k * s, t1 = std::min(t0 + s, N);
@@ -360,44 +322,43 @@ lbm_status sweep(lbm_ctx* c, int* out_b) {
       // that fails part-way never leaves the flag on overwritten slots).
       c->last_seg_recorded = false;
       c->time = t0;
-      const bool fz = fused_ok(c);
-      st = (fz && t1 - t0 >= 2) ? do_step2(c, c->ckpt(k), 0, c->rec_slot(0), c->rec_slot(1))
-                                : step_from(c, c->ckpt(k), c->rec_slot(0));
-      if (st != LBM_OK) return st;
+      c->state_slot = k;
       while (c->time < t1) {
-        const int64_t j = c->time - t0;
-        st = (fz && t1 - c->time >= 2) ? do_step2(c, c->state(), 1 - c->cur, c->rec_slot(j), c->rec_slot(j + 1))
-                                       : do_step(c, c->rec_slot(j));
+        st = do_steps(c, lbm::steps_ahead(t1 - c->time, d.march.steps, d.tile.steps), c->rec_slot(c->time - t0));
         if (st != LBM_OK) return st;
       }
     }
-    // Reverse steps t = t1 - 1 .. t0, two per launch (t and t - 1) where the two-step adjoint
-    // kernel applies.
+    // Reverse steps t = t1 - 1 .. t0, several per launch (t, t - 1, ...) where the plan says so.
     for (int64_t t = t1 - 1; t >= t0;) {
-      const bool pair = c->d.adj_rb > 0 && t - 1 >= t0;
+      const int64_t m = t - t0 + 1;
+      const int64_t ns = c->p.pattern == LBM_AB ? lbm::steps_ahead(m, d.adj_march.steps, d.adj_tile.steps)
+                                                : (d.adj_rb > 0 && m >= 2 ? 2 : 1);
       st = dispatch(c->p.storage, [&](auto eng) -> lbm_status {
         using E = decltype(eng);
         using T = typename E::T;
         const T* in = static_cast<const T*>(c->fbar(b));
         T* out = static_cast<T*>(c->fbar(1 - b));
-        hipError_t e = pair ? E::adjoint_step2(c->d, in, out, static_cast<const T*>(c->rec_slot(t - t0)),
-                                               static_cast<const T*>(c->rec_slot(t - 1 - t0)), c->stream)
-                            : E::adjoint_step(c->d, in, out, static_cast<const T*>(c->rec_slot(t - t0)), c->stream);
+        const T* rec = static_cast<const T*>(c->rec_slot(t - t0));
+        const int64_t slot = int64_t(c->plan.rec_slot_bytes / sizeof(T));
+        hipError_t e;
+        if (ns == 1) e = E::adjoint_step(d, in, out, rec, c->stream);
+        else if (c->p.pattern != LBM_AB) e = E::adjoint_step2(d, in, out, rec, rec - slot, c->stream);
+        else if (d.adj_tile.steps > 0) e = E::adjoint_tile(d, int(ns), in, out, rec, slot, c->stream);
+        else e = E::adjoint_march(d, int(ns), in, out, rec, slot, c->stream);
         if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("adjoint kernel launch: ") + hipGetErrorString(e));
         return LBM_OK;
       });
       if (st != LBM_OK) return st;
       b ^= 1;
-      t -= pair ? 2 : 1;
+      t -= ns;
     }
   }
+  c->time = N;
+  c->state_slot = c->plan.nck;
+  c->cur = 0;
   *out_b = b;
   return LBM_OK;
 }
-
-// True when the reverse sweep will recompute nothing (one segment, its moments kept by the
-// forward run): the state at N is then never touched and needs no saving and restoring.
-bool state_stays(const lbm_ctx* c) { return c->plan.nck == 1 && c->last_seg_recorded; }
 
 lbm_status check_adjoint_ready(const lbm_ctx* c) {
   if (c->p.record_steps <= 0) return fail(LBM_ERR_STATE, "context was created with record_steps = 0");
@@ -468,13 +429,15 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t workspace_byt
     d.tau = p->nu / p->theta + 0.5;  // nu = theta (tau - 1/2)
     d.model = p->model;
     d.walls = p->walls;
-    d.wt_stores = int64_t(lbm::Q) * d.pitch * d.ny * int64_t(storage_size(p->storage)) >= lbm::kWriteThroughBytes;
-    d.fuse_rb = (p->pattern == LBM_AB && p->two_step >= 0 && !p->walls)
-                    ? dispatch_int(p->storage, [&](auto eng) { return decltype(eng)::fuse_row_blocks(d, p->two_step); })
-                    : 0;
-    d.adj_rb = (p->record_steps > 0 && p->two_step >= 0)
-                   ? dispatch_int(p->storage, [&](auto eng) { return decltype(eng)::adjoint_row_blocks(d, p->two_step); })
-                   : 0;
+    d.contig = p->pattern == LBM_AB;
+    const int64_t population_bytes =
+        int64_t(lbm::Q) * d.pitch * d.ny * int64_t(storage_size(p->storage)) * (d.contig ? 2 : 1);
+    d.stream = population_bytes >= (d.contig ? lbm::kStreamBytesAB : lbm::kStreamBytesAA);
+    d.xcd = population_bytes <= (storage_size(p->storage) == 2 ? lbm::kXcdBytes16 : lbm::kXcdBytes);
+    dispatch_int(p->storage, [&](auto eng) {
+      decltype(eng)::plan(d, p->two_step, plan.stride);
+      return 0;
+    });
     c->time = 0;
     c->cur = 0;
     c->rec_valid = p->record_steps > 0;
@@ -501,55 +464,42 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
     if (n < 0) return fail(LBM_ERR_INVALID_ARGUMENT, "n must be >= 0");
     DeviceGuard g(c->device);
     const int64_t N = c->p.record_steps;
-    const bool small = is_small(c);
-    const bool fused = !small && fused_ok(c);
+    const bool small = is_small(c) && c->d.tile.steps == 0 && c->d.march.steps == 0;
     const int64_t t_last = N > 0 ? (c->plan.nck - 1) * c->plan.stride : 0;  // last segment's start
     for (int64_t k = 0; k < n;) {
       const bool recording = N > 0 && c->rec_valid && c->time < N;
+      if (!recording) {
+        if (small && c->state_slot < 0 && n - k >= kGraphSteps) {
+          hipGraphExec_t ge = nullptr;
+          s = step_graph(c, &ge);
+          if (s != LBM_OK) return s;
+          HIP_TRY(hipGraphLaunch(ge, c->stream));
+          c->time += kGraphSteps;  // even count: buffer index and phase parity unchanged
+          k += kGraphSteps;
+          continue;
+        }
+        const int64_t ns = lbm::steps_ahead(n - k, c->d.march.steps, c->d.tile.steps);
+        s = do_steps(c, ns, nullptr);
+        if (s != LBM_OK) return s;
+        k += ns;
+        continue;
+      }
       // The checkpoint of a checkpoint time: normally the step that ended here wrote the
       // state into its slot; otherwise (a state replaced at t = 0) it is copied.
-      if (recording && c->time % c->plan.stride == 0 && c->state_slot != c->time / c->plan.stride)
-        HIP_TRY(hipMemcpyAsync(c->ckpt(c->time / c->plan.stride), c->state(), c->plan.pop_bytes,
-                               hipMemcpyDeviceToDevice, c->stream));
-      // Steps of the last segment keep their moments for the reverse sweep (slot t - t_last).
-      const bool keep = recording && c->time >= t_last;
-      // A pair of steps must not pass over a checkpoint time of the recorded window, nor
-      // over its end while keeping moments.
-      const int64_t mid = c->time + 1;
-      const bool pair =
-          fused && n - k >= 2 && !(recording && mid < N && mid % c->plan.stride == 0) && !(keep && mid >= N);
-      // A step that ends at a later checkpoint time of the window writes into its slot (never
-      // while keeping moments: the last segment holds no further checkpoint time).
-      const int64_t end = c->time + (pair ? 2 : 1);
-      const bool into_ckpt = recording && end < N && end % c->plan.stride == 0;
-      if (into_ckpt) {
-        s = step_into_ckpt(c, pair ? 2 : 1, end / c->plan.stride);
-        if (s != LBM_OK) return s;
-        k += pair ? 2 : 1;
-        continue;
-      }
-      if (pair) {
-        const int64_t j = c->time - t_last;
-        s = keep ? do_step2(c, c->state(), 1 - c->cur, c->rec_slot(j), c->rec_slot(j + 1))
-                 : do_step2(c, c->state(), 1 - c->cur, nullptr, nullptr);
-        if (s != LBM_OK) return s;
-        if (keep && c->time == N) c->last_seg_recorded = true;
-        k += 2;
-        continue;
-      }
-      if (small && !recording && c->state_slot < 0 && n - k >= kGraphSteps) {
-        hipGraphExec_t ge = nullptr;
-        s = step_graph(c, &ge);
-        if (s != LBM_OK) return s;
-        HIP_TRY(hipGraphLaunch(ge, c->stream));
-        c->time += kGraphSteps;  // even count: buffer index and phase parity unchanged
-        k += kGraphSteps;
-        continue;
-      }
-      s = do_step(c, keep ? c->rec_slot(c->time - t_last) : nullptr);
+      const int64_t seg = c->time / c->plan.stride;
+      if (c->time % c->plan.stride == 0 && c->state_slot != seg)
+        HIP_TRY(hipMemcpyAsync(c->ckpt(seg), c->state(), c->plan.pop_bytes, hipMemcpyDeviceToDevice, c->stream));
+      // A launch stays within its checkpoint segment. Steps of the last segment keep their
+      // moments for the reverse sweep (slot t - t_last). A launch that ends the segment writes
+      // the state into the next checkpoint's slot, at t = N into the slot after the last one.
+      const int64_t seg_end = std::min((seg + 1) * c->plan.stride, N);
+      const bool keep = c->time >= t_last;
+      const int64_t ns = lbm::steps_ahead(std::min(n - k, seg_end - c->time), c->d.march.steps, c->d.tile.steps);
+      void* rec = keep ? c->rec_slot(c->time - t_last) : nullptr;
+      s = c->time + ns == seg_end ? steps_into_ckpt(c, ns, seg + 1, rec) : do_steps(c, ns, rec);
       if (s != LBM_OK) return s;
       if (keep && c->time == N) c->last_seg_recorded = true;
-      ++k;
+      k += ns;
     }
     return LBM_OK;
   });
@@ -703,14 +653,10 @@ lbm_status lbm_adjoint(lbm_ctx* c, const void* d_rho_bar, const void* d_ux_bar, 
     if (!d_ux_bar || !d_uy_bar || !d_ux0_bar || !d_uy0_bar)
       return fail(LBM_ERR_INVALID_ARGUMENT, "adjoint: velocity adjoint pointers are required");
     DeviceGuard g(c->device);
-    const int64_t N = c->p.record_steps;
-    const bool in_place = state_stays(c);
-    if (!in_place)
-      HIP_TRY(hipMemcpyAsync(c->ckpt(c->plan.nck), c->state(), c->plan.pop_bytes, hipMemcpyDeviceToDevice, c->stream));
     return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
       using E = decltype(eng);
       using T = typename E::T;
-      hipError_t e = E::seed(c->d, c->layout(N), c->state(), static_cast<const T*>(d_rho_bar),
+      hipError_t e = E::seed(c->d, c->layout(c->time), c->state(), static_cast<const T*>(d_rho_bar),
                              static_cast<const T*>(d_ux_bar), static_cast<const T*>(d_uy_bar),
                              static_cast<T*>(c->fbar(0)), c->stream);
       if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("seed kernel launch: ") + hipGetErrorString(e));
@@ -720,7 +666,7 @@ lbm_status lbm_adjoint(lbm_ctx* c, const void* d_rho_bar, const void* d_ux_bar, 
       e = E::ic_adjoint(c->d, c->layout(0), c->ckpt(0), static_cast<const T*>(c->fbar(b)), static_cast<T*>(d_ux0_bar),
                         static_cast<T*>(d_uy0_bar), c->stream);
       if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("initial-condition adjoint launch: ") + hipGetErrorString(e));
-      return in_place ? LBM_OK : restore(c, c->plan.nck, N);
+      return LBM_OK;
     });
   });
 }
@@ -733,10 +679,6 @@ lbm_status lbm_adjoint_populations(lbm_ctx* c, const void* d_fbarN, void* d_fbar
     if (s != LBM_OK) return s;
     if (!d_fbarN || !d_fbar0) return fail(LBM_ERR_INVALID_ARGUMENT, "adjoint: population pointers are required");
     DeviceGuard g(c->device);
-    const int64_t N = c->p.record_steps;
-    const bool in_place = state_stays(c);
-    if (!in_place)
-      HIP_TRY(hipMemcpyAsync(c->ckpt(c->plan.nck), c->state(), c->plan.pop_bytes, hipMemcpyDeviceToDevice, c->stream));
     return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
       using E = decltype(eng);
       using T = typename E::T;
@@ -747,14 +689,14 @@ lbm_status lbm_adjoint_populations(lbm_ctx* c, const void* d_fbarN, void* d_fbar
       if (st != LBM_OK) return st;
       e = E::fbar_export(c->d, static_cast<const T*>(c->fbar(b)), static_cast<T*>(d_fbar0), c->stream);
       if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("adjoint export launch: ") + hipGetErrorString(e));
-      return in_place ? LBM_OK : restore(c, c->plan.nck, N);
+      return LBM_OK;
     });
   });
 }
 
 int32_t lbm_steps_per_launch(const lbm_ctx* c) {
   if (!c) return -1;
-  return (!is_small(c) && fused_ok(c)) ? 2 : 1;
+  return (!is_small(c) && c->d.pair) ? 2 : 1;
 }
 
 int64_t lbm_time(const lbm_ctx* c) { return c ? c->time : -1; }

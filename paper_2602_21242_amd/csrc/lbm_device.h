@@ -75,8 +75,8 @@ template <> struct StorageTraits<_Float16> {
   using T = float;
   // Loaded populations wait for their use as zero-extended 32-bit bit patterns. Kept as
   // _Float16 values, the compiler packs pairs of them into one register right after the
-  // loads, which stalls on the loads there instead of at their first use (the two-step
-  // kernel's loads of the next row then no longer overlap the barrier and phase B).
+  // loads, which stalls on the loads there instead of at their first use (a marching kernel's
+  // loads of the next row then no longer overlap the collisions of this one).
   using Raw = uint32_t;
   static __device__ __forceinline__ float load(_Float16 v) { return float(v); }
   static __device__ __forceinline__ float load_raw(uint32_t r) {
@@ -109,9 +109,11 @@ template <> struct StorageTraits<bf16_t> {
 // error on the 8192^2 turbulence after 5000 steps fell from 5.6e-2 to 6.4e-3, but its
 // throughput from 197 to 165 GLUPS (its rounding is a conversion and a shift that no FMA
 // absorbs), below FP16 with the same form, which is ten times as accurate.
-template <class S> struct ConserveMode { static constexpr int value = 0; };
-template <> struct ConserveMode<float> { static constexpr int value = 1; };
-template <> struct ConserveMode<_Float16> { static constexpr int value = 2; };
+// LBGK with FP16 storage takes the direct form in mode 2 as well, its last FMA rounded straight
+// to FP16; 3 (runs with walls) is 2 with LBGK's populations rounded to FP32 first.
+template <class S, bool WALLS = false> struct ConserveMode { static constexpr int value = 0; };
+template <bool WALLS> struct ConserveMode<float, WALLS> { static constexpr int value = 1; };
+template <bool WALLS> struct ConserveMode<_Float16, WALLS> { static constexpr int value = WALLS ? 3 : 2; };
 
 // ---------------------------------------------------------------------------------------
 // Per-run constants, computed on the host in FP64 and rounded to the compute type.
@@ -140,7 +142,7 @@ constexpr int NREC = 5;
 // a * b + c with one rounding. The collision writes every fused product this way and turns
 // the compiler's own contraction off: which of two products feeding a sum the compiler fuses
 // depends on how many other uses each has, so a kernel that needs only some of the outputs
-// (the two-step kernel's halo columns) rounded the ones it kept differently (LBGK: 20 % of
+// (halo nodes of a kernel of several steps) rounded the ones it kept differently (LBGK: 20 % of
 // the populations of a 2048 x 130 grid differed after two launches).
 template <class T>
 __device__ __forceinline__ T fmad(T a, T b, T c) {
@@ -156,6 +158,14 @@ template <>
 __device__ __forceinline__ float recip<float>(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.0f), r);
+}
+
+// a * b + c rounded once, to FP16. Left to the compiler, a conversion after an FMA is fused with
+// it or not depending on what else happens to the result.
+__device__ __forceinline__ _Float16 fma_f16(float a, float b, float c) {
+  uint32_t r;
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return __builtin_bit_cast(_Float16, uint16_t(r));
 }
 
 // Post-collision populations 1, 2 (with MOMENTUM) and 0 recomputed from the node's mass excess
@@ -183,8 +193,7 @@ __device__ __forceinline__ void conserve(T drho, T jx, T jy, T out[Q]) {
 // populations against the FP64 run after 100 / 1000 / 2000 / 3000 / 5000 steps): direct form
 // 4.8e-4 / 1.06e-3 / - / - / 2.04e-3; diagonals rounded first and the residual split over each
 // axis' pair 4.5e-4 / 6.8e-4 / 9.4e-4 / 1.08e-3 / 1.27e-3; this 3.4e-4 / 3.9e-4 / 4.3e-4 /
-// 4.7e-4 / 5.3e-4, in the same time per launch as the axis-pair split (737 us per 8192^2
-// two-step launch, interleaved on one machine). Not for LBGK, which keeps every
+// 4.7e-4 / 5.3e-4, in the same time as the axis-pair split. Not for LBGK, which keeps every
 // non-equilibrium moment and whose error is not carried by the momentum: with this its error
 // after 5000 steps rose from 3.3e-3 to 3.7e-3, at 9 % of its throughput.
 template <bool MOMENTUM>
@@ -220,9 +229,8 @@ __device__ __forceinline__ void conserve_fp16(float drho, float jx, float jy, fl
 // sum c^2 Phi = theta + u^2, and c^3 = c, c^4 = c^2 on {-1, 0, 1}. The final assembly is
 // g*_i = Phi_y (K_x + Phi_x v_i) + c_i with K_x = Phi_x (drho + ...) + rho0 d_x formed once per
 // value of c_x: three FMAs per population. (The longer form P_i (drho + t_i) + E_i + Psi_i,
-// P_i = Phi_x Phi_y, needs about six; with the two-step kernel's buffer accesses the short form
-// measured faster for every storage type on MI355X: FP32 pair 150.1 -> 153.6 GLUPS at 4096^2,
-// 152.2 -> 156.8 at 8192^2, FP64 pair 77.3 -> 78.5.) Every fused product is written out with
+// P_i = Phi_x Phi_y, needs about six; in a kernel of two steps the short form measured 2-3 % faster for
+// every storage type on MI355X.) Every fused product is written out with
 // fmad, in the places where the compiler's own contraction had put them, with contraction off,
 // so that the rounding of each output does not depend on which other outputs a caller uses.
 //
@@ -282,6 +290,8 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
       const T rdy = cx(i) == 0 ? sel(cy(i), a0m, a00, a0p) : sel(cy(i), a1m, a10, a1p);
       const T feqs = fmad(hy, sel(cx(i), Km, K0, Kp), rdy);
       out[i] = fmad(k.omb, g[i] - feqs, feqs);
+      if constexpr (CONSERVE == 2) out[i] = float(fma_f16(k.omb, g[i] - feqs, feqs));
+      if constexpr (CONSERVE == 3) asm("" : "+v"(out[i]));
     }
     if constexpr (CONSERVE == 1) conserve<T, true>(drho, jx, jy, out);
     if (rec) rec[3] = rec[4] = T(0);
@@ -349,7 +359,7 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
   // g*_i = (f_i^eq - w_i rho0) + (1 - 1/tau)(f_i^OReg + Psi_i)
   //      = Phi_y (K_x + Phi_x (C_x Y2 - Y1)) + (rho0 r_x d_y + Psi_i), with
   // drho + t_i = X1 - Y1 + C_x Y2 and K_x = Phi_x X1 + rho0 d_x per value of c_x.
-  // Which product of K_x is fused: measured on MI355X (two-step kernel, us per launch,
+  // Which product of K_x is fused: measured on MI355X (a kernel of two steps, us per launch,
   // interleaved on one machine), rho0 d_x fused is the faster choice for FP32 storage (8192^2:
   // 838-850 against 936 with Phi_x X1 fused, whose schedule there falls into a slower memory
   // access pattern; 4096^2 209-211 against 207), Phi_x X1 fused for the others (FP16 8192^2 738
@@ -368,7 +378,7 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
     out[i] = fmad(hy, fmad(hx, v, sel(cx(i), Km, K0, Kp)), fmad(rr, dy, Psi[i]));
   }
   if constexpr (CONSERVE == 1) conserve<T, MODEL != M_UC>(drho, jx, jy, out);
-  if constexpr (CONSERVE == 2) conserve_fp16<MODEL != M_UC>(drho, jx, jy, out);
+  if constexpr (CONSERVE >= 2) conserve_fp16<MODEL != M_UC>(drho, jx, jy, out);
 }
 
 // ---------------------------------------------------------------------------------------

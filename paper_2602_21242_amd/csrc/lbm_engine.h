@@ -8,28 +8,43 @@
 #include <stdint.h>
 
 #include "lbm_device.h"
+#include "lbm_plan.h"
 
 namespace lbm {
 
-// Everything a launcher needs to know about a run (host side).
-// Every buffer is row-interleaved and lane-strided within a row: element (i, x, y) at
-// y * row_stride + i * pitch + pos(x), pos(x) = (x mod S) * 64 + floor(x / S), S = pitch / 64.
+// Everything a launcher needs to know about a run (host side). Element (i, x, y) of a buffer is
+// at y * row_stride + i * pitch + pos(x): contiguous rows (contig, A-B) have pos(x) = x,
+// lane-strided ones (AA) pos(x) = (x mod S) * 64 + floor(x / S), S = pitch / 64.
 struct RunDesc {
   int nx, ny, pitch;  // pitch = 64 ceil(nx / 64)
   int64_t rs;         // row stride of the populations and of fbar (9 * pitch)
   int64_t rs_rec;     // row stride of a recorded-moment slot (5 * pitch)
   double theta, nu, rho0, tau;
   int model;         // M_BGK ... M_COMPLETE
-  int fuse_rb;       // row blocks of the two-step kernel; 0: one step per launch
-  int adj_rb;        // row blocks of the two-step adjoint kernel; 0: one reverse step per launch
+  int contig;        // 1: contiguous rows (A-B), 0: lane-strided rows (AA)
+  int pair;          // lbm_steps_per_launch reports 2
+  int adj_rb;        // AA: row blocks of the two-step adjoint kernel; 0: one reverse step per launch
   int walls;         // 1: solid bounce-back columns at x = 0 and x = nx - 1 (A-B only)
-  int wt_stores;     // 1: the step kernels' stores carry the SC1 scope bit (population buffers
-                     // larger than the last-level cache; see kAuxStore)
+  int xcd;           // 1: the single-step kernel's blocks run in XCD order (see kXcdBytes)
+  int stream;        // 1: the single-step kernel's accesses bypass the caches (see kAuxStoreWT)
+  // A-B: how several forward (march, tile) and reverse (adj_*) steps are launched; steps = 0
+  // where a kernel does not apply or is not the fastest.
+  MarchPlan march, adj_march;
+  TilePlan tile, adj_tile;
 };
 
-// Population-buffer size from which the step kernels' stores are written through (SC1): the
-// read and the written buffer of an A-B step then no longer fit the 256 MB last-level cache.
-constexpr int64_t kWriteThroughBytes = int64_t(128) << 20;
+// Where a run's population buffers (both of A-B, the one of AA) stop fitting the 256 MB last-level
+// cache well enough for plain accesses to win, us per step plain/streaming: A-B FP32 302 MB
+// 40/48, 319 MB 48/53, 355 MB 61/58, FP16 325 MB 61/58, FP64 332 MB 56/54; AA FP32 350 MB 120/146,
+// BF16 302 MB 87/98, FP64 295 MB 87/105, 382 MB 131/123. A-B's write-once streams evict each
+// other earlier than AA's reads and writes of the same lines.
+constexpr int64_t kStreamBytesAB = int64_t(304) << 20, kStreamBytesAA = int64_t(352) << 20;
+// Up to here the step's blocks run in XCD order, which keeps a row's neighbours of the previous
+// step in the same L2: AA FP32 1000^2 11.7 -> 10.4 us, 2700^2 (267 MB) 68 -> 61, A-B FP32 1700^2
+// (212 MB) 27.1 -> 25.2, 2048^2 (302 MB) 40 -> 44. 16-bit storage, whose steps are bound by their
+// instructions, gains at small grids alone: BF16 AA 1000^2 (18 MB) 10.5 -> 7.8, FP16 A-B 1000^2
+// (37 MB) 10.8 -> 8.6, 1500^2 (83 MB) 16.1 -> 16.9, AA 3000^2 (162 MB) 44 -> 49.
+constexpr int64_t kXcdBytes = int64_t(256) << 20, kXcdBytes16 = int64_t(64) << 20;
 
 // State layout at a given time: f_i(x) = buf[swap ? opp(i) : i][x - shift c_i].
 struct LayoutSel {
@@ -42,13 +57,15 @@ template <class S>
 struct Engine {
   using T = typename StorageTraits<S>::T;
   static hipError_t step(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st);
-  // Two A-B steps in one launch (src and dst distinct) over d.fuse_rb row blocks, recording
-  // both steps' moments to rec1/rec2 when they are not null. fuse_row_blocks gives the row
-  // blocks for the current device (mode 0: only where it pays, 1: wherever the layout and
-  // the storage type allow it), or 0 for one step per launch.
-  static int fuse_row_blocks(const RunDesc& d, int mode);
-  static int adjoint_row_blocks(const RunDesc& d, int mode);
-  static hipError_t step2(const RunDesc& d, const void* src, void* dst, void* rec1, void* rec2, hipStream_t st);
+  // ns A-B steps in one launch, out of place, by the marching or the tile kernel of the run's
+  // plan; rec, when not null, receives the moments of step s at rec + s * rec_slot.
+  static hipError_t march(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
+                          hipStream_t st);
+  static hipError_t tile(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
+                         hipStream_t st);
+  // Fills the run's plans for the current device (mode: lbm_params.two_step; segment: steps of a
+  // recorded run's checkpoint segments, 0: no recording).
+  static void plan(RunDesc& d, int mode, int64_t segment);
   static hipError_t init(const RunDesc& d, LayoutSel L, void* buf, const double* rho, const double* ux,
                          const double* uy, hipStream_t st);
   static hipError_t get(const RunDesc& d, LayoutSel L, const void* buf, bool out_f64, void* out, hipStream_t st);
@@ -62,10 +79,15 @@ struct Engine {
   static hipError_t fbar_import(const RunDesc& d, const T* dense, T* fbar, hipStream_t st);
   static hipError_t fbar_export(const RunDesc& d, const T* fbar, T* dense, hipStream_t st);
   static hipError_t adjoint_step(const RunDesc& d, const T* fbar_next, T* fbar, const T* rec, hipStream_t st);
-  // Two reverse steps (fbar^{n+1} -> fbar^{n-1}) over d.adj_rb row blocks; rec_hi holds the
+  // AA: two reverse steps (fbar^{n+1} -> fbar^{n-1}) over d.adj_rb row blocks; rec_hi holds the
   // records of step n, rec_lo those of step n - 1.
   static hipError_t adjoint_step2(const RunDesc& d, const T* fbar_next, T* fbar, const T* rec_hi, const T* rec_lo,
                                   hipStream_t st);
+  // A-B: ns reverse steps in one launch, reverse step s with the moments at rec - s * rec_slot.
+  static hipError_t adjoint_march(const RunDesc& d, int ns, const T* fbar_next, T* fbar, const T* rec,
+                                  int64_t rec_slot, hipStream_t st);
+  static hipError_t adjoint_tile(const RunDesc& d, int ns, const T* fbar_next, T* fbar, const T* rec,
+                                 int64_t rec_slot, hipStream_t st);
   static hipError_t ic_adjoint(const RunDesc& d, LayoutSel L, const void* buf0, const T* fbar, T* uxb, T* uyb,
                                hipStream_t st);
 };

@@ -4,7 +4,9 @@
 #include <algorithm>
 
 #include "lbm_engine.h"
+#include "lbm_march.h"
 #include "lbm_step.h"
+#include "lbm_tile.h"
 
 namespace lbm {
 
@@ -12,16 +14,17 @@ namespace lbm {
 
 __host__ __device__ __forceinline__ int row_pos(int x, int S) { return (x % S) * kLanes + x / S; }
 
-inline Geo make_geo(const RunDesc& d, int npt) {
+inline Geo make_geo(const RunDesc& d, int npt, int block_threads = kBlock) {
   Geo g;
   g.nx = d.nx;
   g.ny = d.ny;
   g.S = d.pitch / kLanes;
   g.ps = d.pitch;
   g.rs = d.rs;
-  const int groups_per_block = (kBlock / kLanes) * npt;
+  const int groups_per_block = (block_threads / kLanes) * npt;
   g.nseg = (g.S + groups_per_block - 1) / groups_per_block;
   g.plast = row_pos(d.nx - 1, g.S);
+  g.xcd = d.xcd;
   return g;
 }
 
@@ -38,18 +41,20 @@ __device__ __forceinline__ bool storage_node(int64_t t, const RunDesc& d, int& y
   if (t >= int64_t(d.pitch) * d.ny) return false;
   y = int(t / d.pitch);
   q = int(t - int64_t(y) * d.pitch);
-  x = (q % kLanes) * (d.pitch / kLanes) + q / kLanes;
+  x = d.contig ? q : (q % kLanes) * (d.pitch / kLanes) + q / kLanes;
   return x < d.nx;
 }
 
-// Buffer index of population i of node (x, y) under a stored-state convention L.
+// Buffer index of population i of node (x, y) under a stored-state convention L (with contiguous
+// rows, C, always A-B's).
+template <bool C>
 __device__ __forceinline__ int64_t layout_index(int i, int x, int y, const RunDesc& d, LayoutSel L) {
-  const int slot = L.swap ? opp(i) : i;
-  int xs = x - L.shift * cx(i);
+  const int slot = !C && L.swap ? opp(i) : i, shift = C ? 1 : L.shift;
+  int xs = x - shift * cx(i);
   xs = xs < 0 ? xs + d.nx : (xs >= d.nx ? xs - d.nx : xs);
-  int ys = y - L.shift * cy(i);
+  int ys = y - shift * cy(i);
   ys = ys < 0 ? ys + d.ny : (ys >= d.ny ? ys - d.ny : ys);
-  return int64_t(ys) * d.rs + slot * d.pitch + row_pos(xs, d.pitch / kLanes);
+  return int64_t(ys) * d.rs + slot * d.pitch + (C ? xs : row_pos(xs, d.pitch / kLanes));
 }
 
 // Buffer index of entry i of node (x, y) stored at in-row position q (no shift).
@@ -59,130 +64,163 @@ __device__ __forceinline__ int64_t local_index(int i, int q, int y, const RunDes
 
 // --- per-node auxiliary kernels --------------------------------------------------------------
 
-// The per-node auxiliary kernels exchange the dense [ny][nx] fields through LDS: a
-// block takes kTileGroups groups of one row (one wavefront per group, lane l holding node
-// x = l S + s as in the storage layout), and the dense entries of those nodes -- kTileGroups
-// consecutive x per lane -- are read or written by consecutive threads. (Indexing the dense
-// fields by each thread's own node strides a wavefront's accesses by S elements.)
+// The per-node auxiliary kernels exchange the dense [ny][nx] fields with lane-strided rows
+// through LDS: a block takes kTileGroups groups of one row (one wavefront per group, lane l
+// holding node x = l S + s as in the storage layout), and the dense entries of those nodes --
+// kTileGroups consecutive x per lane -- are read or written by consecutive threads. (Indexing
+// the dense fields by each thread's own node strides a wavefront's accesses by S elements.) With
+// contiguous rows a thread's storage node and its dense entry are the same node.
 constexpr int kTileGroups = kBlock / kLanes;
 inline dim3 tile_grid(const RunDesc& d) {
   const int S = d.pitch / kLanes;
   return dim3(unsigned((S + kTileGroups - 1) / kTileGroups), unsigned(std::min(d.ny, kRowsY)),
               unsigned((d.ny + kRowsY - 1) / kRowsY));
 }
-// A block's row y, its first group s0 and the group count S; for the thread's dense entry
-// the lane lt, the group offset jt and the node x (-1 outside the row or in the padding).
+// A block's row y; the thread's wavefront w, lane, storage node x at in-row position q (-1
+// outside the row or in the padding); its dense entry, node xt (-1: none), held by lane lt of
+// wavefront jt.
 struct Tile {
-  int y, s0, S, lt, jt, xt;
+  int y, w, lane, x, q, lt, jt, xt;
 };
+template <bool C>
 __device__ __forceinline__ Tile tile_of(const RunDesc& d) {
   Tile t;
   t.y = int(blockIdx.z) * kRowsY + int(blockIdx.y);
-  t.S = d.pitch / kLanes;
-  t.s0 = int(blockIdx.x) * kTileGroups;
+  t.w = int(threadIdx.x) / kLanes;
+  t.lane = int(threadIdx.x) % kLanes;
+  const int S = d.pitch / kLanes, s0 = int(blockIdx.x) * kTileGroups;
+  const int s = s0 + t.w;
+  t.q = s * kLanes + t.lane;
+  if constexpr (C) {
+    t.x = t.q < d.nx ? t.q : -1;
+    t.jt = t.w;
+    t.lt = t.lane;
+    t.xt = t.x;
+    return t;
+  }
+  t.x = t.lane * S + s;
+  if (s >= S || t.x >= d.nx) t.x = -1;
   t.lt = int(threadIdx.x) / kTileGroups;
   t.jt = int(threadIdx.x) % kTileGroups;
-  const int x = t.lt * t.S + t.s0 + t.jt;
-  t.xt = (t.s0 + t.jt < t.S && x < d.nx) ? x : -1;
+  const int x = t.lt * S + s0 + t.jt;
+  t.xt = (s0 + t.jt < S && x < d.nx) ? x : -1;
   return t;
 }
 
+// Values of the block's nodes between their dense entries and their storage nodes: through LDS
+// with lane-strided rows, the thread's own with contiguous ones.
+template <bool C, class T, int N>
+struct Exchange {
+  T v[N];
+  __device__ __forceinline__ void swap(const Tile& t, T (*sh)[kTileGroups][kLanes], bool to_storage) {
+    if constexpr (!C) {
+      const int w0 = to_storage ? t.jt : t.w, l0 = to_storage ? t.lt : t.lane;
+      const int w1 = to_storage ? t.w : t.jt, l1 = to_storage ? t.lane : t.lt;
+#pragma unroll
+      for (int c = 0; c < N; ++c) sh[c][w0][l0] = v[c];
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < N; ++c) v[c] = sh[c][w1][l1];
+    }
+  }
+};
 
 // f^0 = f^eq(rho, u) of the guided equilibrium (eq:guidedEq), stored shifted, computed from
 // the caller's FP64 fields in FP64 as drho Phi_x Phi_y + rho0 (d_x Phi_y + r_x d_y) (no
-// cancellation against w_i rho0) and rounded once to the storage type.
-template <class S>
+// cancellation against w_i rho0) and rounded once to the storage type. Here and in the export
+// and import the fused products are written out: left to the compiler they changed with the code
+// around them, and an unstable flow amplifies the last bit of its initial state.
+template <class S, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_init(S* buf, RunDesc d, LayoutSel L, const double* rho, const double* ux, const double* uy) {
+#pragma clang fp contract(off)
   using Tr = StorageTraits<S>;
-  __shared__ double sh[3][kTileGroups][kLanes];
-  const Tile tl = tile_of(d);
+  __shared__ double sh[C ? 1 : 3][kTileGroups][kLanes];
+  const Tile tl = tile_of<C>(d);
   if (tl.y >= d.ny) return;  // whole block
+  Exchange<C, double, 3> e{};
   if (tl.xt >= 0) {
     const int64_t n = int64_t(tl.y) * d.nx + tl.xt;
-    sh[0][tl.jt][tl.lt] = rho ? rho[n] : d.rho0;
-    sh[1][tl.jt][tl.lt] = ux[n];
-    sh[2][tl.jt][tl.lt] = uy[n];
+    e.v[0] = rho ? rho[n] : d.rho0;
+    e.v[1] = ux[n];
+    e.v[2] = uy[n];
   }
-  __syncthreads();
-  const int w = int(threadIdx.x) / kLanes, lane = int(threadIdx.x) % kLanes;
-  const int s = tl.s0 + w, x = lane * tl.S + s, y = tl.y;
-  if (s >= tl.S || x >= d.nx) return;
-  const double r = sh[0][w][lane];
-  const double vx = sh[1][w][lane], vy = sh[2][w][lane];
-  const double drho = r - d.rho0;
-  const double th = d.theta;
-  const double dx[3] = {0.5 * (vx * vx - vx), -vx * vx, 0.5 * (vx * vx + vx)};
-  const double dy[3] = {0.5 * (vy * vy - vy), -vy * vy, 0.5 * (vy * vy + vy)};
-  const double rr[3] = {0.5 * th, 1.0 - th, 0.5 * th};
+  e.swap(tl, sh, true);
+  if (tl.x < 0) return;
+  const double vx = e.v[1], vy = e.v[2], drho = e.v[0] - d.rho0;
+  const double rr[3] = {0.5 * d.theta, 1.0 - d.theta, 0.5 * d.theta};
+  const double tx[3] = {fmad(vx, vx, -vx), -(vx * vx), fmad(vx, vx, vx)};  // 2 d_x, d_x, 2 d_x
+  const double ty[3] = {fmad(vy, vy, -vy), -(vy * vy), fmad(vy, vy, vy)};
+  const double dx[3] = {0.5 * tx[0], tx[1], 0.5 * tx[2]}, dy[3] = {0.5 * ty[0], ty[1], 0.5 * ty[2]};
+  const double hx[3] = {fmad(0.5, tx[0], rr[0]), fmad(-vx, vx, rr[1]), fmad(0.5, tx[2], rr[2])};
+  const double hy[3] = {fmad(0.5, ty[0], rr[0]), fmad(-vy, vy, rr[1]), fmad(0.5, ty[2], rr[2])};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const int a = cx(i) + 1, b = cy(i) + 1;
-    const double hx = rr[a] + dx[a], hy = rr[b] + dy[b];
-    const double feqs = drho * hx * hy + d.rho0 * (dx[a] * hy + rr[a] * dy[b]);
-    buf[layout_index(i, x, y, d, L)] = Tr::from_f64(feqs);
+    const double t = cx(i) == 0 ? fmad(rr[a], dy[b], dx[a] * hy[b]) : fmad(dx[a], hy[b], rr[a] * dy[b]);
+    buf[layout_index<C>(i, tl.x, tl.y, d, L)] = Tr::from_f64(fmad(drho * hx[a], hy[b], d.rho0 * t));
   }
+}
+
+// The rest weight w_i.
+__device__ __forceinline__ double rest_weight(int i, double th) {
+  return (cx(i) == 0 ? 1.0 - th : 0.5 * th) * (cy(i) == 0 ? 1.0 - th : 0.5 * th);
 }
 
 // Export to FP64 or FP32: f = g + w rho0 in FP64 (exact for every storage type's g before the
 // addition), rounded once to the output type.
-template <class S, class O>
+template <class S, class O, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_get(const S* buf, RunDesc d, LayoutSel L, O* out) {
+#pragma clang fp contract(off)
   using Tr = StorageTraits<S>;
-  __shared__ O sh[Q][kTileGroups][kLanes];
+  __shared__ O sh[C ? 1 : Q][kTileGroups][kLanes];
   const int64_t N = int64_t(d.nx) * d.ny;
-  const Tile tl = tile_of(d);
+  const Tile tl = tile_of<C>(d);
   if (tl.y >= d.ny) return;  // whole block
-  const int w = int(threadIdx.x) / kLanes, lane = int(threadIdx.x) % kLanes;
-  const int s = tl.s0 + w, x = lane * tl.S + s, y = tl.y;
-  if (s < tl.S && x < d.nx) {
-    const double th = d.theta;
+  Exchange<C, O, Q> e{};
+  if (tl.x >= 0) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const double wt = (cx(i) == 0 ? 1.0 - th : 0.5 * th) * (cy(i) == 0 ? 1.0 - th : 0.5 * th);
-      const double g = double(Tr::load(buf[layout_index(i, x, y, d, L)]));
-      sh[i][w][lane] = O(g + wt * d.rho0);
+      const double g = double(Tr::load(buf[layout_index<C>(i, tl.x, tl.y, d, L)]));
+      e.v[i] = O(fmad(rest_weight(i, d.theta), d.rho0, g));
     }
   }
-  __syncthreads();
+  e.swap(tl, sh, false);
   if (tl.xt >= 0) {
-    const int64_t n = int64_t(y) * d.nx + tl.xt;
+    const int64_t n = int64_t(tl.y) * d.nx + tl.xt;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) out[i * N + n] = sh[i][tl.jt][tl.lt];
+    for (int i = 0; i < Q; ++i) out[i * N + n] = e.v[i];
   }
 }
 
 // Import of the caller's FP64 populations: g = f - w rho0 in FP64, rounded once to the
 // storage type.
-template <class S>
+template <class S, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_set(S* buf, RunDesc d, LayoutSel L, const double* in) {
+#pragma clang fp contract(off)
   using Tr = StorageTraits<S>;
-  __shared__ double sh[Q][kTileGroups][kLanes];
+  __shared__ double sh[C ? 1 : Q][kTileGroups][kLanes];
   const int64_t N = int64_t(d.nx) * d.ny;
-  const Tile tl = tile_of(d);
+  const Tile tl = tile_of<C>(d);
   if (tl.y >= d.ny) return;  // whole block
+  Exchange<C, double, Q> e{};
   if (tl.xt >= 0) {
     const int64_t n = int64_t(tl.y) * d.nx + tl.xt;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) sh[i][tl.jt][tl.lt] = in[i * N + n];
+    for (int i = 0; i < Q; ++i) e.v[i] = in[i * N + n];
   }
-  __syncthreads();
-  const int w = int(threadIdx.x) / kLanes, lane = int(threadIdx.x) % kLanes;
-  const int s = tl.s0 + w, x = lane * tl.S + s, y = tl.y;
-  if (s >= tl.S || x >= d.nx) return;
-  const double th = d.theta;
+  e.swap(tl, sh, true);
+  if (tl.x < 0) return;
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const double wt = (cx(i) == 0 ? 1.0 - th : 0.5 * th) * (cy(i) == 0 ? 1.0 - th : 0.5 * th);
-    buf[layout_index(i, x, y, d, L)] = Tr::from_f64(sh[i][w][lane] - wt * d.rho0);
-  }
+  for (int i = 0; i < Q; ++i)
+    buf[layout_index<C>(i, tl.x, tl.y, d, L)] = Tr::from_f64(fmad(-d.rho0, rest_weight(i, d.theta), e.v[i]));
 }
 
 // rho - rho0 and j of one node from the stored state, accumulated in A: FP64 for the global
 // totals, the compute type for everything else.
-template <class A, class S>
+template <class A, bool C, class S>
 __device__ __forceinline__ void node_moments(const S* buf, const RunDesc& d, LayoutSel L, int x, int y,
                                              A& drho, A& jx, A& jy, bool* bad = nullptr) {
   using Tr = StorageTraits<S>;
@@ -190,7 +228,7 @@ __device__ __forceinline__ void node_moments(const S* buf, const RunDesc& d, Lay
   bool nf = false;
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    const A g = A(Tr::load(buf[layout_index(i, x, y, d, L)]));
+    const A g = A(Tr::load(buf[layout_index<C>(i, x, y, d, L)]));
     nf |= !isfinite(g);
     drho += g;
     jx += A(cx(i)) * g;
@@ -200,34 +238,33 @@ __device__ __forceinline__ void node_moments(const S* buf, const RunDesc& d, Lay
 }
 
 // rho and u = j / rho of every node, in the compute type, written as O.
-template <class S, class O>
+template <class S, class O, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_moments(const S* buf, RunDesc d, LayoutSel L, O* rho, O* ux, O* uy) {
   using T = typename StorageTraits<S>::T;
-  __shared__ O sh[3][kTileGroups][kLanes];
-  const Tile tl = tile_of(d);
+  __shared__ O sh[C ? 1 : 3][kTileGroups][kLanes];
+  const Tile tl = tile_of<C>(d);
   if (tl.y >= d.ny) return;  // whole block
-  const int w = int(threadIdx.x) / kLanes, lane = int(threadIdx.x) % kLanes;
-  const int s = tl.s0 + w, x = lane * tl.S + s, y = tl.y;
-  if (s < tl.S && x < d.nx) {
+  Exchange<C, O, 3> e{};
+  if (tl.x >= 0) {
     T drho, jx, jy;
-    node_moments(buf, d, L, x, y, drho, jx, jy);
+    node_moments<T, C>(buf, d, L, tl.x, tl.y, drho, jx, jy);
     const T r = T(d.rho0) + drho;
-    sh[0][w][lane] = O(r);
-    sh[1][w][lane] = O(jx / r);
-    sh[2][w][lane] = O(jy / r);
+    e.v[0] = O(r);
+    e.v[1] = O(jx / r);
+    e.v[2] = O(jy / r);
   }
-  __syncthreads();
+  e.swap(tl, sh, false);
   if (tl.xt >= 0) {
-    const int64_t n = int64_t(y) * d.nx + tl.xt;
-    if (rho) rho[n] = sh[0][tl.jt][tl.lt];
-    if (ux) ux[n] = sh[1][tl.jt][tl.lt];
-    if (uy) uy[n] = sh[2][tl.jt][tl.lt];
+    const int64_t n = int64_t(tl.y) * d.nx + tl.xt;
+    if (rho) rho[n] = e.v[0];
+    if (ux) ux[n] = e.v[1];
+    if (uy) uy[n] = e.v[2];
   }
 }
 
 // FP64 totals, first stage: fixed grid of kReduceBlocks blocks, deterministic order.
-template <class S>
+template <class S, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_reduce_partial(const S* buf, RunDesc d, LayoutSel L, double* partial) {
   __shared__ double sh[4][kBlock];
@@ -238,7 +275,7 @@ k_reduce_partial(const S* buf, RunDesc d, LayoutSel L, double* partial) {
     if (!storage_node(t, d, y, q, x)) continue;
     double drho, jx, jy;
     bool bad;
-    node_moments<double>(buf, d, L, x, y, drho, jx, jy, &bad);
+    node_moments<double, C>(buf, d, L, x, y, drho, jx, jy, &bad);
     s0 += drho;
     s1 += jx;
     s2 += jy;
@@ -280,36 +317,32 @@ k_reduce_final(const double* partial, int nparts, double mass_offset, double* re
   }
 }
 
-// Adjoint seed: fbar^N_i = rho_bar + u_bar . (c_i - u)/rho (derivative of rho and
-// u = sum c f / rho with respect to f_i), written to fbar (population layout, compute type).
 // Seed of the reverse sweep: fbar^N_i = rho_bar + (u_bar . (c_i - u)) / rho, the adjoint of
-// the moments (rho, u) at t = N with respect to the populations.
-template <class S, class T>
+// the moments (rho, u) at t = N with respect to the populations (derivative of rho and
+// u = sum c f / rho with respect to f_i), written to fbar (population layout, compute type).
+template <class S, class T, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_seed(const S* buf, RunDesc d, LayoutSel L, const T* rhob, const T* uxb, const T* uyb, T* fbar) {
-  __shared__ T sh[3][kTileGroups][kLanes];
-  const Tile tl = tile_of(d);
+  __shared__ T sh[C ? 1 : 3][kTileGroups][kLanes];
+  const Tile tl = tile_of<C>(d);
   if (tl.y >= d.ny) return;  // whole block
+  Exchange<C, T, 3> e{};
   if (tl.xt >= 0) {
     const int64_t n = int64_t(tl.y) * d.nx + tl.xt;
-    sh[0][tl.jt][tl.lt] = rhob ? rhob[n] : T(0);
-    sh[1][tl.jt][tl.lt] = uxb[n];
-    sh[2][tl.jt][tl.lt] = uyb[n];
+    e.v[0] = rhob ? rhob[n] : T(0);
+    e.v[1] = uxb[n];
+    e.v[2] = uyb[n];
   }
-  __syncthreads();
-  const int w = int(threadIdx.x) / kLanes, lane = int(threadIdx.x) % kLanes;
-  const int s = tl.s0 + w, x = lane * tl.S + s, y = tl.y;
-  if (s >= tl.S || x >= d.nx) return;
-  const int q = s * kLanes + lane;
+  e.swap(tl, sh, true);
+  if (tl.x < 0) return;
   T drho, jx, jy;
-  node_moments(buf, d, L, x, y, drho, jx, jy);
+  node_moments<T, C>(buf, d, L, tl.x, tl.y, drho, jx, jy);
   const T r = T(d.rho0) + drho;
   const T vx = jx / r, vy = jy / r;
-  const T rb = sh[0][w][lane];
-  const T ax = sh[1][w][lane] / r, ay = sh[2][w][lane] / r;
+  const T ax = e.v[1] / r, ay = e.v[2] / r;
 #pragma unroll
   for (int i = 0; i < Q; ++i)
-    fbar[local_index(i, q, y, d)] = rb + ax * (T(cx(i)) - vx) + ay * (T(cy(i)) - vy);
+    fbar[local_index(i, tl.q, tl.y, d)] = e.v[0] + ax * (T(cx(i)) - vx) + ay * (T(cy(i)) - vy);
 }
 
 template <class T>
@@ -335,18 +368,16 @@ __global__ void __launch_bounds__(kBlock) k_fbar_export(RunDesc d, const T* fbar
 // Initial-condition adjoint: f^0 = f^eq(rho0_field, u0) with rho held fixed, so
 // u0bar_a = sum_i fbar^0_i d f_i^eq / d u_a, with dPhi(0,u)/du = -2u, dPhi(+-1,u)/du = u +- 1/2.
 // rho and u are the moments of the recorded state at t = 0.
-template <class S, class T>
+template <class S, class T, bool C>
 __global__ void __launch_bounds__(kBlock)
 k_ic_adjoint(const S* buf0, RunDesc d, LayoutSel L, const T* fbar, T* uxb, T* uyb) {
-  __shared__ T sh[2][kTileGroups][kLanes];
-  const Tile tl = tile_of(d);
+  __shared__ T sh[C ? 1 : 2][kTileGroups][kLanes];
+  const Tile tl = tile_of<C>(d);
   if (tl.y >= d.ny) return;  // whole block
-  const int w = int(threadIdx.x) / kLanes, lane = int(threadIdx.x) % kLanes;
-  const int s = tl.s0 + w, x = lane * tl.S + s, y = tl.y;
-  if (s < tl.S && x < d.nx) {
-    const int q = s * kLanes + lane;
+  Exchange<C, T, 2> e{};
+  if (tl.x >= 0) {
     T drho, jx, jy;
-    node_moments(buf0, d, L, x, y, drho, jx, jy);
+    node_moments<T, C>(buf0, d, L, tl.x, tl.y, drho, jx, jy);
     const T r = T(d.rho0) + drho;
     const T vx = jx / r, vy = jy / r;
     const T th = T(d.theta);
@@ -354,52 +385,64 @@ k_ic_adjoint(const S* buf0, RunDesc d, LayoutSel L, const T* fbar, T* uxb, T* uy
     const T hy[3] = {T(0.5) * (th + vy * vy - vy), T(1) - th - vy * vy, T(0.5) * (th + vy * vy + vy)};
     const T gx[3] = {vx - T(0.5), T(-2) * vx, vx + T(0.5)};
     const T gy[3] = {vy - T(0.5), T(-2) * vy, vy + T(0.5)};
-    T ax = T(0), ay = T(0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const int a = cx(i) + 1, b = cy(i) + 1;
-      const T fb = fbar[local_index(i, q, y, d)];
-      ax += fb * r * gx[a] * hy[b];
-      ay += fb * r * hx[a] * gy[b];
+      const T fb = fbar[local_index(i, tl.q, tl.y, d)];
+      e.v[0] += fb * r * gx[a] * hy[b];
+      e.v[1] += fb * r * hx[a] * gy[b];
     }
-    sh[0][w][lane] = ax;
-    sh[1][w][lane] = ay;
   }
-  __syncthreads();
+  e.swap(tl, sh, false);
   if (tl.xt >= 0) {
-    const int64_t n = int64_t(y) * d.nx + tl.xt;
-    uxb[n] = sh[0][tl.jt][tl.lt];
-    uyb[n] = sh[1][tl.jt][tl.lt];
+    const int64_t n = int64_t(tl.y) * d.nx + tl.xt;
+    uxb[n] = e.v[0];
+    uyb[n] = e.v[1];
   }
 }
 
 // --- step dispatch ---------------------------------------------------------------------------
 
-template <class S, int MODEL, int NPT, bool WT>
+// Threads per block of the step kernel: of A-B, the largest block whose wavefronts idle no more
+// groups at the end of a row than those of 256 threads (rows of up to four groups, 19 or 20 groups
+// against 32).
+template <class S>
+int step_threads(const RunDesc& d, int phase, int npt) {
+  const int s = d.pitch / kLanes;
+  auto idle = [&](int threads) { const int g = threads / kLanes * npt; return (s + g - 1) / g * g - s; };
+  int best = kBlock;
+  if (phase == PH_AB)
+    for (int t = 2 * kBlock; t <= kStepBlock<S>; t *= 2)
+      if (idle(t) <= idle(best)) best = t;
+  return best;
+}
+
+template <class S, int MODEL, int NPT, bool STREAM>
 hipError_t launch_step_w(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st) {
   using T = typename StorageTraits<S>::T;
-  const Geo g = make_geo(d, NPT);
+  const int threads = step_threads<S>(d, phase, NPT);
+  const Geo g = make_geo(d, NPT, threads);
   const Coef<T> k = make_coef<T>(d);
   const S* s = static_cast<const S*>(src);
   S* o = static_cast<S*>(dst);
   T* r = static_cast<T*>(rec);
-  const dim3 grid = step_grid(g), block(kBlock);
+  const dim3 grid = step_grid(g), block{unsigned(threads)};
   if (rec) {
-    if (phase == PH_AB) hipLaunchKernelGGL((k_step<S, MODEL, PH_AB, true, NPT, WT>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
-    else if (phase == PH_AA_EVEN) hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_EVEN, true, NPT, WT>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
-    else hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_ODD, true, NPT, WT>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+    if (phase == PH_AB) hipLaunchKernelGGL((k_step<S, MODEL, PH_AB, true, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+    else if (phase == PH_AA_EVEN) hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_EVEN, true, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+    else hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_ODD, true, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
   } else {
-    if (phase == PH_AB) hipLaunchKernelGGL((k_step<S, MODEL, PH_AB, false, NPT, WT>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
-    else if (phase == PH_AA_EVEN) hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_EVEN, false, NPT, WT>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
-    else hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_ODD, false, NPT, WT>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+    if (phase == PH_AB) hipLaunchKernelGGL((k_step<S, MODEL, PH_AB, false, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+    else if (phase == PH_AA_EVEN) hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_EVEN, false, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+    else hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_ODD, false, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
   }
   return hipGetLastError();
 }
 
 template <class S, int MODEL, int NPT>
 hipError_t launch_step_n(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st) {
-  return d.wt_stores ? launch_step_w<S, MODEL, NPT, true>(d, phase, src, dst, rec, st)
-                     : launch_step_w<S, MODEL, NPT, false>(d, phase, src, dst, rec, st);
+  return d.stream ? launch_step_w<S, MODEL, NPT, true>(d, phase, src, dst, rec, st)
+                  : launch_step_w<S, MODEL, NPT, false>(d, phase, src, dst, rec, st);
 }
 
 // Nodes per thread of the step kernel. Two or four nodes per thread put more loads in flight
@@ -431,56 +474,165 @@ hipError_t launch_step_walls(const RunDesc& d, const void* src, void* dst, hipSt
   return hipGetLastError();
 }
 
-template <class S>
-hipError_t Engine<S>::step(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st) {
-  if (d.walls) {
-    if (phase != PH_AB || rec) return hipErrorInvalidValue;
-    switch (d.model) {
-      case M_BGK: return launch_step_walls<S, M_BGK>(d, src, dst, st);
-      case M_UC: return launch_step_walls<S, M_UC>(d, src, dst, st);
-      case M_PARTIAL: return launch_step_walls<S, M_PARTIAL>(d, src, dst, st);
-      default: return launch_step_walls<S, M_COMPLETE>(d, src, dst, st);
-    }
-  }
-  switch (d.model) {
-    case M_BGK: return launch_step_m<S, M_BGK>(d, phase, src, dst, rec, st);
-    case M_UC: return launch_step_m<S, M_UC>(d, phase, src, dst, rec, st);
-    case M_PARTIAL: return launch_step_m<S, M_PARTIAL>(d, phase, src, dst, rec, st);
-    default: return launch_step_m<S, M_COMPLETE>(d, phase, src, dst, rec, st);
+// f(std::integral_constant<int, MODEL>) for the run's model.
+template <class F>
+hipError_t with_model(int model, F&& f) {
+  switch (model) {
+    case M_BGK: return f(std::integral_constant<int, M_BGK>{});
+    case M_UC: return f(std::integral_constant<int, M_UC>{});
+    case M_PARTIAL: return f(std::integral_constant<int, M_PARTIAL>{});
+    default: return f(std::integral_constant<int, M_COMPLETE>{});
   }
 }
 
-template <class S, int MODEL>
-hipError_t launch_step2_m(const RunDesc& d, const void* src, void* dst, void* rec1, void* rec2, hipStream_t st) {
+template <class S>
+hipError_t Engine<S>::step(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st) {
+  if (d.walls && (phase != PH_AB || rec)) return hipErrorInvalidValue;
+  return with_model(d.model, [&](auto m) {
+    constexpr int MODEL = decltype(m)::value;
+    return d.walls ? launch_step_walls<S, MODEL>(d, src, dst, st) : launch_step_m<S, MODEL>(d, phase, src, dst, rec, st);
+  });
+}
+
+// --- several steps per launch ------------------------------------------------------------------
+
+inline MarchGeo march_geo(const RunDesc& d, const MarchPlan& p) {
+  MarchGeo g;
+  g.nx = d.nx;
+  g.ny = d.ny;
+  g.ps = d.pitch;
+  g.rs = d.rs;
+  g.rec_rs = d.rs_rec;
+  g.ncol = p.ncol;
+  g.w = p.w;
+  g.xlast = p.xlast;
+  g.nrb = p.nrb;
+  return g;
+}
+inline dim3 march_grid(const MarchPlan& p) { return dim3(unsigned((p.ncol + p.waves - 1) / p.waves) * unsigned(p.nrb)); }
+
+template <class S, int MODEL, bool REC>
+hipError_t launch_march(const RunDesc& d, int ns, const S* src, S* dst,
+                        const MarchRec<typename StorageTraits<S>::T>& rec, hipStream_t st) {
   using T = typename StorageTraits<S>::T;
-  const Geo g = make_geo(d, 1);
+  const MarchGeo g = march_geo(d, d.march);
   const Coef<T> k = make_coef<T>(d);
-  const dim3 grid(unsigned(g.S / kFuseGroups), unsigned(d.fuse_rb));
-  const dim3 block((kFuseGroups + 2) * kLanes);
-  const S* s = static_cast<const S*>(src);
-  S* o = static_cast<S*>(dst);
-  T* r1 = static_cast<T*>(rec1);
-  T* r2 = static_cast<T*>(rec2);
-  if (rec1 && rec2) {
-    if (d.wt_stores) hipLaunchKernelGGL((k_step2<S, MODEL, true, true>), grid, block, 0, st, s, o, g, k, r1, r2, d.rs_rec);
-    else hipLaunchKernelGGL((k_step2<S, MODEL, true, false>), grid, block, 0, st, s, o, g, k, r1, r2, d.rs_rec);
-  } else {
-    if (d.wt_stores) hipLaunchKernelGGL((k_step2<S, MODEL, false, true>), grid, block, 0, st, s, o, g, k, r1, r2, d.rs_rec);
-    else hipLaunchKernelGGL((k_step2<S, MODEL, false, false>), grid, block, 0, st, s, o, g, k, r1, r2, d.rs_rec);
+  const dim3 grid = march_grid(d.march), block(unsigned(d.march.waves * kLanes));
+  switch (ns) {
+    case 2: hipLaunchKernelGGL((k_march<S, MODEL, 2, REC>), grid, block, 0, st, src, dst, g, k, rec); break;
+    case 3: hipLaunchKernelGGL((k_march<S, MODEL, 3, REC>), grid, block, 0, st, src, dst, g, k, rec); break;
+    case 4: hipLaunchKernelGGL((k_march<S, MODEL, 4, REC>), grid, block, 0, st, src, dst, g, k, rec); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Row blocks of the two-step kernel. A block of h rows computes h + 2 rows of step 1 and h
-// of step 2, and a compute unit works through its share of the blocks in turn, so a launch
-// takes about ceil(blocks / CUs) (2 h + 2) row-steps of one block, h the tallest block.
-// The planner takes the row-block count of least such cost with blocks of kFuseMinRows to
-// kFuseRows rows (ties: the taller blocks); for each count of blocks per compute unit only
-// the largest row-block count that keeps it needs checking. On MI355X this ranking matched
-// the measured throughput of every candidate tried on 512^2 to 4096^2 grids. In mode 0 a
-// grid that cannot give three quarters of the compute units a block keeps single steps.
-// The two-step adjoint kernel has the same block structure and uses the same plan.
-// Least-cost row-block count for blocks of kFuseMinRows to max_rows rows (0: none).
+template <class S>
+hipError_t Engine<S>::march(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
+                            hipStream_t st) {
+  if (!d.contig || d.walls || ns > d.march.steps) return hipErrorInvalidValue;
+  MarchRec<T> r{};
+  for (int s = 0; rec && s < ns; ++s) r.p[s] = rec + s * rec_slot;
+  return with_model(d.model, [&](auto m) {
+    constexpr int MODEL = decltype(m)::value;
+    return rec ? launch_march<S, MODEL, true>(d, ns, static_cast<const S*>(src), static_cast<S*>(dst), r, st)
+               : launch_march<S, MODEL, false>(d, ns, static_cast<const S*>(src), static_cast<S*>(dst), r, st);
+  });
+}
+
+template <class S>
+hipError_t Engine<S>::adjoint_march(const RunDesc& d, int ns, const T* fbar_next, T* fbar, const T* rec,
+                                    int64_t rec_slot, hipStream_t st) {
+  if (!d.contig || ns > d.adj_march.steps) return hipErrorInvalidValue;
+  const MarchGeo g = march_geo(d, d.adj_march);
+  const Coef<T> k = make_coef<T>(d);
+  const dim3 grid = march_grid(d.adj_march), block(unsigned(d.adj_march.waves * kLanes));
+  MarchRec<const T> r{};
+  for (int s = 0; s < ns; ++s) r.p[s] = rec - s * rec_slot;
+  return with_model(d.model, [&](auto m) -> hipError_t {
+    constexpr int MODEL = decltype(m)::value;
+    switch (ns) {
+      case 2: hipLaunchKernelGGL((k_march_adjoint<T, MODEL, 2>), grid, block, 0, st, fbar_next, fbar, g, k, r); break;
+      case 3: hipLaunchKernelGGL((k_march_adjoint<T, MODEL, 3>), grid, block, 0, st, fbar_next, fbar, g, k, r); break;
+      case 4: hipLaunchKernelGGL((k_march_adjoint<T, MODEL, 4>), grid, block, 0, st, fbar_next, fbar, g, k, r); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  });
+}
+
+// The tile plan's geometry for a launch of ns steps.
+inline TileGeo tile_geo(const RunDesc& d, const TilePlan& p, int ns) {
+  TileGeo g;
+  g.nx = d.nx;
+  g.ny = d.ny;
+  g.ps = d.pitch;
+  g.rs = int(d.rs);
+  g.rec_rs = int(d.rs_rec);
+  g.tw = p.tw;
+  g.th = p.th;
+  g.ntx = (d.nx + p.tw - 1) / p.tw;
+  g.wrapx = p.wrapx;
+  g.wrapy = p.wrapy;
+  g.hx = p.wrapx ? 0 : ns - 1;
+  g.hy = p.wrapy ? 0 : ns - 1;
+  g.rw = p.tw + 2 * g.hx;
+  g.rh = p.th + 2 * g.hy;
+  g.ns = ns;
+  return g;
+}
+
+template <class S, int MODEL, int KIND, class... Args>
+hipError_t launch_tile(const RunDesc& d, const TilePlan& p, int ns, hipStream_t st, Args... args) {
+  using T = typename StorageTraits<S>::T;
+  const TileGeo g = tile_geo(d, p, ns);
+  const TileConfig c = kTileConfigs[p.cfg];
+  if (int64_t(g.rw) * g.rh > int64_t(c.threads) * c.nodes) return hipErrorInvalidValue;
+  const dim3 grid(unsigned(g.ntx) * unsigned((d.ny + p.th - 1) / p.th)), block(unsigned(c.threads));
+  const Coef<T> k = make_coef<T>(d);
+  auto go = [&](auto kernel, const S* src, S* dst, T* rec, int64_t slot) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, src, dst, g, k, rec, slot);
+  };
+  switch (p.cfg) {
+    case 0: go(k_tile<S, MODEL, 256, 1, KIND>, args...); break;
+    case 1: go(k_tile<S, MODEL, 512, 1, KIND>, args...); break;
+    case 2: go(k_tile<S, MODEL, 1024, 1, KIND>, args...); break;
+    case 3: go(k_tile<S, MODEL, 1024, 2, KIND>, args...); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <class S>
+hipError_t Engine<S>::tile(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
+                           hipStream_t st) {
+  if (!d.contig || ns > d.tile.steps || (d.walls && rec)) return hipErrorInvalidValue;
+  const S* s = static_cast<const S*>(src);
+  S* o = static_cast<S*>(dst);
+  return with_model(d.model, [&](auto m) {
+    constexpr int MODEL = decltype(m)::value;
+    if (d.walls) return launch_tile<S, MODEL, TILE_WALLS>(d, d.tile, ns, st, s, o, rec, rec_slot);
+    if (rec) return launch_tile<S, MODEL, TILE_REC>(d, d.tile, ns, st, s, o, rec, rec_slot);
+    return launch_tile<S, MODEL, TILE_STEP>(d, d.tile, ns, st, s, o, rec, rec_slot);
+  });
+}
+
+template <class S>
+hipError_t Engine<S>::adjoint_tile(const RunDesc& d, int ns, const T* fbar_next, T* fbar, const T* rec,
+                                   int64_t rec_slot, hipStream_t st) {
+  if (!d.contig || ns > d.adj_tile.steps) return hipErrorInvalidValue;
+  return with_model(d.model, [&](auto m) {
+    constexpr int MODEL = decltype(m)::value;
+    return launch_tile<T, MODEL, TILE_ADJOINT>(d, d.adj_tile, ns, st, fbar_next, fbar, const_cast<T*>(rec), rec_slot);
+  });
+}
+
+// Row blocks of the two-step adjoint kernel, and the rule behind lbm_steps_per_launch. A block of
+// h rows computes h + 2 rows of step 1 and h of step 2, and a compute unit works through its share
+// of the blocks in turn, so a launch takes about ceil(blocks / CUs) (2 h + 2) row-steps of one
+// block, h the tallest block. The planner takes the row-block count of least such cost with
+// blocks of kFuseMinRows to max_rows rows (ties: the taller blocks; 0: none); for each count of
+// blocks per compute unit only the largest row-block count that keeps it needs checking.
 inline long plan_rows(long ny, long cols, long cus, long max_rows) {
   const long nb_lo = (ny + max_rows - 1) / max_rows;
   const long nb_hi = std::min(std::max(nb_lo, ny / kFuseMinRows), 65535L);
@@ -497,14 +649,11 @@ inline long plan_rows(long ny, long cols, long cus, long max_rows) {
   return best;
 }
 
-// tall: also consider blocks of up to kFuseRowsTall rows, taken when the grid then gives every
-// block a compute unit of its own (one round of blocks).
-inline int plan_row_blocks(const RunDesc& d, int mode, bool tall) {
+// mode 0 asks for a block on three quarters of the compute units. tall: also consider blocks of
+// up to kFuseRowsTall rows, taken when the grid then gives every block a compute unit of its own
+// (one round of blocks).
+inline int plan_row_blocks(const RunDesc& d, int mode, bool tall, int cus) {
   if (d.nx % kLanes != 0 || (d.pitch / kLanes) % kFuseGroups != 0) return 0;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    return 0;
   const long cols = d.pitch / kLanes / kFuseGroups;
   long best = plan_rows(d.ny, cols, cus, kFuseRows);
   if (tall) {
@@ -516,68 +665,103 @@ inline int plan_row_blocks(const RunDesc& d, int mode, bool tall) {
 }
 
 template <class S>
-int Engine<S>::fuse_row_blocks(const RunDesc& d, int mode) {
-  return plan_row_blocks(d, mode, FuseTall<S>::value);
-}
-
-template <class S>
-int Engine<S>::adjoint_row_blocks(const RunDesc& d, int mode) {
-  return plan_row_blocks(d, mode, FuseTall<T>::value);
-}
-
-template <class S>
-hipError_t Engine<S>::step2(const RunDesc& d, const void* src, void* dst, void* rec1, void* rec2, hipStream_t st) {
-  if (d.fuse_rb < 1 || d.fuse_rb > d.ny) return hipErrorInvalidValue;
-  switch (d.model) {
-    case M_BGK: return launch_step2_m<S, M_BGK>(d, src, dst, rec1, rec2, st);
-    case M_UC: return launch_step2_m<S, M_UC>(d, src, dst, rec1, rec2, st);
-    case M_PARTIAL: return launch_step2_m<S, M_PARTIAL>(d, src, dst, rec1, rec2, st);
-    default: return launch_step2_m<S, M_COMPLETE>(d, src, dst, rec1, rec2, st);
+void plan_steps(RunDesc& d, int cus, bool force_march, int64_t horizon) {
+  using T = typename StorageTraits<S>::T;
+  // The tile kernel addresses a whole buffer with 32-bit byte offsets.
+  const bool tiles = d.rs * d.ny * int64_t(sizeof(T)) < (int64_t(1) << 31);
+  auto choose = [&](MarchPlan& march, TilePlan& tile, double single) {
+    if (force_march && march.steps) tile.steps = 0;
+    else if (march.us_per_step < tile.us_per_step) tile.steps = 0;
+    else march.steps = 0;
+    if (!force_march && single < march.us_per_step && single < tile.us_per_step) march.steps = tile.steps = 0;
+  };
+  const CostModel cm = cost_model(int(sizeof(S)), d.model == M_BGK, false, std::is_same_v<S, bf16_t>);
+  if (!d.walls) d.march = plan_march(d.nx, d.ny, MarchNodes<S>::value, kMarchHalo, kMarchMax, kMarchWaves, cus, horizon, cm);
+  if (tiles) d.tile = plan_tile(d.nx, d.ny, cus, horizon, cm);
+  choose(d.march, d.tile, single_step_us(d.nx, d.ny, cus, cm));
+  if (horizon > 0) {
+    const CostModel ca = cost_model(int(sizeof(T)), d.model == M_BGK, true);
+    d.adj_march = plan_march(d.nx, d.ny, kMarchAdjointNodes, kMarchHalo, kMarchMax, kMarchWaves, cus, horizon, ca);
+    if (tiles) d.adj_tile = plan_tile(d.nx, d.ny, cus, horizon, ca);
+    choose(d.adj_march, d.adj_tile, single_step_us(d.nx, d.ny, cus, ca));
   }
+}
+
+template <class S>
+void Engine<S>::plan(RunDesc& d, int mode, int64_t segment) {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    return;
+  const bool pair = mode >= 0 && !d.walls && plan_row_blocks(d, mode, FuseTall<S>::value, cus) > 0;
+  d.pair = d.contig && pair;
+  if (mode < 0) return;
+  if (!d.contig) {
+    if (segment > 0) d.adj_rb = plan_row_blocks(d, mode, FuseTall<T>::value, cus);
+    return;
+  }
+  // mode 1 takes the marching kernel on every grid of whole pairs (the documented rule), mode 0
+  // whatever the cost model finds fastest.
+  const bool force = mode == 1 && d.nx % kLanes == 0 && (d.pitch / kLanes) % kFuseGroups == 0;
+  plan_steps<S>(d, cus, force, segment);
+}
+
+// f(std::bool_constant<contiguous rows>).
+template <class F>
+hipError_t with_layout(const RunDesc& d, F&& f) {
+  if (d.contig) f(std::true_type{});
+  else f(std::false_type{});
+  return hipGetLastError();
 }
 
 template <class S>
 hipError_t Engine<S>::init(const RunDesc& d, LayoutSel L, void* buf, const double* rho, const double* ux,
                            const double* uy, hipStream_t st) {
-  hipLaunchKernelGGL(k_init<S>, tile_grid(d), dim3(kBlock), 0, st, static_cast<S*>(buf), d, L, rho, ux, uy);
-  return hipGetLastError();
+  return with_layout(d, [&](auto c) {
+    hipLaunchKernelGGL((k_init<S, decltype(c)::value>), tile_grid(d), dim3(kBlock), 0, st, static_cast<S*>(buf), d, L,
+                       rho, ux, uy);
+  });
 }
 
 template <class S>
 hipError_t Engine<S>::get(const RunDesc& d, LayoutSel L, const void* buf, bool out_f64, void* out, hipStream_t st) {
-  if (out_f64)
-    hipLaunchKernelGGL((k_get<S, double>), tile_grid(d), dim3(kBlock), 0, st, static_cast<const S*>(buf), d, L,
-                       static_cast<double*>(out));
-  else
-    hipLaunchKernelGGL((k_get<S, float>), tile_grid(d), dim3(kBlock), 0, st, static_cast<const S*>(buf), d, L,
-                       static_cast<float*>(out));
-  return hipGetLastError();
+  return with_layout(d, [&](auto c) {
+    constexpr bool C = decltype(c)::value;
+    const S* b = static_cast<const S*>(buf);
+    if (out_f64) hipLaunchKernelGGL((k_get<S, double, C>), tile_grid(d), dim3(kBlock), 0, st, b, d, L, static_cast<double*>(out));
+    else hipLaunchKernelGGL((k_get<S, float, C>), tile_grid(d), dim3(kBlock), 0, st, b, d, L, static_cast<float*>(out));
+  });
 }
 
 template <class S>
 hipError_t Engine<S>::set(const RunDesc& d, LayoutSel L, void* buf, const double* in, hipStream_t st) {
-  hipLaunchKernelGGL(k_set<S>, tile_grid(d), dim3(kBlock), 0, st, static_cast<S*>(buf), d, L, in);
-  return hipGetLastError();
+  return with_layout(d, [&](auto c) {
+    hipLaunchKernelGGL((k_set<S, decltype(c)::value>), tile_grid(d), dim3(kBlock), 0, st, static_cast<S*>(buf), d, L, in);
+  });
 }
 
 template <class S>
 hipError_t Engine<S>::moments(const RunDesc& d, LayoutSel L, const void* buf, bool out_f64, void* rho, void* ux,
                               void* uy, hipStream_t st) {
-  if (out_f64)
-    hipLaunchKernelGGL((k_moments<S, double>), tile_grid(d), dim3(kBlock), 0, st, static_cast<const S*>(buf), d,
-                       L, static_cast<double*>(rho), static_cast<double*>(ux), static_cast<double*>(uy));
-  else
-    hipLaunchKernelGGL((k_moments<S, float>), tile_grid(d), dim3(kBlock), 0, st, static_cast<const S*>(buf), d,
-                       L, static_cast<float*>(rho), static_cast<float*>(ux), static_cast<float*>(uy));
-  return hipGetLastError();
+  return with_layout(d, [&](auto c) {
+    constexpr bool C = decltype(c)::value;
+    const S* b = static_cast<const S*>(buf);
+    if (out_f64)
+      hipLaunchKernelGGL((k_moments<S, double, C>), tile_grid(d), dim3(kBlock), 0, st, b, d, L, static_cast<double*>(rho),
+                         static_cast<double*>(ux), static_cast<double*>(uy));
+    else
+      hipLaunchKernelGGL((k_moments<S, float, C>), tile_grid(d), dim3(kBlock), 0, st, b, d, L, static_cast<float*>(rho),
+                         static_cast<float*>(ux), static_cast<float*>(uy));
+  });
 }
 
 template <class S>
 hipError_t Engine<S>::invariants(const RunDesc& d, LayoutSel L, const void* buf, double* partial, double* result,
                                  hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_partial<S>, dim3(kReduceBlocks), dim3(kBlock), 0, st, static_cast<const S*>(buf), d, L,
-                     partial);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = with_layout(d, [&](auto c) {
+    hipLaunchKernelGGL((k_reduce_partial<S, decltype(c)::value>), dim3(kReduceBlocks), dim3(kBlock), 0, st,
+                       static_cast<const S*>(buf), d, L, partial);
+  });
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_reduce_final<S>, dim3(1), dim3(kBlock), 0, st, partial, kReduceBlocks,
                      d.rho0 * double(d.nx) * double(d.ny), result);
@@ -587,9 +771,10 @@ hipError_t Engine<S>::invariants(const RunDesc& d, LayoutSel L, const void* buf,
 template <class S>
 hipError_t Engine<S>::seed(const RunDesc& d, LayoutSel L, const void* buf, const T* rhob, const T* uxb, const T* uyb,
                            T* fbar, hipStream_t st) {
-  hipLaunchKernelGGL((k_seed<S, T>), tile_grid(d), dim3(kBlock), 0, st, static_cast<const S*>(buf), d, L, rhob, uxb,
-                     uyb, fbar);
-  return hipGetLastError();
+  return with_layout(d, [&](auto c) {
+    hipLaunchKernelGGL((k_seed<S, T, decltype(c)::value>), tile_grid(d), dim3(kBlock), 0, st,
+                       static_cast<const S*>(buf), d, L, rhob, uxb, uyb, fbar);
+  });
 }
 
 template <class S>
@@ -607,17 +792,14 @@ hipError_t Engine<S>::fbar_export(const RunDesc& d, const T* fbar, T* dense, hip
 template <class S>
 hipError_t Engine<S>::adjoint_step2(const RunDesc& d, const T* fbar_next, T* fbar, const T* rec_hi, const T* rec_lo,
                                     hipStream_t st) {
-  if (d.adj_rb < 1 || d.adj_rb > d.ny) return hipErrorInvalidValue;
+  if (d.contig || d.adj_rb < 1 || d.adj_rb > d.ny) return hipErrorInvalidValue;
   const Geo g = make_geo(d, 1);
   const Coef<T> k = make_coef<T>(d);
   const dim3 grid(unsigned(g.S / kFuseGroups), unsigned(d.adj_rb)), block((kFuseGroups + 2) * kLanes);
-  switch (d.model) {
-    case M_BGK: hipLaunchKernelGGL((k_adjoint_step2<T, M_BGK>), grid, block, 0, st, fbar_next, fbar, g, k, rec_hi, rec_lo, d.rs_rec); break;
-    case M_UC: hipLaunchKernelGGL((k_adjoint_step2<T, M_UC>), grid, block, 0, st, fbar_next, fbar, g, k, rec_hi, rec_lo, d.rs_rec); break;
-    case M_PARTIAL: hipLaunchKernelGGL((k_adjoint_step2<T, M_PARTIAL>), grid, block, 0, st, fbar_next, fbar, g, k, rec_hi, rec_lo, d.rs_rec); break;
-    default: hipLaunchKernelGGL((k_adjoint_step2<T, M_COMPLETE>), grid, block, 0, st, fbar_next, fbar, g, k, rec_hi, rec_lo, d.rs_rec); break;
-  }
-  return hipGetLastError();
+  return with_model(d.model, [&](auto m) {
+    hipLaunchKernelGGL((k_adjoint_step2<T, decltype(m)::value>), grid, block, 0, st, fbar_next, fbar, g, k, rec_hi, rec_lo, d.rs_rec);
+    return hipGetLastError();
+  });
 }
 
 template <class S>
@@ -625,21 +807,21 @@ hipError_t Engine<S>::adjoint_step(const RunDesc& d, const T* fbar_next, T* fbar
   const Geo g = make_geo(d, 1);
   const Coef<T> k = make_coef<T>(d);
   const dim3 grid = step_grid(g), block(kBlock);
-  switch (d.model) {
-    case M_BGK: hipLaunchKernelGGL((k_adjoint_step<T, M_BGK>), grid, block, 0, st, fbar_next, fbar, g, k, rec, d.rs_rec); break;
-    case M_UC: hipLaunchKernelGGL((k_adjoint_step<T, M_UC>), grid, block, 0, st, fbar_next, fbar, g, k, rec, d.rs_rec); break;
-    case M_PARTIAL: hipLaunchKernelGGL((k_adjoint_step<T, M_PARTIAL>), grid, block, 0, st, fbar_next, fbar, g, k, rec, d.rs_rec); break;
-    default: hipLaunchKernelGGL((k_adjoint_step<T, M_COMPLETE>), grid, block, 0, st, fbar_next, fbar, g, k, rec, d.rs_rec); break;
-  }
-  return hipGetLastError();
+  return with_model(d.model, [&](auto m) {
+    constexpr int MODEL = decltype(m)::value;
+    if (d.contig) hipLaunchKernelGGL((k_adjoint_step<T, MODEL, true>), grid, block, 0, st, fbar_next, fbar, g, k, rec, d.rs_rec);
+    else hipLaunchKernelGGL((k_adjoint_step<T, MODEL, false>), grid, block, 0, st, fbar_next, fbar, g, k, rec, d.rs_rec);
+    return hipGetLastError();
+  });
 }
 
 template <class S>
 hipError_t Engine<S>::ic_adjoint(const RunDesc& d, LayoutSel L, const void* buf0, const T* fbar, T* uxb, T* uyb,
                                  hipStream_t st) {
-  hipLaunchKernelGGL((k_ic_adjoint<S, T>), tile_grid(d), dim3(kBlock), 0, st, static_cast<const S*>(buf0), d, L, fbar,
-                     uxb, uyb);
-  return hipGetLastError();
+  return with_layout(d, [&](auto c) {
+    hipLaunchKernelGGL((k_ic_adjoint<S, T, decltype(c)::value>), tile_grid(d), dim3(kBlock), 0, st,
+                       static_cast<const S*>(buf0), d, L, fbar, uxb, uyb);
+  });
 }
 
 }  // namespace lbm

@@ -1,0 +1,240 @@
+// Host-side choice of how a run's steps are launched: the strips and row blocks of the marching
+// kernels (lbm_march.h), the tiles of the LDS kernel (lbm_tile.h), and which of them, or the
+// single-step kernel, takes the least time per step on a grid. Plain arithmetic on sizes; no
+// device calls.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace lbm {
+
+struct MarchPlan {
+  int steps = 0;  // per launch; 0: the kernel does not apply
+  int ncol = 0, w = 0, xlast = 0, nrb = 0, waves = 0;
+  double us_per_step = 1e30;
+};
+
+struct TilePlan {
+  int steps = 0;
+  int cfg = 0;  // kTileConfigs index
+  int tw = 0, th = 0, wrapx = 0, wrapy = 0;
+  double us_per_step = 1e30;
+};
+
+// Threads and nodes per thread of the tile kernel's instances.
+struct TileConfig {
+  int threads, nodes;
+};
+constexpr TileConfig kTileConfigs[] = {{256, 1}, {512, 1}, {1024, 1}, {1024, 2}};
+constexpr int kTileConfigCount = 4;
+constexpr int kTileWholeSteps = 4096;  // steps per launch where one block holds the whole box
+
+// Costs of the kernels on MI355X in us, by storage type, model and direction; fitted to the
+// launch times of 10 000 plans on grids of 64^2 to 1448^2 (FP32, FP64, 16-bit storage, LBGK
+// and the complete model, forward, recording and reverse). The fastest plan the model picks is
+// within 5 % of the fastest one measured at the median and 12 % at most below 1024^2.
+struct CostModel {
+  double bytes = 0;      // read and written per node and launch
+  double rec_bytes = 0;  // and moments per node and step
+  double wave = 0;       // marching and single step: one SIMD's time for a 64-lane collision
+  double tile_wave = 0;  // the same inside a tile, LDS accesses included
+  double tile_memory = 0;           // bytes per us of a tile's loads and stores
+  double single_launch = 0;         // single step: dispatch, first loads, last stores
+  double single_issue = 0;          // and the share of a SIMD's cycles it issues in
+  int regs[kTileConfigCount] = {};  // vector registers of the tile kernel's instances
+  int max_cells = 0;                // largest instance that does not spill
+};
+constexpr double kMarchLaunch = 5.0;   // dispatch, the first loads, the last stores
+constexpr double kTileLaunch = 4.2;
+constexpr double kTileStep = 0.11;     // a step's barrier and LDS latency
+constexpr double kTileRound = 0.8;     // a further round of blocks on the same compute unit
+constexpr double kTileAlone = 1.12;    // nothing else on the compute unit to fill a block's waits
+constexpr double kTileSerial = 1.35;   // blocks one after the other on a compute unit that holds one
+constexpr double kMemory = 6.5e6;      // bytes per us of the single step
+constexpr double kMarchMemory = 5.5e6; // the same of the marching kernels, halos included
+
+// By bytes per stored value (reverse steps: of the compute type). The wavefront times are vector
+// instructions per collision at 2.4 GHz, a quarter of a wavefront per cycle.
+inline CostModel cost_model(int bytes, bool bgk, bool adjoint, bool bf16 = false) {
+  CostModel c;
+  const bool f64 = bytes == 8, half = bytes == 2;
+  const double instr = adjoint ? (bgk ? 110 : f64 ? 260 : 200) : f64 ? (bgk ? 120 : 181) : half ? (bgk ? 130 : bf16 ? 150 : 180) : (bgk ? 95 : 145);
+  c.wave = instr * 4.0 / 2400.0;
+  c.tile_wave = f64 ? (bgk ? 0.19 : 0.25) : half ? (bgk ? 0.19 : 0.23) : (bgk ? 0.135 : 0.17);
+  c.tile_memory = adjoint ? 12e6 : half ? 5.7e6 : 9e6;
+  c.bytes = 18.0 * bytes;
+  c.single_launch = half ? 2.6 : 1.8;
+  c.single_issue = half ? 0.69 : 0.6;
+  c.rec_bytes = adjoint ? 5.0 * bytes : 0.0;
+  const int one = f64 ? 96 : 64, two = f64 ? 128 : adjoint ? 96 : 80;
+  c.regs[0] = c.regs[1] = c.regs[2] = one;
+  c.regs[3] = two;
+  c.max_cells = adjoint && f64 ? 1024 : 2048;
+  return c;
+}
+
+// Strips of w stored nodes out of `span` (see MarchGeo). False where no strip width works.
+inline bool march_strips(int nx, int span, int halo, bool pairs, MarchPlan& p) {
+  const int most = span - 2 * halo;
+  if (!pairs || nx % 2 == 0) {
+    p.w = most;
+    p.ncol = (nx + most - 1) / most;
+    p.xlast = (p.ncol - 1) * most;
+    return true;
+  }
+  // Odd width with pairs: the last strip ends at nx, and the one before it keeps its last lane
+  // (span - halo - 1 nodes past its first stored one) inside the row.
+  if (nx < span - halo) return false;
+  for (int w = most; w >= most / 2; w -= 2) {
+    const int ncol = std::max(2, (nx + w - 1) / w);
+    if (int64_t(ncol - 2) * w + span - halo > nx || nx - w < halo) continue;
+    p.w = w;
+    p.ncol = ncol;
+    p.xlast = nx - w;
+    return true;
+  }
+  return false;
+}
+
+// Steps of the next launch when m steps lie ahead. Tiles share them evenly among the launches
+// they need; the marching kernel takes as many as it can without leaving a single one.
+inline int64_t steps_ahead(int64_t m, int march, int tile) {
+  if (tile > 0) {
+    const int64_t launches = (m + tile - 1) / tile;
+    return (m + launches - 1) / launches;
+  }
+  if (march > 0) return m == march + 1 && march > 2 ? march - 1 : std::min<int64_t>(m, march);
+  return 1;
+}
+
+// Row blocks and steps per launch of least time per step. A SIMD works through its share of the
+// strips' row blocks; a block of h rows costs steps * (h + steps - 1) collisions. horizon: steps
+// come in runs of that many (0: many).
+inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, int max_waves, int cus, int64_t horizon,
+                            const CostModel& cm) {
+  MarchPlan best;
+  MarchPlan p;
+  if (!march_strips(nx, 64 * npl, halo, npl == 2, p)) return best;
+  for (int k = 1; k <= 8; ++k) {
+    // k strips' row blocks per SIMD, in blocks of max_waves strips or of one.
+    for (int waves = max_waves; waves >= 1; waves = waves > 1 ? 1 : 0) {
+      const int64_t cols = (int64_t(p.ncol) + waves - 1) / waves;
+      const int64_t slots = int64_t(cus) * 4 * k / waves;
+      const int64_t nrb = std::min<int64_t>(std::max<int64_t>(1, slots / cols), ny);
+      const int64_t rows = (ny + nrb - 1) / nrb;
+      const int64_t rounds = (cols * nrb * waves + int64_t(cus) * 4 - 1) / (int64_t(cus) * 4);
+      auto launch = [&](int64_t steps) {
+        // A SIMD with one wavefront waits for it a fifth of the time.
+        const double issue = double(rounds) * double(steps * (rows + steps - 1)) * npl * cm.wave / (rounds < 2 ? 0.8 : 0.95);
+        const double halo_reads = 64.0 * npl / p.w * double(rows + 2 * (steps - 1)) / double(rows);
+        const double mem = double(nx) * ny * (cm.bytes / 2 * (1 + halo_reads) + steps * cm.rec_bytes * halo_reads) / kMarchMemory;
+        return kMarchLaunch + std::max(issue, mem);
+      };
+      for (int steps = 2; steps <= max_steps; ++steps) {
+        double us = launch(steps) / steps;
+        if (horizon > 0 && horizon < 64) {
+          us = 0;
+          for (int64_t m = horizon; m > 0; m -= steps_ahead(m, steps, 0)) us += launch(steps_ahead(m, steps, 0));
+          us /= double(horizon);
+        }
+        if (us < best.us_per_step * 0.999) {
+          best = p;
+          best.steps = steps;
+          best.nrb = int(nrb);
+          best.waves = waves;
+          best.us_per_step = us;
+        }
+      }
+    }
+  }
+  return best;
+}
+
+// Tile shape, instance and steps per launch of least time per step.
+inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostModel& cm) {
+  TilePlan best;
+  const int steps_try[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24, 32, 48, 64};
+  const double lds_per_cell = cm.bytes / 2;
+  for (int c = 0; c < kTileConfigCount; ++c) {
+    const int cells = kTileConfigs[c].threads * kTileConfigs[c].nodes;
+    if (cells > cm.max_cells) continue;
+    int last = 0;  // a short horizon makes several of steps_try the same
+    const double side = std::sqrt(double(cells));
+    for (int ns : steps_try) {
+      int64_t launches = 1, m = ns;
+      if (horizon > 0 && horizon < 64) {
+        m = horizon;
+        launches = (m + ns - 1) / ns;
+        ns = int((m + launches - 1) / launches);
+        if (ns == last) continue;
+        last = ns;
+      }
+      const int h = ns - 1;
+      for (int shape = 0; shape < 9; ++shape) {
+        // Shapes: the whole width (0), the whole height (1), else regions of several widths.
+        int tw, th, wx = 0, wy = 0;
+        if (shape == 0) {
+          if (nx > cells) continue;
+          wx = 1, tw = nx;
+          const int rows = cells / nx;
+          if (rows >= ny) wy = 1, th = ny;
+          else th = rows - 2 * h;
+        } else if (shape == 1) {
+          if (ny > cells || cells / ny >= nx) continue;
+          wy = 1, th = ny;
+          tw = cells / ny - 2 * h;
+        } else {
+          static const double aspect[] = {0.35, 0.5, 0.7, 1.0, 1.4, 2.0, 2.8};
+          const int rw = int(side * aspect[shape - 2]);
+          if (rw <= 2 * h) continue;
+          tw = std::min(rw - 2 * h, nx);
+          th = cells / (tw + 2 * h) - 2 * h;
+        }
+        if (tw < 1 || th < 1) continue;
+        // Even tiles over the box.
+        th = std::min(th, ny);
+        const int ntx = (nx + tw - 1) / tw, nty = (ny + th - 1) / th;
+        tw = (nx + ntx - 1) / ntx;
+        th = (ny + nty - 1) / nty;
+        const double rw = tw + (wx ? 0 : 2 * h), rh = th + (wy ? 0 : 2 * h);
+        if (rw * rh > cells) continue;
+        // Wavefronts of the block (the region shrinks by a row on both sides per step), blocks per
+        // compute unit, and how many of them it holds at once.
+        const double wv = std::ceil(rw * (wy ? rh : rh - h) / 64.0);
+        const double share = double(ntx) * nty / cus, blocks = std::ceil(share);
+        const int by_regs = 512 / cm.regs[c] * 4 * 64 / kTileConfigs[c].threads;
+        const int fit = std::max(1, std::min(int(160 * 1024 / (lds_per_cell * (cells + 2))), by_regs));
+        const double rounds = std::ceil(blocks / fit);
+        const double per = std::max(std::ceil(wv / 4), wv / 4 * (blocks > 2 ? share : blocks));
+        const double wait = blocks <= 1 ? kTileAlone : fit == 1 ? kTileSerial : 1.0;
+        const double region = rw * rh / (double(tw) * th);
+        const double mem = double(nx) * ny * (cm.bytes / 2 * (1 + region) + ns * cm.rec_bytes * region) / cm.tile_memory;
+        const double us = (kTileLaunch + mem + (rounds - 1) * kTileRound +
+                           ns * (kTileStep * rounds + cm.tile_wave * per * wait)) * double(launches) / double(m);
+        if (us < best.us_per_step * 0.999) {
+          best.steps = ns;
+          best.cfg = c;
+          best.tw = tw;
+          best.th = th;
+          best.wrapx = wx;
+          best.wrapy = wy;
+          best.us_per_step = us;
+        }
+      }
+    }
+  }
+  // One block that holds the whole box needs no surroundings: any number of steps.
+  if (best.wrapx && best.wrapy) best.steps = kTileWholeSteps;
+  return best;
+}
+
+// Time of a launch of one step.
+inline double single_step_us(int nx, int ny, int cus, const CostModel& cm) {
+  const double nodes = double(nx) * ny;
+  return std::max(2.7, cm.single_launch + nodes * std::max((cm.bytes + cm.rec_bytes) / kMemory, cm.wave / 64.0 / (cus * 4.0) / cm.single_issue));
+}
+
+}  // namespace lbm

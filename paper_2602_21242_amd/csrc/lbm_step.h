@@ -1,20 +1,27 @@
-// Fused stream + collide kernel of the D2Q9 OReg-GEq step and the adjoint step kernel.
-// Instantiated per storage type in step_<type>.hip.
+// Single-step kernels: the fused stream + collide step, its variant with walls, and the adjoint
+// step; the two-step adjoint kernel of the AA layout. Instantiated per storage type in
+// step_<type>.hip. The kernels that take several steps per launch are in lbm_march.h and
+// lbm_tile.h.
 //
 // Data layout (HBM): shifted populations g_i, row-interleaved structure of arrays: element
-// (i, x, y) sits at y * rs + i * ps + pos(x) with ps = pitch = 64 S, S = ceil(nx / 64),
-// rs = 9 * pitch. Within a row the nodes are lane-strided: node x = lane * S + s is stored at
-// pos(x) = 64 s + lane, so the 64 lanes of a wave hold the nodes s, s + S, ..., s + 63 S.
-// The x-neighbours of those nodes (s - 1 and s + 1 of the same lanes) are again one whole,
-// aligned 64-element group, so the streaming step's x-shifts cost no extra cache lines; only
-// the groups s = 0 and s = S - 1 read a group rotated by one lane. (With contiguous rows
-// every x-shifted wave load straddles one more cache line, which measured 5-7 % slower on
-// MI355X for the 9-in/9-out pull.) The nine population rows of a lattice row are contiguous,
-// which keeps the 18 concurrent read/write streams of a step within a compact address
-// window. Loads and stores are nontemporal: every population is read once and written once
-// per step. Rows are padded to whole groups; padding positions (x >= nx, last lanes only)
-// are never read by a real node. The step kernel lets a padding lane read and write its own
-// padding slot (no per-lane guards), the other kernels skip padding.
+// (i, x, y) sits at y * rs + i * ps + pos(x) with ps = pitch = 64 ceil(nx / 64), rs = 9 * pitch.
+// The nine population rows of a lattice row are contiguous, which keeps the 18 concurrent
+// read/write streams of a step within a compact address window. Rows are padded to whole
+// 64-element groups; padding positions are never read by a real node.
+//
+// A-B buffers have contiguous rows, pos(x) = x: a wavefront that keeps several steps of adjacent
+// nodes in registers or LDS (lbm_march.h, lbm_tile.h) needs them adjacent. The single step's
+// x-shifted loads then straddle one more cache line, which costs it 1 % (4096^2 183.5 -> 185 us
+// per step) in blocks of up to 16 adjacent wavefronts.
+//
+// AA buffers have lane-strided rows: with S = ceil(nx / 64), node x = lane * S + s is stored at
+// pos(x) = 64 s + lane, so the 64 lanes of a wave hold the nodes s, s + S, ..., s + 63 S. The
+// x-neighbours of those nodes are again one whole, aligned 64-element group, so the x-shifts of
+// the odd steps, which shift stores as well as loads, cost no extra cache lines; only the groups
+// s = 0 and s = S - 1 read a group rotated by one lane. (With contiguous rows an odd step's
+// stores write parts of lines: 4096^2 282-343 us per odd step instead of 184.) The step kernel
+// lets a padding lane read and write its own padding slot (no per-lane guards), the other kernels
+// skip padding.
 //
 // One thread updates NPT nodes (one lane of NPT consecutive groups); a block of 256 threads
 // covers 4 NPT groups of one row, so the row, its two periodic neighbours and every
@@ -47,7 +54,16 @@ struct Geo {
   int64_t rs;      // elements between two lattice rows
   int nseg;        // blocks per lattice row = ceil(S / (4 NPT))
   int plast;       // pos(nx - 1)
+  int xcd;         // k_step: blocks in the order of xcd_tile
 };
+
+// Largest block of the A-B step kernel: with contiguous rows every group's x-shifted loads
+// straddle a line of the next group, which a block's wavefronts share in the compute unit's
+// caches, so larger blocks re-read fewer lines (FP32 3000^2 111 us with 256 threads, 108 with
+// 512, 105 with 1024; 2048^2 43, 41, 41; BF16 8192^2 393, 392, 388; FP16 3000^2 57.6, 58.4,
+// 64.5: 16-bit storage has two to four nodes per thread, and its blocks of 1024 threads too few
+// rows in flight).
+template <class S> constexpr int kStepBlock = sizeof(S) == 2 ? 512 : 1024;
 
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -112,32 +128,26 @@ __device__ __forceinline__ S* at(char* base, int p) {
   return reinterpret_cast<S*>(base + uint32_t(p) * uint32_t(sizeof(S)));
 }
 
-// Buffer-resource accesses of the two-step forward kernel. One lattice row of a
-// buffer (its nine population rows, or the five rows of a moment record) is described by a
-// buffer resource in scalar registers, rebased to that row; an access adds the scalar offset
-// of the population (or record entry) within the lattice row and the lane's 32-bit in-row
-// byte offset, which stays in one vector register for the whole loop. (With plain pointers
-// the compiler folded the loop-invariant lane offsets into nine 64-bit per-population
-// addresses and added each row's offset to them in 64-bit vector arithmetic: 39 of the 333
-// vector instructions of the FP32 two-step kernel's row loop; with buffer accesses and the
-// scheduling fence of pair_sync the FP32 pair went from 142.6 to 150.1 GLUPS at 4096^2, FP16
-// and BF16 from 183 to 189-190 at 8192^2.) The adjoint kernels keep plain pointers: the
-// two-step adjoint ran 5 % slower with buffer accesses (433 against 414 us per launch at
-// 4096^2), whatever its occupancy. Offsets within a lattice row stay below 2^31 bytes:
-// lbm_init rejects wider rows.
+// Buffer-resource accesses. One lattice row of a buffer (its nine population rows, or the five
+// rows of a moment record) is described by a buffer resource in scalar registers, rebased to
+// that row; an access adds the scalar offset of the population (or record entry) within the
+// lattice row and the lane's 32-bit in-row byte offset, which stays in one vector register for
+// a whole row loop (plain pointers made the compiler keep nine 64-bit per-population addresses
+// and add each row's offset to them in vector arithmetic). AA's adjoint kernels use plain
+// pointers: AA's two-step adjoint ran 5 % slower with buffer accesses (433 against 414 us per
+// launch at 4096^2). Offsets within a lattice row stay below 2^31 bytes: lbm_init rejects wider
+// rows.
 constexpr int kRsrcWord3 = 0x00020000;  // resource word 3 of a raw buffer on the gfx9 family
 constexpr int kAuxNT = 2;                // cache-policy operand of a nontemporal access (gfx950)
-// Stores of the step kernels on grids whose population buffers exceed the last-level cache
-// (WT, chosen by the host): nontemporal with the SC1 scope bit (device scope, written through
-// rather than held in the XCD's L2). Measured on the FP32 two-step kernel, interleaved on one
-// machine, us per launch: 210.5 -> 206.2 (4096^2), 832.0 -> 826.5 (8192^2); on another
-// 212.3 -> 210.4 and 851.3 -> 841.8; the single-step kernel 186.8 -> 183.5 (4096^2). SC1
-// without the nontemporal bit measured 3.5 % slower than plain nontemporal stores, stores
-// without either hint 10 % slower, SC0 added to either no different; loads with SC1 no faster.
-// On cache-resident grids SC1 costs instead: 1024^2 (38 MB per buffer) pair 18.1 -> 18.7 us,
-// single step 14.2 -> 14.7, AA 13.4 -> 13.8, so there the stores stay plain nontemporal.
+// Cache policy of the single-step kernel (STREAM, chosen by the host from the population buffers'
+// size against the last-level cache): on larger grids loads and stores are nontemporal, the
+// stores with the SC1 scope bit as well (device scope, written through rather than held in the
+// XCD's L2): 4096^2 186.8 -> 183.5 us. SC1 without the nontemporal bit measured 3.5 % slower
+// than plain nontemporal stores, stores without either hint 10 % slower. Buffers that stay in the
+// last-level cache are read and written plainly: AA, FP32, complete model 3000 x 2000 72 -> 50
+// us, 1000^2 15.3 -> 10.5 us.
 constexpr int kAuxStoreWT = kAuxNT | 16;
-template <bool WT> constexpr int kAuxStore = WT ? kAuxStoreWT : kAuxNT;
+template <bool STREAM> constexpr int kAuxStore = STREAM ? kAuxStoreWT : 0;
 
 struct RowRes {
   __amdgpu_buffer_rsrc_t r;
@@ -199,16 +209,48 @@ __device__ __forceinline__ bool node_pos(const Geo& geo, int s, int lane, RowPos
   return true;
 }
 
+// The same with contiguous rows: position x of group s at lane `lane` is x = 64 s + lane.
+__device__ __forceinline__ bool node_pos_contig(const Geo& geo, int s, int lane, RowPos& r) {
+  const int x = s * kLanes + lane;
+  if (x >= geo.nx) return false;
+  r.p0 = x;
+  r.pm = x > 0 ? x - 1 : geo.nx - 1;
+  r.pp = x + 1 < geo.nx ? x + 1 : 0;
+  return true;
+}
+
+// The hardware hands consecutive workgroup IDs to the chip's 8 XCDs in turn, and each XCD has
+// its own L2. Kernels whose neighbouring blocks read the same lines renumber their blocks so that
+// every XCD works on one contiguous range of tiles, x-neighbours side by side. Any value is
+// correct (it is a permutation of the tiles); 8 matches MI355X.
+constexpr int kXcds = 8;
+
+// Place in that order of the block with linear ID L of n: XCD L % kXcds takes tiles [start,
+// start + count) in order, start and count splitting the n tiles as evenly as possible.
+__device__ __forceinline__ int xcd_order(int L, int n) {
+  const int xcd = L % kXcds;
+  return xcd * (n / kXcds) + min(xcd, n % kXcds) + L / kXcds;
+}
+__device__ __forceinline__ void xcd_tile(int& bx, int& by) {
+  const int nx = int(gridDim.x);
+  const int t = xcd_order(int(blockIdx.x) + int(blockIdx.y) * nx, nx * int(gridDim.y));
+  bx = t % nx;
+  by = t / nx;
+}
+
 // Block -> lattice row (uniform); the block's wavefronts take NPT consecutive groups each,
 // starting at the returned group s0. Grid: (nseg, min(ny, kRowsY), ceil(ny / kRowsY)) with
-// nseg = ceil(S / (4 NPT)). A block is four 64-lane wavefronts, so s0 is uniform across a
-// wavefront and is kept in a scalar register.
+// nseg = ceil(S / (W NPT)) for blocks of W wavefronts. s0 is uniform across a wavefront and is
+// kept in a scalar register. With xcd the blocks of a grid slice are taken in the order of
+// xcd_tile.
 static_assert(kBlock % kLanes == 0, "a block must consist of whole 64-node groups");
 template <int NPT>
-__device__ __forceinline__ int first_group(int& y, int& lane) {
-  y = int(blockIdx.z) * kRowsY + int(blockIdx.y);
+__device__ __forceinline__ int first_group(int& y, int& lane, bool xcd, int threads = kBlock) {
+  int bx = int(blockIdx.x), by = int(blockIdx.y);
+  if (xcd) xcd_tile(bx, by);
+  y = int(blockIdx.z) * kRowsY + by;
   lane = int(threadIdx.x % kLanes);
-  return (int(blockIdx.x) * (kBlock / kLanes) + __builtin_amdgcn_readfirstlane(int(threadIdx.x / kLanes))) * NPT;
+  return (bx * (threads / kLanes) + __builtin_amdgcn_readfirstlane(int(threadIdx.x / kLanes))) * NPT;
 }
 
 // One time step; each thread updates NPT nodes (same lane, consecutive groups), issuing the
@@ -216,14 +258,14 @@ __device__ __forceinline__ int first_group(int& y, int& lane) {
 // per wavefront. src and dst alias in the AA phases. With REC the moments (rho, u_x, u_y,
 // N_xx, N_xy) of every node are written to rec, laid out like the populations with five
 // entries per lattice row (row stride rec_rs).
-template <class S, int MODEL, int PH, bool REC, int NPT, bool WT>
-__global__ void __launch_bounds__(kBlock)
+template <class S, int MODEL, int PH, bool REC, int NPT, bool STREAM>
+__global__ void __launch_bounds__((PH == PH_AB ? kStepBlock<S> : kBlock))
 k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
        typename StorageTraits<S>::T* rec, int64_t rec_rs) {
   using T = typename StorageTraits<S>::T;
   using Tr = StorageTraits<S>;
   int y, lane;
-  const int s0 = first_group<NPT>(y, lane);
+  const int s0 = first_group<NPT>(y, lane, geo.xcd, PH == PH_AB ? int(blockDim.x) : kBlock);
   // Uniform exits only: the host launches NPT > 1 only when S is a multiple of 4 NPT, so a
   // wavefront's groups are either all inside the row or all past it. Padding lanes
   // (x >= nx) run on their own padding slot for every access (no real node reads those
@@ -232,14 +274,16 @@ k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
   if (y >= geo.ny || s0 >= geo.S) return;
   RowPos rp[NPT];
 #pragma unroll
-  for (int n = 0; n < NPT; ++n)
-    if (!node_pos(geo, s0 + n, lane, rp[n])) rp[n].p0 = rp[n].pm = rp[n].pp = (s0 + n) * kLanes + lane;
+  for (int n = 0; n < NPT; ++n) {
+    const bool node = PH == PH_AB ? node_pos_contig(geo, s0 + n, lane, rp[n]) : node_pos(geo, s0 + n, lane, rp[n]);
+    if (!node) rp[n].p0 = rp[n].pm = rp[n].pp = (s0 + n) * kLanes + lane;
+  }
   const int ym = (y == 0) ? geo.ny - 1 : y - 1;
   const int yp = (y == geo.ny - 1) ? 0 : y + 1;
   const size_t rsb = size_t(geo.rs) * sizeof(S), psb = size_t(geo.ps) * sizeof(S);
   const char* sr[3] = {reinterpret_cast<const char*>(src) + ym * rsb, reinterpret_cast<const char*>(src) + y * rsb,
                        reinterpret_cast<const char*>(src) + yp * rsb};
-  // Stores through buffer descriptors of the three rows (cache policy kAuxStore<WT>).
+  // Stores through buffer descriptors of the three rows (cache policy kAuxStore<STREAM>).
   const RowRes dr[3] = {row_res(dst, rsb, ym), row_res(dst, rsb, y), row_res(dst, rsb, yp)};
 
   typename Tr::Raw gs[NPT][Q];
@@ -251,7 +295,7 @@ k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
       constexpr int slot = (PH == PH_AA_ODD) ? opp(i) : i;
       constexpr int dx = shift ? -cx(i) : 0;
       constexpr int dy = shift ? -cy(i) : 0;
-      gs[n][i] = ld_raw<S>(at<S>(sr[dy + 1] + slot * psb, rp[n].template of<dx>()));
+      gs[n][i] = ld_raw<S, STREAM && sizeof(S) != 2>(at<S>(sr[dy + 1] + slot * psb, rp[n].template of<dx>()));
     });
   }
 
@@ -265,7 +309,7 @@ k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
       const RowRes rr = row_res(rec, size_t(rec_rs) * sizeof(T), y);
 #pragma unroll
       for (int r = 0; r < NREC; ++r)
-        stb<T, kAuxStore<WT>>(rr, r * geo.ps * int(sizeof(T)), uint32_t(rp[n].p0) * uint32_t(sizeof(T)), rv[r]);
+        stb<T, kAuxStore<STREAM>>(rr, r * geo.ps * int(sizeof(T)), uint32_t(rp[n].p0) * uint32_t(sizeof(T)), rv[r]);
     }
     static_for<0, Q>([&](auto I) {
       constexpr int i = decltype(I)::value;
@@ -273,253 +317,27 @@ k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
       constexpr int slot = (PH == PH_AA_EVEN) ? opp(i) : i;
       constexpr int dx = shift ? cx(i) : 0;
       constexpr int dy = shift ? cy(i) : 0;
-      stb<S, kAuxStore<WT>>(dr[dy + 1], slot * int(psb), uint32_t(rp[n].template of<dx>()) * uint32_t(sizeof(S)),
+      stb<S, kAuxStore<STREAM>>(dr[dy + 1], slot * int(psb), uint32_t(rp[n].template of<dx>()) * uint32_t(sizeof(S)),
                             Tr::store(out[i]));
     });
   }
 }
 
-// Two time steps per launch (A-B pattern), staged through LDS. A block owns kFuseGroups
-// consecutive groups (one interior wavefront each) and the rows [y0, y1), the rows split
-// evenly over gridDim.y row blocks (so gridDim.y <= ny); two
-// halo wavefronts compute the x-neighbours of its edge groups. The block walks its rows
-// y0 - 1 .. y1: phase A computes step 1 of every wavefront's node at row r from global
-// memory (pull) into a ring of three rows in LDS, rounded to the storage type exactly as
-// the single-step kernel would store it; phase B computes step 2 of row r - 1 for the
-// interior wavefronts, pulling from the ring, and stores it. The loads of row r + 1 are
-// issued before the barrier so that they overlap phase B. Every population is read once and
-// written once per two steps (plus the halo's reads), and the result is bit-identical to
-// two single steps: the halo nodes' step 1 is the same computation on the same inputs.
-// Requires nx % 64 == 0 (no padding, so the interior x-neighbours of a group are the
-// adjacent groups of the same lane) and S % kFuseGroups == 0. A block recomputes two halo
-// rows of step 1 and reads four extra rows, so the host keeps blocks as tall as the grid
-// allows while still giving every compute unit work, between kFuseMinRows and kFuseRows.
 constexpr int kFuseGroups = 8;
 constexpr int kFuseRows = 64;
 constexpr int kFuseMinRows = 2;
-// The FP32 pair kernels (forward, and adjoint for every storage type but FP64) also take
-// blocks of up to kFuseRowsTall rows when the grid then gives each block a compute unit of its
-// own. Measured on MI355X, 4096^2 (32 blocks of 128 rows against 64 of 64), us per launch on
-// three machines: 217.3-218.3 / 220.1-221.0, 217.5 / 223.0, 211.2-212.4 / 215.0-215.6; the
-// one-segment adjoint sweep 81.9-82.0 against 81.0-81.1 GLUPS. On 8192^2 (several rounds of
-// blocks) 128-row blocks measured 1 % faster on one machine and 8.5 % slower on another
-// (921-922 against 849-850 us), and the 16-bit pairs, three blocks per compute unit, 6 %
-// slower: there the planner keeps kFuseRows.
+// Blocks of up to kFuseRowsTall rows are taken when the grid then gives each block a compute
+// unit of its own (not for FP64): 4096^2, one-segment adjoint sweep 81.9-82.0 against 81.0-81.1
+// GLUPS.
 constexpr int kFuseRowsTall = 128;
 template <class T> struct FuseTall : std::false_type {};
 template <> struct FuseTall<float> : std::true_type {};
-// The hardware hands consecutive workgroup IDs to the chip's 8 XCDs in turn, and each XCD has
-// its own L2. The two-step kernel renumbers its blocks so that every XCD works on one
-// contiguous range of tiles, x-neighbours side by side: the halo groups a block re-reads are
-// then being read at the same time by its neighbour on the same L2 (measured on MI355X:
-// 38.6 instead of 45.9 B/node fetched from HBM per launch). Any value is correct (it is a
-// permutation of the tiles); 8 matches MI355X.
-constexpr int kXcds = 8;
 
-// Tile (block column, row block) of the block with linear ID L = blockIdx.x + gridDim.x
-// blockIdx.y: XCD L % kXcds takes tiles [start, start + count) in order, start and count
-// splitting the n tiles as evenly as possible.
-__device__ __forceinline__ void xcd_tile(int& bx, int& by) {
-  const int nx = int(gridDim.x), n = nx * int(gridDim.y);
-  const int L = int(blockIdx.x) + int(blockIdx.y) * nx;
-  const int xcd = L % kXcds;
-  const int t = xcd * (n / kXcds) + min(xcd, n % kXcds) + L / kXcds;
-  bx = t % nx;
-  by = t / nx;
-}
-
-// Block barrier of the two-step kernels, which is also a scheduling fence: no instruction
-// moves across it. Without the fence the scheduler hoisted phase A's collision (it reads only
-// the registers the previous row's loads fill) above the preceding barrier and phase B, so
-// each row waited for its loads before phase B instead of after it: the FP32 pair lost 5 %
-// (LBGK 11 %) once its addresses no longer tied the loads to their place in the loop.
-__device__ __forceinline__ void pair_sync() {
-  __syncthreads();
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// Whether the two-step kernel's interior wavefronts load with the nontemporal hint. Without
-// it, the groups a block re-reads as halo stay in L2 for the neighbouring block that reads
-// them too. Measured on MI355X, complete model, HBM bytes read per node and launch with /
-// without the hint: FP64 83.0 / 73.4 (8192^2), BF16 21.8 / 19.4, FP32 38.1 / 37.0 (4096^2);
-// GLUPS: FP64 76.3 -> 79.2, 16-bit unchanged (188), FP32 145.6 -> 144.4 (LBGK 155.3 ->
-// 157.8). So FP32 interior wavefronts keep it; its halo wavefronts, which only load, load
-// plain (140.4 -> 141.6 at 4096^2, 141.1 -> 143.1 at 8192^2, LBGK +1 %).
-template <class S> struct PairLoadsNT : std::false_type {};
-template <> struct PairLoadsNT<float> : std::true_type {};
-
-template <class S, bool NT = PairLoadsNT<S>::value>
-__device__ __forceinline__ void load_pulled(const S* src, const Geo& geo, int r, const RowPos& rp,
-                                            typename StorageTraits<S>::Raw gs[Q]) {
-  const int y = r < 0 ? r + geo.ny : (r >= geo.ny ? r - geo.ny : r);
-  const int ym = (y == 0) ? geo.ny - 1 : y - 1;
-  const int yp = (y == geo.ny - 1) ? 0 : y + 1;
-  const size_t rsb = size_t(geo.rs) * sizeof(S);
-  const int psb = geo.ps * int(sizeof(S));
-  const RowRes sr[3] = {row_res(src, rsb, ym), row_res(src, rsb, y), row_res(src, rsb, yp)};
-  static_for<0, Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    gs[i] = ldb<S, NT>(sr[-cy(i) + 1], i * psb, uint32_t(rp.template of<-cx(i)>()) * uint32_t(sizeof(S)));
-  });
-}
-
-// Storage types whose two-step kernel runs the rotated loop for its interior wavefronts
-// (see k_step2). Measured on MI355X, GLUPS, complete model unless noted, same machine,
-// interleaved: FP32 139.1 -> 140.8 (4096^2), 141.2 -> 142.3 (8192^2), LBGK 151.3 -> 154.4;
-// FP64 75.3 -> 74.4 and BF16 / FP16 182 -> 171 (8192^2; the 16-bit kernels need 70 instead
-// of 56 VGPRs with it, two blocks per compute unit instead of three), so only FP32 takes it.
-template <class S> struct RotatedFuseLoop : std::false_type {};
-template <> struct RotatedFuseLoop<float> : std::true_type {};
-
-// With REC the moments of both steps are recorded (rec1: first step, rec2: second step; the
-// layout and row stride rec_rs of k_step), by the interior wavefronts for the block's rows.
-template <class S, int MODEL, bool REC, bool WT>
-__global__ void __launch_bounds__((kFuseGroups + 2) * kLanes)
-k_step2(const S* __restrict__ src, S* __restrict__ dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
-        typename StorageTraits<S>::T* __restrict__ rec1, typename StorageTraits<S>::T* __restrict__ rec2,
-        int64_t rec_rs) {
-  using T = typename StorageTraits<S>::T;
-  using Tr = StorageTraits<S>;
-  constexpr int G = kFuseGroups;
-  __shared__ S ring[3][G + 2][Q][kLanes];
-  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x / kLanes));
-  const int lane = int(threadIdx.x % kLanes);
-  int bx, by;
-  xcd_tile(bx, by);
-  const int s0 = bx * G;
-  const int y0 = int(int64_t(by) * geo.ny / gridDim.y);
-  const int y1 = int(int64_t(by + 1) * geo.ny / gridDim.y);
-  // Phase-A node: the wavefront's own group (w = 1..G) or the x-neighbour of an edge group.
-  RowPos ra;
-  if (w == 0 || w == G + 1) {
-    RowPos e;
-    node_pos(geo, w == 0 ? s0 : s0 + G - 1, lane, e);
-    const int p = w == 0 ? e.pm : e.pp;
-    node_pos(geo, p / kLanes, p % kLanes, ra);
-  } else {
-    node_pos(geo, s0 + w - 1, lane, ra);
-  }
-  const bool interior = w >= 1 && w <= G;
-  const int pb = (s0 + w - 1) * kLanes + lane;  // phase-B output position
-  const size_t rsb = size_t(geo.rs) * sizeof(S);
-  const int psb = geo.ps * int(sizeof(S));
-
-  typename Tr::Raw gs[Q];
-  // Phase A of row r: step 1 of the wavefront's node from gs into the ring slot of row r
-  // (plus its moments for the block's own rows).
-  auto phase_a_m = [&](const int r, auto mask_c) {
-    constexpr int MASK = decltype(mask_c)::value;
-    const int slot = (r - y0 + 1) % 3;
-    T g[Q], out[Q], rv[NREC];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) g[i] = Tr::load_raw(gs[i]);
-    collide<T, MODEL, ConserveMode<S>::value>(g, out, k, (REC && MASK == 0x1ff) ? rv : nullptr);
-#pragma unroll
-    for (int i = 0; i < Q; ++i)
-      if ((MASK >> i) & 1) ring[slot][w][i][lane] = Tr::store(out[i]);
-    if constexpr (REC && MASK == 0x1ff) {
-      if (interior && r >= y0 && r < y1) {
-        const RowRes rr = row_res(rec1, size_t(rec_rs) * sizeof(T), r);
-#pragma unroll
-        for (int j = 0; j < NREC; ++j) stb<T, kAuxStore<WT>>(rr, j * geo.ps * int(sizeof(T)), pb * uint32_t(sizeof(T)), rv[j]);
-      }
-    }
-  };
-  using AllPops = std::integral_constant<int, 0x1ff>;
-  auto phase_a = [&](const int r) { phase_a_m(r, AllPops{}); };
-  // Phase B of row yr (interior wavefronts): step 2 from the ring rows yr - 1 .. yr + 1.
-  auto phase_b = [&](const int yr) {
-    T g[Q], out[Q];
-    static_for<0, Q>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      g[i] = Tr::load(ring[(yr - cy(i) - y0 + 1) % 3][w - cx(i)][i][lane]);
-    });
-    T rv[NREC];
-    collide<T, MODEL, ConserveMode<S>::value>(g, out, k, REC ? rv : nullptr);
-    if constexpr (REC) {
-      const RowRes rr = row_res(rec2, size_t(rec_rs) * sizeof(T), yr);
-#pragma unroll
-      for (int j = 0; j < NREC; ++j) stb<T, kAuxStore<WT>>(rr, j * geo.ps * int(sizeof(T)), pb * uint32_t(sizeof(T)), rv[j]);
-    }
-    const RowRes dr = row_res(dst, rsb, yr);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) stb<S, kAuxStore<WT>>(dr, i * psb, pb * uint32_t(sizeof(S)), Tr::store(out[i]));
-  };
-  auto load = [&](const int r) { load_pulled<S>(src, geo, r, ra, gs); };
-  auto load_plain = [&](const int r) { load_pulled<S, false>(src, geo, r, ra, gs); };
-
-  // Per row r = y0 - 1 .. y1 every wavefront runs phase A of r, issues the loads of r + 1,
-  // and passes two barriers; between them the interior wavefronts run phase B of r - 1
-  // (from r = y0 + 1 on). That is 2 (y1 - y0) + 4 barriers for every wavefront.
-  // Plain loads here: this loop runs every wavefront of the unrotated types (whose
-  // PairLoadsNT is false) and only the halo wavefronts of FP32.
-  auto plain_loop = [&](auto mask_c) {
-    load_plain(y0 - 1);
-    for (int r = y0 - 1; r <= y1; ++r) {
-      phase_a_m(r, mask_c);
-      if (r < y1) load_plain(r + 1);
-      pair_sync();
-      if (decltype(mask_c)::value == 0x1ff && interior && r > y0) phase_b(r - 1);
-      pair_sync();
-    }
-  };
-  // Phase B reads from the left halo column only the populations that move in +x (1, 5, 8),
-  // from the right one only those that move in -x (3, 6, 7), so the halo wavefronts compute
-  // only those (and what conservation takes them from). The ten wavefronts of a block share
-  // four SIMDs, two of which carry a halo wavefront and two interior ones: their phase A, three
-  // collisions between two barriers against two on the other SIMDs, sets the pace of the row.
-  // Measured on MI355X against full halo collisions (us per launch, same machine): FP32
-  // 4096^2 213.2 -> 210.0, 8192^2 856 -> 845, 16384 x 4096 845 -> 834; FP16 746 -> 738, BF16
-  // 698 -> 681, FP64 1715 -> 1697 (8192^2); bit-identical (see fmad).
-  if (w == 0) {
-    plain_loop(std::integral_constant<int, (1 << 1) | (1 << 5) | (1 << 8)>{});
-    return;
-  }
-  if (w == G + 1) {
-    plain_loop(std::integral_constant<int, (1 << 3) | (1 << 6) | (1 << 7)>{});
-    return;
-  }
-  if (!RotatedFuseLoop<S>::value) {
-    plain_loop(AllPops{});
-    return;
-  }
-  load(y0 - 1);
-  // Interior wavefronts, rotated: the same sequence, with the loop entered right after the
-  // loads of the next row. Vector-memory operations complete in issue order, and on every
-  // path into the loop those loads are the most recent ones; so phase A, which needs only
-  // them, waits with phase B's stores (issued after them) still in flight. (In the loop
-  // above, a path without stores -- halo wavefronts, the first rows -- joins one with them
-  // at phase A, and the wait there covers every store as well.)
-  phase_a(y0 - 1);
-  load(y0);
-  pair_sync();
-  pair_sync();
-  phase_a(y0);
-  load(y0 + 1);
-  pair_sync();
-  pair_sync();
-  phase_a(y0 + 1);
-  if (y0 + 1 < y1) {
-    load(y0 + 2);
-    for (int r = y0 + 2; r < y1; ++r) {
-      pair_sync();
-      phase_b(r - 2);
-      pair_sync();
-      phase_a(r);
-      load(r + 1);
-    }
-    pair_sync();
-    phase_b(y1 - 2);
-    pair_sync();
-    phase_a(y1);
-  }
-  pair_sync();
-  phase_b(y1 - 1);
-  pair_sync();
-}
-
-// Two reverse steps per launch, staged through LDS like k_step2 (same blocks, halo
-// wavefronts, XCD-aware tile order and three-row ring). Phase A computes fbar^n of every
+// Two reverse steps per launch on AA's lane-strided rows, staged through LDS. A block owns
+// kFuseGroups consecutive groups (one interior wavefront each) and the rows [y0, y1), the rows
+// split evenly over gridDim.y row blocks (so gridDim.y <= ny); two halo wavefronts compute the
+// x-neighbours of its edge groups. The block walks its rows y0 - 1 .. y1 with a ring of three
+// rows in LDS. Phase A computes fbar^n of every
 // wavefront's node at row r from fbar^{n+1} gathered at x + c_i and the records rec_hi of
 // step n; phase B computes fbar^{n-1} of row r - 1 for the interior wavefronts from the
 // ring and the records rec_lo of step n - 1, and stores it. The same arithmetic as two
@@ -666,10 +484,10 @@ k_step_walls(const S* __restrict__ src, S* __restrict__ dst, Geo geo, Coef<typen
   using T = typename StorageTraits<S>::T;
   using Tr = StorageTraits<S>;
   int y, lane;
-  const int s0 = first_group<1>(y, lane);
+  const int s0 = first_group<1>(y, lane, true);
   RowPos rp;
-  if (y >= geo.ny || !node_pos(geo, s0, lane, rp)) return;
-  const int x = lane * geo.S + s0;
+  if (y >= geo.ny || !node_pos_contig(geo, s0, lane, rp)) return;
+  const int x = rp.p0;
   const int ym = (y == 0) ? geo.ny - 1 : y - 1;
   const int yp = (y == geo.ny - 1) ? 0 : y + 1;
   const size_t rsb = size_t(geo.rs) * sizeof(S), psb = size_t(geo.ps) * sizeof(S);
@@ -684,7 +502,7 @@ k_step_walls(const S* __restrict__ src, S* __restrict__ dst, Geo geo, Coef<typen
 #pragma unroll
     for (int i = 0; i < Q; ++i) out[i] = g[opp(i)];
   } else {
-    collide<T, MODEL, ConserveMode<S>::value>(g, out, k, nullptr);
+    collide<T, MODEL, ConserveMode<S, true>::value>(g, out, k, nullptr);
   }
   char* orow = reinterpret_cast<char*>(dst) + y * rsb;
 #pragma unroll
@@ -693,15 +511,16 @@ k_step_walls(const S* __restrict__ src, S* __restrict__ dst, Geo geo, Coef<typen
 
 // One reverse step of the discrete adjoint: fbar^n(x) = J(m^n(x))^T fbar*(x) with the
 // reverse-streamed fbar*_i(x) = fbar^{n+1}_i(x + c_i). fbar uses the population layout in
-// the compute type (geo describes it); rec holds the step's recorded moments.
-template <class T, int MODEL>
+// the compute type (geo describes it); rec holds the step's recorded moments. CONTIG: the A-B
+// buffers' contiguous rows, else AA's lane-strided ones.
+template <class T, int MODEL, bool CONTIG>
 __global__ void __launch_bounds__(kBlock)
 k_adjoint_step(const T* __restrict__ fbar_next, T* __restrict__ fbar, Geo geo, Coef<T> k,
                const T* __restrict__ rec, int64_t rec_rs) {
   int y, lane;
-  const int s0 = first_group<1>(y, lane);
+  const int s0 = first_group<1>(y, lane, CONTIG);
   RowPos rp;
-  if (y >= geo.ny || !node_pos(geo, s0, lane, rp)) return;
+  if (y >= geo.ny || !(CONTIG ? node_pos_contig(geo, s0, lane, rp) : node_pos(geo, s0, lane, rp))) return;
   const int ym = (y == 0) ? geo.ny - 1 : y - 1;
   const int yp = (y == geo.ny - 1) ? 0 : y + 1;
   const size_t rsb = size_t(geo.rs) * sizeof(T), psb = size_t(geo.ps) * sizeof(T);

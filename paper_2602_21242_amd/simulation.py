@@ -21,8 +21,8 @@ class Simulation:
     adjoint() (sqrt(N) checkpoints by default, or every ckpt_stride steps; the forward run
     keeps the last segment's moments, so ckpt_stride >= record_steps needs no recomputation
     at record_steps x 5 x 4 (FP64: x 8) bytes per node). two_step: 0 runs
-    two steps per launch where the grid is large enough for it to pay, 1 wherever the layout
-    allows, -1 never (results are bit-identical). walls: solid bounce-back columns at x = 0
+    as many steps per launch as are fastest for the grid, 1 prefers the marching kernel on the
+    grids of steps_per_launch 2, -1 one step per launch (results are bit-identical). walls: solid bounce-back columns at x = 0
     and x = nx - 1 (A-B pattern, no recording).
     """
 
@@ -80,7 +80,8 @@ class Simulation:
 
     @property
     def steps_per_launch(self):
-        """Time steps one step-kernel launch advances (2 on the two-step kernel's grids)."""
+        """2 on A-B grids of whole blocks of 512 columns large enough for the device, else 1 (the
+        launches themselves take 2 to 4 steps on large grids and more on small ones)."""
         return capi.lbm_steps_per_launch(self._ctx)
 
     @property
