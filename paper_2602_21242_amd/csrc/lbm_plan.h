@@ -42,19 +42,22 @@ struct CostModel {
   double wave = 0;       // marching and single step: one SIMD's time for a 64-lane collision
   double tile_wave = 0;  // the same inside a tile, LDS accesses included
   double tile_memory = 0;           // bytes per us of a tile's loads and stores
+  double march_launch = 0;          // marching: dispatch, the first loads, the last stores
+  double march_alone = 0;           // share of a SIMD's cycles that one wavefront issues in
+  double march_many = 0;            // and that very many would
+  bool march_spread = false;        // three and more wavefronts per SIMD even out over the SIMDs
+  double march_memory = 0;          // bytes per us, the halos of the reverse march included
   double single_launch = 0;         // single step: dispatch, first loads, last stores
   double single_issue = 0;          // and the share of a SIMD's cycles it issues in
   int regs[kTileConfigCount] = {};  // vector registers of the tile kernel's instances
   int max_cells = 0;                // largest instance that does not spill
 };
-constexpr double kMarchLaunch = 5.0;   // dispatch, the first loads, the last stores
 constexpr double kTileLaunch = 4.2;
 constexpr double kTileStep = 0.11;     // a step's barrier and LDS latency
 constexpr double kTileRound = 0.8;     // a further round of blocks on the same compute unit
 constexpr double kTileAlone = 1.12;    // nothing else on the compute unit to fill a block's waits
 constexpr double kTileSerial = 1.35;   // blocks one after the other on a compute unit that holds one
 constexpr double kMemory = 6.5e6;      // bytes per us of the single step
-constexpr double kMarchMemory = 5.5e6; // the same of the marching kernels, halos included
 
 // By bytes per stored value (reverse steps: of the compute type). The wavefront times are vector
 // instructions per collision at 2.4 GHz, a quarter of a wavefront per cycle.
@@ -64,9 +67,14 @@ inline CostModel cost_model(int bytes, bool bgk, bool adjoint, bool bf16 = false
   const double instr = adjoint ? (bgk ? 110 : f64 ? 260 : 200) : f64 ? (bgk ? 120 : 181) : half ? (bgk ? 130 : bf16 ? 150 : 180) : (bgk ? 95 : 145);
   c.wave = instr * 4.0 / 2400.0;
   c.tile_wave = f64 ? (bgk ? 0.19 : 0.25) : half ? (bgk ? 0.19 : 0.23) : (bgk ? 0.135 : 0.17);
-  c.tile_memory = adjoint ? 12e6 : half ? 5.7e6 : 9e6;
+  c.tile_memory = adjoint ? 12e6 : half ? 6.5e6 : 9e6;
   c.bytes = 18.0 * bytes;
-  c.single_launch = half ? 2.6 : 1.8;
+  c.march_launch = adjoint ? 5.0 : 3.0;
+  c.march_alone = adjoint ? 0.7 : f64 ? 0.63 : half && !bf16 ? 0.8 : half ? 0.73 : 0.79;
+  c.march_many = adjoint ? 1.0 : f64 ? 0.78 : half ? 1.03 : 0.95;
+  c.march_memory = adjoint ? 5.5e6 : half && bf16 ? 5.0e6 : 4.6e6;
+  c.march_spread = half;
+  c.single_launch = half ? 2.4 : 1.8;
   c.single_issue = half ? 0.69 : 0.6;
   c.rec_bytes = adjoint ? 5.0 * bytes : 0.0;
   const int one = f64 ? 96 : 64, two = f64 ? 128 : adjoint ? 96 : 80;
@@ -111,8 +119,12 @@ inline int64_t steps_ahead(int64_t m, int march, int tile) {
 }
 
 // Row blocks and steps per launch of least time per step. A SIMD works through its share of the
-// strips' row blocks; a block of h rows costs steps * (h + steps - 1) collisions. horizon: steps
-// come in runs of that many (0: many).
+// strips' row blocks; a block of h rows costs steps * (h + steps - 1) collisions, and more
+// wavefronts per SIMD fill more of each other's waits. Fitted to 300 launches from 1000^2 to
+// 8192^2 (7 to 9 % off in the mean, the picked plan within 4 % of the fastest one): FP16 8192^2
+// 388 us per step with two wavefronts per SIMD and two steps, 326 with six and three; BF16 340 and
+// 284; FP64 2024^2 40.3 with one wavefront, 38.5 with two; FP32 2048^2 24.4 with three steps, 22.8
+// with four. horizon: steps come in runs of that many (0: many).
 inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, int max_waves, int cus, int64_t horizon,
                             const CostModel& cm) {
   MarchPlan best;
@@ -127,11 +139,19 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
       const int64_t rows = (ny + nrb - 1) / nrb;
       const int64_t rounds = (cols * nrb * waves + int64_t(cus) * 4 - 1) / (int64_t(cus) * 4);
       auto launch = [&](int64_t steps) {
-        // A SIMD with one wavefront waits for it a fifth of the time.
-        const double issue = double(rounds) * double(steps * (rows + steps - 1)) * npl * cm.wave / (rounds < 2 ? 0.8 : 0.95);
+        const double share = cm.march_spread && rounds > 2 ? double(cols * nrb * waves) / (cus * 4.0) : double(rounds);
+        const double rate = cm.march_many - (cm.march_many - cm.march_alone) / double(rounds);
+        const double issue = share * double(steps * (rows + steps - 1)) * npl * cm.wave / rate * (waves > 1 ? 1.01 : 1.0);
+        // The forward march's halo reads hit the caches; near balance its issue and its accesses
+        // delay each other (a norm of order 6), while reverse steps hide one behind the other.
+        if (cm.rec_bytes == 0) {
+          const double mem = double(nx) * ny * cm.bytes / cm.march_memory;
+          const double i3 = issue * issue * issue, m3 = mem * mem * mem;
+          return cm.march_launch + std::max(2.0, std::cbrt(std::sqrt(i3 * i3 + m3 * m3)));
+        }
         const double halo_reads = 64.0 * npl / p.w * double(rows + 2 * (steps - 1)) / double(rows);
-        const double mem = double(nx) * ny * (cm.bytes / 2 * (1 + halo_reads) + steps * cm.rec_bytes * halo_reads) / kMarchMemory;
-        return kMarchLaunch + std::max(issue, mem);
+        const double mem = double(nx) * ny * (cm.bytes / 2 * (1 + halo_reads) + steps * cm.rec_bytes * halo_reads);
+        return cm.march_launch + std::max(issue, mem / cm.march_memory);
       };
       for (int steps = 2; steps <= max_steps; ++steps) {
         double us = launch(steps) / steps;
