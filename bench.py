@@ -102,11 +102,25 @@ def make_sim(w, model, storage, pattern, fields, **kw):
                       pattern=pattern, **kw)
 
 
+def launch_steps(sim, nx, ny):
+    """Steps of one launch of lbm_step(n) for a run of many steps, complete model, on MI355X (the
+    cost model's choice on grids of 4096^2 and more; other grids: 1 where steps_per_launch is 1,
+    else 2 as a lower bound)."""
+    from paper_2602_21242_amd import capi
+    if sim.steps_per_launch == 1:
+        return 1
+    if nx * ny < 4096 * 4096:
+        return 2
+    if sim.params.storage in (capi.LBM_F64, capi.LBM_F32):
+        return 4
+    return 3 if nx * ny >= 8192 * 8192 else 2
+
+
 def spin_up(sim, seconds):
     """Keep the GPU busy with steps of `sim` (a throwaway context) for about `seconds`, and
     return with a last chunk still queued, so that work enqueued next starts without an idle
     gap. The GPU's clocks change after every idle period: the first milliseconds of a burst of
-    two-step launches run fast, the next 15-20 ms up to 1.5x slower, then the launches settle
+    launches run fast, the next 15-20 ms up to 1.5x slower, then the launches settle
     (measured per launch on MI355X), and only the steady state says what a long run gets."""
     import torch
     chunk = 16 * sim.steps_per_launch
@@ -305,32 +319,28 @@ def main():
     # same configuration, with no pause between the spin-up, the warm-up and the timed steps.
     sim = make_sim(w, args.model, args.storage, args.pattern, fields)
     spin = make_sim(w, args.model, args.storage, args.pattern, fields)
-    spl = 1 if args.single_step else sim.steps_per_launch
+    spl = 1 if args.single_step else launch_steps(sim, w.nx, w.ny)
     ms = timer(sim, args.steps, args.warmup, spin=spin, spin_s=args.spin_up)
     del spin
     inv = sim.invariants(allow_nonfinite=True)
     del sim
     glups = nodes / (ms * 1e-3) / 1e9
     launch_s = spl * ms * 1e-3
-    # Roofline: one read and one write of the nine populations per node update (72 B in FP32)
-    # times the updates of one launch, over the launch time. A launch of the two-step kernel
-    # performs two updates and keeps the intermediate state in LDS, so its own floor is one
-    # read and one write per launch (36 B per update in FP32), reported as pair_floor.
-    achieved = ALG_BYTES[args.storage] * spl * nodes / launch_s / 1e9
+    # Roofline. A launch reads and writes the nine populations of a node once (72 B in FP32)
+    # whatever number of steps it takes; `achieved` is that over the launch time. A single step is
+    # bound by this traffic; with several steps per launch the vector instructions bind, and
+    # hbm_frac_per_update says how far the run is beyond one read and one write per update.
+    achieved = ALG_BYTES[args.storage] * nodes / launch_s / 1e9
     log(f"[bench] {ms:.4f} ms/step ({spl} step(s) per launch), {glups:.2f} GLUPS "
         f"(cold {cold_ms:.4f} ms/step, {nodes / (cold_ms * 1e-3) / 1e9:.2f} GLUPS), "
-        f"{achieved:.0f} GB/s algorithmic at {ALG_BYTES[args.storage]} B per node update")
+        f"{achieved:.0f} GB/s algorithmic at {ALG_BYTES[args.storage]} B per node and launch")
     traffic = load_traffic(w.name, args.model, args.storage, args.pattern)
-    kernel = (f"k_step2<{args.storage},{args.model}>" if spl == 2 else f"k_step<{args.storage},{args.model},{args.pattern}>")
-    roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    kernel = (f"k_march<{args.storage},{args.model},{spl}>" if spl > 1 else f"k_step<{args.storage},{args.model},{args.pattern}>")
+    roofline = {"bound": "hbm" if spl == 1 else "vector issue", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kernel, "steps_per_launch": spl,
-                "alg_bytes_per_node_update": ALG_BYTES[args.storage], "launch_us": launch_s * 1e6,
+                "alg_bytes_per_node_launch": ALG_BYTES[args.storage],
+                "hbm_frac_per_update": achieved * spl / HBM_PEAK_GBS, "launch_us": launch_s * 1e6,
                 "traffic_frac": None if traffic is None else traffic / launch_s / 1e9 / HBM_PEAK_GBS}
-    if spl == 2:
-        floor = ALG_BYTES[args.storage] * nodes / launch_s / 1e9
-        roofline["pair_floor"] = {"bytes_per_node_update": ALG_BYTES[args.storage] // 2, "achieved": floor,
-                                  "frac": floor / HBM_PEAK_GBS}
-
     out = {
         "metric": METRIC, "value": glups, "unit": "GLUPS", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
@@ -360,7 +370,7 @@ def main():
                                    ("uc", "aa"), ("partial", "aa")):
                 log(f"[bench] variant tg4096 {model} f32 {pattern}")
                 s = make_sim(w, model, "f32", pattern, fields)
-                sp = s.steps_per_launch
+                sp = launch_steps(s, w.nx, w.ny)
                 m = time_steady(s, steps_v)
                 res[f"tg4096/{model}/f32/{pattern}"] = {
                     "ms_per_step": m, "GLUPS": nodes / (m * 1e-3) / 1e9, "steps_per_launch": sp,
@@ -389,12 +399,11 @@ def main():
             for storage in ("f64", "f32", "f16", "bf16"):
                 log(f"[bench] variant turb8192 complete {storage} ab")
                 s = make_sim(wt, "complete", storage, "ab", tf)
-                sp = s.steps_per_launch
+                sp = launch_steps(s, wt.nx, wt.ny)
                 m = time_steady(s, 200)
                 ent = {"ms_per_step": m, "GLUPS": nt / (m * 1e-3) / 1e9, "steps_per_launch": sp,
                        "hbm_frac_per_update": ALG_BYTES[storage] * nt / (m * 1e-3) / 1e9 / HBM_PEAK_GBS}
-                if sp == 2:
-                    ent["pair_floor_frac"] = ALG_BYTES[storage] * nt / (sp * m * 1e-3) / 1e9 / HBM_PEAK_GBS
+                ent["hbm_frac_per_launch"] = ent["hbm_frac_per_update"] / sp
                 del s
                 res[f"turb8192/complete/{storage}/ab"] = ent
             return res
