@@ -46,6 +46,7 @@ struct CostModel {
   double march_alone = 0;           // share of a SIMD's cycles that one wavefront issues in
   double march_many = 0;            // and that very many would
   bool march_spread = false;        // three and more wavefronts per SIMD even out over the SIMDs
+  double march_memory_alone = 0;    // bytes per us with one wavefront per SIMD, whose rows stay closer together
   double march_memory = 0;          // bytes per us, the halos of the reverse march included
   double single_launch = 0;         // single step: dispatch, first loads, last stores
   double single_issue = 0;          // and the share of a SIMD's cycles it issues in
@@ -71,9 +72,10 @@ inline CostModel cost_model(int bytes, bool bgk, bool adjoint, bool bf16 = false
   c.tile_memory = adjoint ? 12e6 : half ? 6.5e6 : 9e6;
   c.bytes = 18.0 * bytes;
   c.march_launch = adjoint ? 5.0 : 3.0;
-  c.march_alone = adjoint ? 0.7 : f64 ? 0.63 : half && !bf16 ? 0.8 : half ? 0.73 : 0.79;
+  c.march_alone = adjoint ? 0.7 : f64 ? 0.63 : half && !bf16 ? 0.8 : 0.73;
   c.march_many = adjoint ? 1.0 : f64 ? 0.78 : half ? 1.03 : 0.95;
-  c.march_memory = adjoint ? 5.5e6 : half && bf16 ? 5.0e6 : 4.6e6;
+  c.march_memory = adjoint ? 5.5e6 : half ? (bf16 ? 5.0e6 : 4.6e6) : 4.45e6;
+  c.march_memory_alone = adjoint || half ? c.march_memory : f64 ? 4.65e6 : 5.1e6;
   c.march_spread = half;
   c.single_launch = half ? 2.4 : 1.8;
   c.single_issue = half ? 0.69 : 0.6;
@@ -125,7 +127,7 @@ inline int64_t steps_ahead(int64_t m, int march, int tile) {
 // 8192^2 (7 to 9 % off in the mean, the picked plan within 4 % of the fastest one): FP16 8192^2
 // 388 us per step with two wavefronts per SIMD and two steps, 326 with six and three; BF16 340 and
 // 284; FP64 2024^2 40.3 with one wavefront, 38.5 with two; FP32 2048^2 24.4 with three steps, 22.8
-// with four. horizon: steps come in runs of that many (0: many).
+// with four; FP32 LBGK 4096^2, bound by memory, 63.6 with one wavefront per SIMD, 72.3 with three. horizon: steps come in runs of that many (0: many).
 inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, int max_waves, int cus, int64_t horizon,
                             const CostModel& cm) {
   MarchPlan best;
@@ -146,7 +148,7 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
         // The forward march's halo reads hit the caches; near balance its issue and its accesses
         // delay each other (a norm of order 6), while reverse steps hide one behind the other.
         if (cm.rec_bytes == 0) {
-          const double mem = double(nx) * ny * cm.bytes / cm.march_memory;
+          const double mem = double(nx) * ny * cm.bytes / (rounds < 2 ? cm.march_memory_alone : cm.march_memory);
           const double i3 = issue * issue * issue, m3 = mem * mem * mem;
           return cm.march_launch + std::max(2.0, std::cbrt(std::sqrt(i3 * i3 + m3 * m3)));
         }
@@ -161,7 +163,8 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
           for (int64_t m = horizon; m > 0; m -= steps_ahead(m, steps, 0)) us += launch(steps_ahead(m, steps, 0));
           us /= double(horizon);
         }
-        if (us < best.us_per_step * 0.999) {
+        // Fewer, longer row blocks unless more of them gain a hundredth.
+        if (us < best.us_per_step * 0.99) {
           best = p;
           best.steps = steps;
           best.nrb = int(nrb);
