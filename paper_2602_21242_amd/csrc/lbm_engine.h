@@ -34,10 +34,10 @@ struct RunDesc {
 };
 
 // Where a run's population buffers (both of A-B, the one of AA) stop fitting the 256 MB last-level
-// cache well enough for plain accesses to win, us per step plain/streaming: A-B FP32 302 MB
-// 40/48, 319 MB 48/53, 355 MB 61/58, FP16 325 MB 61/58, FP64 332 MB 56/54; AA FP32 350 MB 120/146,
-// BF16 302 MB 87/98, FP64 295 MB 87/105, 382 MB 131/123. A-B's write-once streams evict each
-// other earlier than AA's reads and writes of the same lines.
+// cache well enough for plain accesses to win, us per step plain/streaming on uniform fields: A-B
+// FP32 302 MB 40/48, 319 MB 48/53, 355 MB 61/58, FP16 325 MB 61/58, FP64 332 MB 56/54; AA FP32
+// 350 MB 120/146, BF16 302 MB 87/98, FP64 295 MB 87/105, 382 MB 131/123. A-B's write-once streams
+// evict each other earlier than AA's reads and writes of the same lines.
 constexpr int64_t kStreamBytesAB = int64_t(304) << 20, kStreamBytesAA = int64_t(352) << 20;
 // Up to here the step's blocks run in XCD order, which keeps a row's neighbours of the previous
 // step in the same L2: AA FP32 1000^2 11.7 -> 10.4 us, 2700^2 (267 MB) 68 -> 61, A-B FP32 1700^2

@@ -46,7 +46,7 @@ struct CostModel {
   double march_alone = 0;           // share of a SIMD's cycles that one wavefront issues in
   double march_many = 0;            // and that very many would
   bool march_spread = false;        // three and more wavefronts per SIMD even out over the SIMDs
-  double march_memory_alone = 0;    // bytes per us with one wavefront per SIMD, whose rows stay closer together
+  double march_memory_alone = 0;    // bytes per us, one wavefront per SIMD: its rows stay close
   double march_memory = 0;          // bytes per us, the halos of the reverse march included
   double single_launch = 0;         // single step: dispatch, first loads, last stores
   double single_issue = 0;          // and the share of a SIMD's cycles it issues in
@@ -127,7 +127,8 @@ inline int64_t steps_ahead(int64_t m, int march, int tile) {
 // 8192^2 (7 to 9 % off in the mean, the picked plan within 4 % of the fastest one): FP16 8192^2
 // 388 us per step with two wavefronts per SIMD and two steps, 326 with six and three; BF16 340 and
 // 284; FP64 2024^2 40.3 with one wavefront, 38.5 with two; FP32 2048^2 24.4 with three steps, 22.8
-// with four; FP32 LBGK 4096^2, bound by memory, 63.6 with one wavefront per SIMD, 72.3 with three. horizon: steps come in runs of that many (0: many).
+// with four; FP32 LBGK 4096^2, bound by memory, 63.6 with one wavefront per SIMD, 72.3 with three.
+// horizon: steps come in runs of that many (0: many).
 inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, int max_waves, int cus, int64_t horizon,
                             const CostModel& cm) {
   MarchPlan best;
