@@ -46,7 +46,7 @@ struct Plan {
   size_t red_off = 0, res_off = 0;
   int64_t stride = 0;                 // checkpoint spacing s
   int64_t nck = 0;                    // checkpoints at t = 0, s, 2s, ... (< N)
-  size_t ckpt_off = 0;                // nck + 1 slots (the last holds the state at t = N)
+  size_t ckpt_off = 0;                // nck + 1 slots (the last: the sweep's second buffer)
   size_t rec_off = 0, rec_slot_bytes = 0;
   size_t fbar_off[2] = {0, 0}, fbar_bytes = 0;
   size_t total = 0;
@@ -223,20 +223,20 @@ lbm_status check_ctx(const lbm_ctx* c) {
 
 lbm_status reduce_totals(lbm_ctx* c, double* partial, double* result, double out[3]);
 
-// ns steps in one launch from the current state into dst; rec (or null) receives the moment
+// ns steps in one launch from the state src of time t into dst; rec (or null) receives the moment
 // records of the steps, one slot after the other. Out of place, except AA's own buffer (ns = 1).
-lbm_status launch_steps(lbm_ctx* c, int64_t ns, void* dst, void* rec) {
+lbm_status launch_steps(lbm_ctx* c, int64_t ns, int64_t t, const void* src, void* dst, void* rec) {
   return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
     using E = decltype(eng);
     using T = typename E::T;
     hipError_t e;
     if (ns == 1) {
-      const int ph = c->p.pattern == LBM_AB ? lbm::PH_AB : ((c->time & 1) ? lbm::PH_AA_ODD : lbm::PH_AA_EVEN);
-      e = E::step(c->d, ph, c->state(), dst, rec, c->stream);
+      const int ph = c->p.pattern == LBM_AB ? lbm::PH_AB : ((t & 1) ? lbm::PH_AA_ODD : lbm::PH_AA_EVEN);
+      e = E::step(c->d, ph, src, dst, rec, c->stream);
     } else {
       const int64_t slot = int64_t(c->plan.rec_slot_bytes / sizeof(T));
-      e = c->d.tile.steps > 0 ? E::tile(c->d, int(ns), c->state(), dst, static_cast<T*>(rec), slot, c->stream)
-                              : E::march(c->d, int(ns), c->state(), dst, static_cast<T*>(rec), slot, c->stream);
+      e = c->d.tile.steps > 0 ? E::tile(c->d, int(ns), src, dst, static_cast<T*>(rec), slot, c->stream)
+                              : E::march(c->d, int(ns), src, dst, static_cast<T*>(rec), slot, c->stream);
     }
     if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("step kernel launch: ") + hipGetErrorString(e));
     return LBM_OK;
@@ -247,7 +247,7 @@ lbm_status launch_steps(lbm_ctx* c, int64_t ns, void* dst, void* rec) {
 // or buffer 0 from a checkpoint slot.
 lbm_status do_steps(lbm_ctx* c, int64_t ns, void* rec) {
   const int b = c->state_slot < 0 && c->p.pattern == LBM_AB ? 1 - c->cur : 0;
-  const lbm_status s = launch_steps(c, ns, c->ws + c->plan.pop_off[b], rec);
+  const lbm_status s = launch_steps(c, ns, c->time, c->state(), c->ws + c->plan.pop_off[b], rec);
   if (s != LBM_OK) return s;
   c->cur = b;
   c->state_slot = -1;
@@ -257,7 +257,7 @@ lbm_status do_steps(lbm_ctx* c, int64_t ns, void* rec) {
 
 // ns steps into checkpoint slot k, which then holds the state (the next step reads it there).
 lbm_status steps_into_ckpt(lbm_ctx* c, int64_t ns, int64_t k, void* rec) {
-  const lbm_status s = launch_steps(c, ns, c->ckpt(k), rec);
+  const lbm_status s = launch_steps(c, ns, c->time, c->state(), c->ckpt(k), rec);
   if (s != LBM_OK) return s;
   c->state_slot = k;
   c->cur = 0;
@@ -308,8 +308,9 @@ lbm_status step_graph(lbm_ctx* c, hipGraphExec_t* out) {
 // launch reads the checkpoint slot directly, so no copy restores it), then traversed
 // backwards with the adjoint kernels. The last segment's moments are usually still in the
 // slots from the forward run, which recorded them; with a single segment (stride >= N)
-// nothing is recomputed at all. The state at N is in checkpoint slot nck, where the forward run
-// left it, and is the current state again at the end.
+// nothing is recomputed at all. The state at N stays where it is: the recomputed segments go
+// back and forth between the slot after the last checkpoint and the population buffer that does
+// not hold it (AA: stay in that slot).
 lbm_status sweep(lbm_ctx* c, int* out_b) {
   const int64_t N = c->p.record_steps, s = c->plan.stride;
   const lbm::RunDesc& d = c->d;
@@ -321,11 +322,16 @@ lbm_status sweep(lbm_ctx* c, int* out_b) {
       // The slots are about to hold this segment's moments (cleared first, so that a sweep
       // that fails part-way never leaves the flag on overwritten slots).
       c->last_seg_recorded = false;
-      c->time = t0;
-      c->state_slot = k;
-      while (c->time < t1) {
-        st = do_steps(c, lbm::steps_ahead(t1 - c->time, d.march.steps, d.tile.steps), c->rec_slot(c->time - t0));
+      void* const slot = c->ckpt(c->plan.nck);
+      void* const other = c->p.pattern == LBM_AB ? c->ws + c->plan.pop_off[1 - c->cur] : slot;
+      const void* src = c->ckpt(k);
+      for (int64_t t = t0; t < t1;) {
+        const int64_t ns = lbm::steps_ahead(t1 - t, d.march.steps, d.tile.steps);
+        void* const dst = src == slot ? other : slot;
+        st = launch_steps(c, ns, t, src, dst, c->rec_slot(t - t0));
         if (st != LBM_OK) return st;
+        src = dst;
+        t += ns;
       }
     }
     // Reverse steps t = t1 - 1 .. t0, several per launch (t, t - 1, ...) where the plan says so.
@@ -353,9 +359,6 @@ lbm_status sweep(lbm_ctx* c, int* out_b) {
       t -= ns;
     }
   }
-  c->time = N;
-  c->state_slot = c->plan.nck;
-  c->cur = 0;
   *out_b = b;
   return LBM_OK;
 }
@@ -491,12 +494,12 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
         HIP_TRY(hipMemcpyAsync(c->ckpt(seg), c->state(), c->plan.pop_bytes, hipMemcpyDeviceToDevice, c->stream));
       // A launch stays within its checkpoint segment. Steps of the last segment keep their
       // moments for the reverse sweep (slot t - t_last). A launch that ends the segment writes
-      // the state into the next checkpoint's slot, at t = N into the slot after the last one.
+      // the state into the next checkpoint's slot (at t = N there is none).
       const int64_t seg_end = std::min((seg + 1) * c->plan.stride, N);
       const bool keep = c->time >= t_last;
       const int64_t ns = lbm::steps_ahead(std::min(n - k, seg_end - c->time), c->d.march.steps, c->d.tile.steps);
       void* rec = keep ? c->rec_slot(c->time - t_last) : nullptr;
-      s = c->time + ns == seg_end ? steps_into_ckpt(c, ns, seg + 1, rec) : do_steps(c, ns, rec);
+      s = c->time + ns == seg_end && seg_end < N ? steps_into_ckpt(c, ns, seg + 1, rec) : do_steps(c, ns, rec);
       if (s != LBM_OK) return s;
       if (keep && c->time == N) c->last_seg_recorded = true;
       k += ns;
