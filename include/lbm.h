@@ -135,7 +135,14 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t workspace_byt
  * is LBM_ERR_INVALID_ARGUMENT. While the context records (record_steps > 0), the state at
  * every checkpoint time below record_steps is saved and the steps of the last checkpoint
  * segment also write their moments for the reverse sweep; stepping past record_steps is
- * allowed but disables lbm_adjoint. */
+ * allowed but disables lbm_adjoint.
+ * The calls may be captured into a HIP graph (on the context's stream; lbm_time counts the
+ * captured steps, not the replays). A replay goes on from the state and buffer that the capture
+ * started from, so it advances the state if the captured calls end in that buffer and so do the
+ * eager calls between replays. Outside the recorded window, counting
+ * ceil(n / lbm_steps_per_launch) launches for each call, that is with LBM_AB when their sum is
+ * even and with LBM_AA when the sum of the steps is. (The launches themselves may be fewer; a
+ * context that has been captured keeps them odd or even as counted.) */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t n);
 
 /* Density and velocity rho = sum_i f_i, u = sum_i c_i f_i / rho (the macroscopic densities the

@@ -162,6 +162,11 @@ struct lbm_ctx {
   // The record slots hold the moments of the last segment's steps, written by the forward
   // run, so the reverse sweep need not recompute that segment.
   bool last_seg_recorded = false;
+  // Work of this context was captured into a graph. Its replays read and write the population
+  // buffers of the capture, so from then on every A-B call of lbm_step flips the buffers as often
+  // as launches of lbm_steps_per_launch steps would, odd or even, whatever the plan: which calls
+  // can be replayed, and mixed with eager ones, does not depend on the launch plans.
+  bool captured = false;
   // Step graphs, built on first use: [A-B buffer index or AA phase parity at the start].
   hipStream_t capture = nullptr;  // private stream, used only to record the graphs
   hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -263,6 +268,22 @@ lbm_status steps_into_ckpt(lbm_ctx* c, int64_t ns, int64_t k, void* rec) {
   c->cur = 0;
   c->time += ns;
   return LBM_OK;
+}
+
+// Notes whether the context's stream is being captured (the null stream cannot be).
+void note_capture(lbm_ctx* c) {
+  if (c->captured || !c->stream || c->p.pattern != LBM_AB) return;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (cs == hipStreamCaptureStatusNone) return;
+  c->captured = true;
+  dispatch_int(c->p.storage, [&](auto eng) {
+    decltype(eng)::plan(c->d, c->p.two_step, c->plan.stride, true);
+    return 0;
+  });
 }
 
 bool is_small(const lbm_ctx* c) { return int64_t(c->d.pitch) * c->d.ny <= kGraphMaxPositions; }
@@ -438,7 +459,7 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t workspace_byt
     d.stream = population_bytes >= (d.contig ? lbm::kStreamBytesAB : lbm::kStreamBytesAA);
     d.xcd = population_bytes <= (storage_size(p->storage) == 2 ? lbm::kXcdBytes16 : lbm::kXcdBytes);
     dispatch_int(p->storage, [&](auto eng) {
-      decltype(eng)::plan(d, p->two_step, plan.stride);
+      decltype(eng)::plan(d, p->two_step, plan.stride, false);
       return 0;
     });
     c->time = 0;
@@ -466,9 +487,11 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
     if (s != LBM_OK) return s;
     if (n < 0) return fail(LBM_ERR_INVALID_ARGUMENT, "n must be >= 0");
     DeviceGuard g(c->device);
+    note_capture(c);
     const int64_t N = c->p.record_steps;
     const bool small = is_small(c) && c->d.tile.steps == 0 && c->d.march.steps == 0;
     const int64_t t_last = N > 0 ? (c->plan.nck - 1) * c->plan.stride : 0;  // last segment's start
+    int odd = -1;  // captured: whether the launches that are left outside the window are odd in number
     for (int64_t k = 0; k < n;) {
       const bool recording = N > 0 && c->rec_valid && c->time < N;
       if (!recording) {
@@ -481,7 +504,14 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
           k += kGraphSteps;
           continue;
         }
-        const int64_t ns = lbm::steps_ahead(n - k, c->d.march.steps, c->d.tile.steps);
+        int64_t ns;
+        if (c->captured) {
+          if (odd < 0) odd = int((lbm_steps_per_launch(c) == 2 ? (n - k + 1) / 2 : n - k) & 1);
+          ns = lbm::steps_ahead_parity(n - k, c->d.march.steps, c->d.tile.steps, odd);
+          odd ^= 1;
+        } else {
+          ns = lbm::steps_ahead(n - k, c->d.march.steps, c->d.tile.steps);
+        }
         s = do_steps(c, ns, nullptr);
         if (s != LBM_OK) return s;
         k += ns;
@@ -514,6 +544,7 @@ lbm_status lbm_moments(lbm_ctx* c, lbm_dtype out_dtype, void* d_rho, void* d_ux,
     if (s != LBM_OK) return s;
     if (out_dtype != LBM_F64 && out_dtype != LBM_F32) return fail(LBM_ERR_UNSUPPORTED, "moments: output must be F64 or F32");
     DeviceGuard g(c->device);
+    note_capture(c);
     return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
       using E = decltype(eng);
       hipError_t e = E::moments(c->d, c->layout(c->time), c->state(), out_dtype == LBM_F64, d_rho, d_ux, d_uy, c->stream);
@@ -530,6 +561,7 @@ lbm_status lbm_get_populations(lbm_ctx* c, lbm_dtype out_dtype, void* d_f) {
     if (!d_f) return fail(LBM_ERR_INVALID_ARGUMENT, "output is NULL");
     if (out_dtype != LBM_F64 && out_dtype != LBM_F32) return fail(LBM_ERR_UNSUPPORTED, "populations: output must be F64 or F32");
     DeviceGuard g(c->device);
+    note_capture(c);
     return dispatch(c->p.storage, [&](auto eng) -> lbm_status {
       using E = decltype(eng);
       hipError_t e = E::get(c->d, c->layout(c->time), c->state(), out_dtype == LBM_F64, d_f, c->stream);
@@ -545,6 +577,7 @@ lbm_status lbm_set_populations(lbm_ctx* c, const double* d_f) {
     if (s != LBM_OK) return s;
     if (!d_f) return fail(LBM_ERR_INVALID_ARGUMENT, "input is NULL");
     DeviceGuard g(c->device);
+    note_capture(c);
     if (c->time != 0) c->rec_valid = false;
     c->last_seg_recorded = false;
     // The new state goes to a population buffer; a checkpoint slot keeps what it holds.

@@ -64,8 +64,9 @@ struct Engine {
   static hipError_t tile(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
                          hipStream_t st);
   // Fills the run's plans for the current device (mode: lbm_params.two_step; segment: steps of a
-  // recorded run's checkpoint segments, 0: no recording).
-  static void plan(RunDesc& d, int mode, int64_t segment);
+  // recorded run's checkpoint segments, 0: no recording). captured: no plan of single steps alone
+  // where lbm_steps_per_launch reports 2 (see lbm_ctx::captured).
+  static void plan(RunDesc& d, int mode, int64_t segment, bool captured);
   static hipError_t init(const RunDesc& d, LayoutSel L, void* buf, const double* rho, const double* ux,
                          const double* uy, hipStream_t st);
   static hipError_t get(const RunDesc& d, LayoutSel L, const void* buf, bool out_f64, void* out, hipStream_t st);

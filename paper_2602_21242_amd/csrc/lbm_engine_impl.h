@@ -665,15 +665,16 @@ inline int plan_row_blocks(const RunDesc& d, int mode, bool tall, int cus) {
 }
 
 template <class S>
-void plan_steps(RunDesc& d, int cus, bool force_march, int64_t horizon) {
+void plan_steps(RunDesc& d, int cus, bool force_march, bool no_single, int64_t horizon) {
   using T = typename StorageTraits<S>::T;
   // The tile kernel addresses a whole buffer with 32-bit byte offsets.
   const bool tiles = d.rs * d.ny * int64_t(sizeof(T)) < (int64_t(1) << 31);
   auto choose = [&](MarchPlan& march, TilePlan& tile, double single) {
+    const bool several = no_single && (march.steps || tile.steps);
     if (force_march && march.steps) tile.steps = 0;
     else if (march.us_per_step < tile.us_per_step) tile.steps = 0;
     else march.steps = 0;
-    if (!force_march && single < march.us_per_step && single < tile.us_per_step) march.steps = tile.steps = 0;
+    if (!force_march && !several && single < march.us_per_step && single < tile.us_per_step) march.steps = tile.steps = 0;
   };
   const CostModel cm = cost_model(int(sizeof(S)), d.model == M_BGK, false, std::is_same_v<S, bf16_t>);
   if (!d.walls) d.march = plan_march(d.nx, d.ny, MarchNodes<S>::value, kMarchHalo, kMarchMax, kMarchWaves, cus, horizon, cm);
@@ -688,7 +689,7 @@ void plan_steps(RunDesc& d, int cus, bool force_march, int64_t horizon) {
 }
 
 template <class S>
-void Engine<S>::plan(RunDesc& d, int mode, int64_t segment) {
+void Engine<S>::plan(RunDesc& d, int mode, int64_t segment, bool captured) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -703,7 +704,7 @@ void Engine<S>::plan(RunDesc& d, int mode, int64_t segment) {
   // mode 1 takes the marching kernel on every grid of whole pairs (the documented rule), mode 0
   // whatever the cost model finds fastest.
   const bool force = mode == 1 && d.nx % kLanes == 0 && (d.pitch / kLanes) % kFuseGroups == 0;
-  plan_steps<S>(d, cus, force, segment);
+  plan_steps<S>(d, cus, force, captured && pair, segment);
 }
 
 // f(std::bool_constant<contiguous rows>).

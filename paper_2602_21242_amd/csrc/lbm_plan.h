@@ -121,6 +121,14 @@ inline int64_t steps_ahead(int64_t m, int march, int tile) {
   return 1;
 }
 
+// The same where the launches that are left have to be odd or even in number: the call then ends
+// in the buffer it started from, or in the other one, whatever the plan. march or tile >= 2; one
+// step cannot take an even number of launches.
+inline int64_t steps_ahead_parity(int64_t m, int march, int tile, bool odd) {
+  const int64_t ns = steps_ahead(m, march, tile);
+  return ns > 1 && m - ns == int64_t(odd) ? ns - 1 : ns;
+}
+
 // Row blocks and steps per launch of least time per step. A SIMD works through its share of the
 // strips' row blocks; a block of h rows costs steps * (h + steps - 1) collisions, and more
 // wavefronts per SIMD fill more of each other's waits. Fitted to 300 launches from 1000^2 to

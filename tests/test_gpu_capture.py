@@ -63,3 +63,50 @@ def test_replays_past_a_recorded_run_advance(pattern, stride, adjoint):
         _replay(s, g)
         b.step(2)
         assert _equal(s, a, b)
+
+
+# Calls whose launches, lbm_steps_per_launch steps each, are even in number (AA: whose steps are):
+# boxes on which the plans take tiles, one block for the whole box, walls, the marching kernel, and
+# (512 x 2000) single steps.
+CALLS = [(64, 64, "f64", {}, (16,)), (200, 130, "f32", {}, (2,)), (7, 90, "f64", {}, (64,)),
+         (256, 256, "f32", {}, (20,)), (256, 256, "f32", {}, (3, 1)), (801, 3, "f64", dict(walls=True), (16,)),
+         (2041, 1200, "f32", {}, (2,)), (2041, 1200, "bf16", {}, (5, 1)), (2048, 1100, "f32", {}, (4,)),
+         (2048, 1100, "f64", {}, (3,)), (2048, 1100, "f32", {}, (1, 2)), (512, 2000, "f16", {}, (3,)),
+         (512, 100, "f32", dict(two_step=1), (4,)), (512, 100, "f32", dict(two_step=-1), (10,)),
+         (200, 130, "f32", dict(pattern="aa"), (3, 1))]
+
+
+@pytest.mark.parametrize("nx,ny,storage,kw,calls", CALLS)
+def test_captured_calls_replay(nx, ny, storage, kw, calls):
+    """The rule of lbm_step's documentation, with the same calls made eagerly between replays."""
+    s, a, b = _pair(nx, ny, storage, **kw)
+    spl = a.steps_per_launch
+    assert sum(calls if kw.get("pattern") == "aa" else ((n + spl - 1) // spl for n in calls)) % 2 == 0
+
+    def run(sim):
+        for n in calls:
+            sim.step(n)
+
+    g = _capture(s, lambda: run(a))
+    for k in range(4):
+        if k == 2:
+            run(a)
+        else:
+            _replay(s, g)
+        s.synchronize()
+        run(b)
+        assert _equal(s, a, b), k
+
+
+def test_captured_readout_follows_eager_steps():
+    """A captured readout alone: eager calls of an even count leave the state in its buffer."""
+    import torch
+    s, a, b = _pair(200, 130, "f32")
+    out = []
+    g = _capture(s, lambda: out.append(a.populations()))
+    for n in (2, 8, 20):
+        a.step(n)
+        s.synchronize()
+        _replay(s, g)
+        b.step(n)
+        assert torch.equal(out[0], b.populations()), n
