@@ -402,17 +402,26 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
 // -e_y on (z, q), e = theta (1 - theta) + u^2 (u^2 - 1), and K on the four with q or d on both
 // axes. The corrections only reweight F: psi takes the (d, z) and (z, d) parts out of the OReg
 // population's weights (partial and complete model), and the prefactor moves Q from (q, z) to
-// (z, q). Checked against the complex-step derivative of the literal collision. About 190 vector
+// (z, q). Checked against the complex-step derivative of the literal collision. About 195 vector
 // instructions for the FP32 complete model, against 325 for the same forms summed over c. Every
 // fused product is written out, so that all reverse kernels agree bit for bit.
 //
-// Where fbar* varies little over the nine populations, as in a smooth flow, all but (z, z) are
-// small: they are formed from differences to v_0, and every output is fbs_0 plus a sum of small
-// terms, rounded once, since errors of one sign over smooth regions add up over the steps.
-// Enstrophy gradient of the 16384 x 4096 shear layer along the perturbation, FP32 against FP64
-// central differences: 2.8e-6 after 500 steps and 9.7e-5 after 3000 (sums over c: 4.1e-6 and
-// 8.6e-5; equally exact arrangements of this code between 1.0e-4 and 1.1e-4, one with sums of
-// the full values 1.7e-4): at 3000 steps it is the FP32 trajectory that is off.
+// Every output is written as fbs_i plus one sum of small terms: the part of fbs that the collision
+// keeps (multiples of 1, c_x and c_y: mass and momentum) is not recomputed, only the second
+// differences are, so a single rounding at the size of fbs_i is left. Adding the same terms to the
+// momentum part one by one lost all below half a unit in its last place, where the flow is smooth
+// always on the same side: the adjoint's diffusion of long waves (2e-8 of the momentum part per
+// step) went missing. Enstrophy gradient of the 16384 x 4096 shear layer along the perturbation,
+// FP32 against FP64 central differences, over four realizations of the initial state:
+//                             500 steps           3000 steps
+//   this                      -2.3e-6, -6.1e-6    -2.9e-5 to 3.9e-5
+//   this evaluated in FP64    -2.5e-6, -5.4e-6    -2.8e-5 to 3.9e-5 (the FP32 run's own error)
+//   terms one by one           2.8e-6, -2.2e-6    -2.1e-4 to -9.7e-5
+//   sums over c                4.1e-6,  0.4e-6    -5.7e-5 to  8.6e-5
+// Root mean square error of the gradient of 400 steps of a shear layer at 333 x 190 against FP64:
+// 1.2e-7, one by one 4.6e-6, sums over c 4.7e-6. It costs 4 vector instructions and, with the nine
+// fbs held to the end, 8 to 18 registers (8 reverse steps of 1024^2 140 -> 143 us, of 4096^2 1632
+// -> 1641).
 template <class T, int MODEL>
 __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], const Coef<T>& k, T fbar[Q]) {
 #pragma clang fp contract(off)
@@ -427,30 +436,35 @@ __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], c
   const T Fzq = zu + zl, Fzd = zu - zl;
   const T Fqz = q0, Fqq = fmad(T(-2), q0, qp + qm), Fqd = qp - qm;
   const T Fdz = d0, Fdq = fmad(T(-2), d0, dp + dm), Fdd = dp - dm;
-  // Equilibrium part rho A0 B0 (shifted by a constant): value fbs_0 + e0, twice the derivatives ex2, ey2.
-  const T htx = h * (k.th + x2), hty = h * (k.th + y2);
-  const T vq = fmad(huy, Fqd, fmad(hty, Fqq, Fqz));
-  const T vd = fmad(huy, Fdd, fmad(hty, Fdq, Fdz));
-  const T fx = T(2) * ux, fy = T(2) * uy;
-  const T e0 = fmad(hux, vd, fmad(htx, vq, fmad(huy, Fzd, hty * Fzq)));
-  const T ex2 = fmad(fx, vq, vd);
-  const T ey2 = fmad(hux, fmad(fy, Fdq, Fdd), fmad(htx, fmad(fy, Fqq, Fqd), fmad(fy, Fzq, Fzd)));
+  // Equilibrium part rho A0 B0: with dJ/dj = dJ/du / rho, the terms that are linear in fbs beyond
+  // the kept ones. t: dJ/drho - fbs_0 at fixed j; rx, ry: 2 dJ/dj - Fdz, Fzd.
+  const T htx = h * (k.th + x2), hty = h * (k.th + y2), fx = T(2) * ux, fy = T(2) * uy;
+  const T nq = fmad(huy, Fqd, hty * Fqq), nd = fmad(hty, Fdq, huy * Fdd), vq = Fqz + nq;
+  const T e1 = fmad(fy, Fdq, Fdd), e2 = fmad(fy, Fqq, Fqd), me = fmad(hux, e1, htx * e2);
+  const T te = fmad(-huy, me, fmad(k.th - htx, vq, (k.th - hty) * Fzq));
+  const T rx = fmad(fx, vq, nd), ry = fmad(fy, Fzq, me);
+  // fbar_i = fbs_i + w (what m's adjoints (t, jx, jy, Db, Nb) give more than fbs's own expansion
+  // in c beyond 1, c_x, c_y); w = 1, but 1/tau for LBGK, which keeps omb fbs.
+  auto assemble = [&](T t, T jx, T jy, T Db, T Nb) {
+    constexpr bool BGK = MODEL == M_BGK;
+    const T w = T(1) - k.omb;
+    auto put = [&](int i, T a) { fbar[i] = BGK ? fmad(w, a, fbs[i]) : fbs[i] + a; };
+    const T tx = fmad(-h, Fqz, BGK ? t : t + Db), ty = fmad(-h, Fzq, BGK ? t : t - Db);
+    const T td = fmad(-h, Fqz + Fzq, t), u5 = BGK ? td : td + Nb, u6 = BGK ? td : td - Nb;
+    const T a5 = fmad(T(-0.25), Fqq + Fdd, u5), a6 = fmad(T(-0.25), Fqq - Fdd, u6);
+    const T b5 = fmad(T(-0.25), Fdq + Fqd, jx + jy), b8 = fmad(T(-0.25), Fdq - Fqd, jx - jy);
+    put(0, t);
+    put(1, tx + jx);
+    put(2, ty + jy);
+    put(3, tx - jx);
+    put(4, ty - jy);
+    put(5, a5 + b5);
+    put(6, a6 - b8);
+    put(7, a5 - b5);
+    put(8, a6 + b8);
+  };
   if (MODEL == M_BGK) {
-    // The equilibrium weighted 1 - omb = 1/tau, and omb fbs directly: fbs_i = fbs_0 + (fbs_i -
-    // fbs_0). dJ/dj = dJ/du / rho.
-    const T es = T(1) - k.omb, hes = h * es;
-    const T jxb = hes * ex2, jyb = hes * ey2;
-    const T t = fmad(-jyb, uy, fmad(-jxb, ux, es * e0));
-    const T tp = t + jxb, tm = t - jxb;
-    fbar[0] = z0 + t;
-    fbar[1] = z0 + fmad(k.omb, p0, tp);
-    fbar[2] = z0 + fmad(k.omb, zu, t + jyb);
-    fbar[3] = z0 + fmad(k.omb, m0, tm);
-    fbar[4] = z0 + fmad(k.omb, zl, t - jyb);
-    fbar[5] = z0 + fmad(k.omb, fbs[5] - z0, tp + jyb);
-    fbar[6] = z0 + fmad(k.omb, fbs[6] - z0, tm + jyb);
-    fbar[7] = z0 + fmad(k.omb, fbs[7] - z0, tm - jyb);
-    fbar[8] = z0 + fmad(k.omb, fbs[8] - z0, tp - jyb);
+    assemble(te, h * rx, h * ry, T(0), T(0));
     return;
   }
   // Per-axis moments.
@@ -477,20 +491,14 @@ __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], c
     Wqz = Wqz - Qw;
     Wzq = Wzq + Qw;
   }
-  // N_xx: twice the form, S, and its u-derivatives over two.
+  // N_xx: twice the form, S, and its u-derivatives over two. The coefficients with q or d on both
+  // axes, as sums over the y-index first.
+  const T hq = fmad(b21, Fqd, b22 * Fqq), hd = fmad(b21, Fdd, b22 * Fdq);
   T S = fmad(ex, Wqz, -(ey * Wzq));
-  S = fmad(fmad(a22, hty, -(htx * b22)), Fqq, S);
-  S = fmad(fmad(a22, huy, -(htx * b21)), Fqd, S);
-  S = fmad(fmad(a21, hty, -(hux * b22)), Fdq, S);
-  S = fmad(Kdd, Fdd, S);
-  T Sx = fmad(dex, Wqz, Kddx * Fdd);
-  Sx = fmad(fmad(da, hty, -(hux * b22)), Fqq, Sx);
-  Sx = fmad(fmad(da, huy, -(hux * b21)), Fqd, Sx);
-  Sx = fmad(fmad(hda, hty, T(-0.25) * b22), Fdq, Sx);
-  T Sy = fmad(-dey, Wzq, Kddy * Fdd);
-  Sy = fmad(fmad(a22, huy, -(htx * db)), Fqq, Sy);
-  Sy = fmad(fmad(T(0.25), a22, -(htx * hdb)), Fqd, Sy);
-  Sy = fmad(fmad(a21, huy, -(hux * db)), Fdq, Sy);
+  S = fmad(-hux, hd, fmad(-htx, hq, fmad(a21, nd, fmad(a22, nq, S))));
+  T Sx = fmad(T(-0.25), hd, fmad(hda, nd, fmad(-hux, hq, fmad(da, nq, dex * Wqz))));
+  T Sy = fmad(T(0.25), fmad(a22, e2, a21 * e1), -(dey * Wzq));
+  Sy = fmad(-hux, fmad(hdb, Fdd, db * Fdq), fmad(-htx, fmad(hdb, Fqd, db * Fqq), Sy));
   if (MODEL == M_UC) {
     S = fmad(ux * (k.c3 - x2), Fdz, fmad(-uy * (k.c3 - y2), Fzd, S));
     Sx = fmad(h * fmad(T(-3), x2, k.c3), Fdz, Sx);
@@ -502,26 +510,17 @@ __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], c
   const T Nxxb = k.omb_inv4th2 * S;
   const T Nxyb = k.omb_inv4th2 * fmad(a12, g1, k.th * g2);
   // dJ/du through N, then the chain (rho, u, N) -> (rho, j, D, P_xy).
-  const T rinv = recip(rho), hrho = h * rho;
-  const T uxb = fmad(hrho, ex2, fmad(ky * fmad(T(-3), x2, k.r0), g1, fmad(kx, Sx, uxc)));
-  const T uyb = fmad(hrho, ey2, fmad(ky * fmad(T(-3), y2, k.r0), g3, fmad(kx, Sy, uyc)));
+  const T rinv = recip(rho);
+  const T uxb = fmad(ky * fmad(T(-3), x2, k.r0), g1, fmad(kx, Sx, uxc));
+  const T uyb = fmad(ky * fmad(T(-3), y2, k.r0), g3, fmad(kx, Sy, uyc));
   const T jxb = fmad(uxb, rinv, -fmad(Nxxb, ux, Nxyb * uy));
   const T jyb = fmad(uyb, rinv, fmad(Nxxb, uy, -(Nxyb * ux)));
   const T Db = h * Nxxb;
-  // dJ/drho = fbs_0 + e0 - Nxxb (ux^2 - uy^2)/2 - Nxyb ux uy - (dJ/dj) . u
-  T t = fmad(Db, dy2, e0);
+  // dJ/drho - fbs_0 = te - Nxxb (ux^2 - uy^2)/2 - Nxyb ux uy - (jxb, jyb) . u
+  T t = fmad(Db, dy2, te);
   t = fmad(-Nxyb * ux, uy, t);
   t = fmad(-jyb, uy, fmad(-jxb, ux, t));
-  const T tx = t + Db, ty = t - Db, tp = t + jyb, tm = t - jyb, xp = jxb + Nxyb, xm = jxb - Nxyb;
-  fbar[0] = z0 + t;
-  fbar[1] = z0 + (tx + jxb);
-  fbar[2] = z0 + (ty + jyb);
-  fbar[3] = z0 + (tx - jxb);
-  fbar[4] = z0 + (ty - jyb);
-  fbar[5] = z0 + (tp + xp);
-  fbar[6] = z0 + (tp - xp);
-  fbar[7] = z0 + (tm - xm);
-  fbar[8] = z0 + (tm + xm);
+  assemble(t, fmad(h, rx, jxb), fmad(h, ry, jyb), Db, Nxyb);
 }
 
 }  // namespace lbm

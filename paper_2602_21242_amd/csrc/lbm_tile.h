@@ -45,11 +45,17 @@ struct TileCells {
   S c[Q][CELLS + 2];
 };
 
+// Least wavefronts per SIMD that the registers have to allow. FP32 reverse tiles of one node per
+// thread want 70 registers, which leaves a compute unit one block of 1024 threads; held to 64 (one
+// spilled) it takes two: 8 reverse steps of 1024^2 in one segment 155.8 -> 142.8 us.
+template <class S, int M, int KIND>
+constexpr int kTileWaves = KIND == TILE_ADJOINT && sizeof(S) == 4 && M == 1 ? 8 : 1;
+
 // KIND TILE_STEP / TILE_WALLS: ns forward steps (with the bounce-back columns of k_step_walls);
 // TILE_REC: step s also writes its moments to rec + s rec_slot; TILE_ADJOINT: ns reverse steps
 // on fbar (S is the compute type), reverse step s with the moments at rec - s rec_slot.
 template <class S, int MODEL, int NT, int M, int KIND>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, (kTileWaves<S, M, KIND>))
 k_tile(const S* __restrict__ src, S* __restrict__ dst, TileGeo g, Coef<typename StorageTraits<S>::T> k,
        typename StorageTraits<S>::T* rec, int64_t rec_slot) {
   using T = typename StorageTraits<S>::T;
