@@ -427,7 +427,9 @@ hipError_t launch_step_w(const RunDesc& d, int phase, const void* src, void* dst
   S* o = static_cast<S*>(dst);
   T* r = static_cast<T*>(rec);
   const dim3 grid = step_grid(g), block{unsigned(threads)};
-  if (rec) {
+  if (d.walls) {
+    hipLaunchKernelGGL((k_step<S, MODEL, PH_AB, false, NPT, STREAM, true>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
+  } else if (rec) {
     if (phase == PH_AB) hipLaunchKernelGGL((k_step<S, MODEL, PH_AB, true, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
     else if (phase == PH_AA_EVEN) hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_EVEN, true, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
     else hipLaunchKernelGGL((k_step<S, MODEL, PH_AA_ODD, true, NPT, STREAM>), grid, block, 0, st, s, o, g, k, r, d.rs_rec);
@@ -465,15 +467,6 @@ hipError_t launch_step_m(const RunDesc& d, int phase, const void* src, void* dst
   return launch_step_n<S, MODEL, 1>(d, phase, src, dst, rec, st);
 }
 
-template <class S, int MODEL>
-hipError_t launch_step_walls(const RunDesc& d, const void* src, void* dst, hipStream_t st) {
-  using T = typename StorageTraits<S>::T;
-  const Geo g = make_geo(d, 1);
-  hipLaunchKernelGGL((k_step_walls<S, MODEL>), step_grid(g), dim3(kBlock), 0, st, static_cast<const S*>(src),
-                     static_cast<S*>(dst), g, make_coef<T>(d));
-  return hipGetLastError();
-}
-
 // f(std::integral_constant<int, MODEL>) for the run's model.
 template <class F>
 hipError_t with_model(int model, F&& f) {
@@ -490,7 +483,7 @@ hipError_t Engine<S>::step(const RunDesc& d, int phase, const void* src, void* d
   if (d.walls && (phase != PH_AB || rec)) return hipErrorInvalidValue;
   return with_model(d.model, [&](auto m) {
     constexpr int MODEL = decltype(m)::value;
-    return d.walls ? launch_step_walls<S, MODEL>(d, src, dst, st) : launch_step_m<S, MODEL>(d, phase, src, dst, rec, st);
+    return launch_step_m<S, MODEL>(d, phase, src, dst, rec, st);
   });
 }
 

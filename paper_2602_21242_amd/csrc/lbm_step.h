@@ -1,4 +1,4 @@
-// Single-step kernels: the fused stream + collide step, its variant with walls, and the adjoint
+// Single-step kernels: the fused stream + collide step (with or without walls) and the adjoint
 // step; the two-step adjoint kernel of the AA layout. Instantiated per storage type in
 // step_<type>.hip. The kernels that take several steps per launch are in lbm_march.h and
 // lbm_tile.h.
@@ -258,8 +258,11 @@ __device__ __forceinline__ int first_group(int& y, int& lane, bool xcd, int thre
 // loads of all of them before the first collision so that more memory traffic is in flight
 // per wavefront. src and dst alias in the AA phases. With REC the moments (rho, u_x, u_y,
 // N_xx, N_xy) of every node are written to rec, laid out like the populations with five
-// entries per lattice row (row stride rec_rs).
-template <class S, int MODEL, int PH, bool REC, int NPT, bool STREAM>
+// entries per lattice row (row stride rec_rs). With WALLS (A-B) the columns x = 0 and x = nx - 1 are
+// solid (fullway bounce-back, the isothermal shocktube of Sec. 5): a wall node pulls its populations
+// like any node and, instead of colliding, sends each back the way it came, g*_i = g_opp(i) (exact
+// in the shifted storage since w_i = w_opp(i)).
+template <class S, int MODEL, int PH, bool REC, int NPT, bool STREAM, bool WALLS = false>
 __global__ void __launch_bounds__((PH == PH_AB ? kStepBlock<S> : kBlock))
 k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
        typename StorageTraits<S>::T* rec, int64_t rec_rs) {
@@ -305,7 +308,12 @@ k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
     T g[Q], out[Q], rv[NREC];
 #pragma unroll
     for (int i = 0; i < Q; ++i) g[i] = Tr::load_raw(gs[n][i]);
-    collide<T, MODEL, ConserveMode<S>::value>(g, out, k, REC ? rv : nullptr);
+    collide<T, MODEL, ConserveMode<S, WALLS>::value>(g, out, k, REC ? rv : nullptr);
+    if constexpr (WALLS) {
+      const bool wall = rp[n].p0 == 0 || rp[n].p0 == geo.nx - 1;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) out[i] = wall ? g[opp(i)] : out[i];
+    }
     if constexpr (REC) {
       const RowRes rr = row_res(rec, size_t(rec_rs) * sizeof(T), y);
 #pragma unroll
@@ -472,42 +480,6 @@ k_adjoint_step2(const T* __restrict__ fbar_next, T* __restrict__ fbar, Geo geo, 
   __syncthreads();
   phase_b(y1 - 1);
   __syncthreads();
-}
-
-// One A-B time step with solid columns at x = 0 and x = nx - 1 (fullway bounce-back, the
-// isothermal shocktube of Sec. 5): a wall node pulls its populations like any node and,
-// instead of colliding, sends each back the way it came, g*_i = g_opp(i) (exact in the
-// shifted storage since w_i = w_opp(i)); fluid nodes collide as in k_step. One node per
-// thread, no padding access; used only for wall runs, which are small.
-template <class S, int MODEL>
-__global__ void __launch_bounds__(kBlock)
-k_step_walls(const S* __restrict__ src, S* __restrict__ dst, Geo geo, Coef<typename StorageTraits<S>::T> k) {
-  using T = typename StorageTraits<S>::T;
-  using Tr = StorageTraits<S>;
-  int y, lane;
-  const int s0 = first_group<1>(y, lane, true);
-  RowPos rp;
-  if (y >= geo.ny || !node_pos_contig(geo, s0, lane, rp)) return;
-  const int x = rp.p0;
-  const int ym = (y == 0) ? geo.ny - 1 : y - 1;
-  const int yp = (y == geo.ny - 1) ? 0 : y + 1;
-  const size_t rsb = size_t(geo.rs) * sizeof(S), psb = size_t(geo.ps) * sizeof(S);
-  const char* sr[3] = {reinterpret_cast<const char*>(src) + ym * rsb, reinterpret_cast<const char*>(src) + y * rsb,
-                       reinterpret_cast<const char*>(src) + yp * rsb};
-  T g[Q], out[Q];
-  static_for<0, Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    g[i] = Tr::load(ld1(at<S>(sr[-cy(i) + 1] + i * psb, rp.template of<-cx(i)>())));
-  });
-  if (x == 0 || x == geo.nx - 1) {
-#pragma unroll
-    for (int i = 0; i < Q; ++i) out[i] = g[opp(i)];
-  } else {
-    collide<T, MODEL, ConserveMode<S, true>::value>(g, out, k, nullptr);
-  }
-  char* orow = reinterpret_cast<char*>(dst) + y * rsb;
-#pragma unroll
-  for (int i = 0; i < Q; ++i) st1(at<S>(orow + i * psb, rp.p0), Tr::store(out[i]));
 }
 
 // One reverse step of the discrete adjoint: fbar^n(x) = J(m^n(x))^T fbar*(x) with the

@@ -51,7 +51,7 @@ struct TileCells {
 template <class S, int M, int KIND>
 constexpr int kTileWaves = KIND == TILE_ADJOINT && sizeof(S) == 4 && M == 1 ? 8 : 1;
 
-// KIND TILE_STEP / TILE_WALLS: ns forward steps (with the bounce-back columns of k_step_walls);
+// KIND TILE_STEP / TILE_WALLS: ns forward steps (with the bounce-back columns of k_step);
 // TILE_REC: step s also writes its moments to rec + s rec_slot; TILE_ADJOINT: ns reverse steps
 // on fbar (S is the compute type), reverse step s with the moments at rec - s rec_slot.
 template <class S, int MODEL, int NT, int M, int KIND>
