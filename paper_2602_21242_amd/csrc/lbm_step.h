@@ -150,6 +150,14 @@ constexpr int kAuxNT = 2;                // cache-policy operand of a nontempora
 constexpr int kAuxStoreWT = kAuxNT | 16;
 template <bool STREAM> constexpr int kAuxStore = STREAM ? kAuxStoreWT : 0;
 
+// Which loads of a streaming step are nontemporal. A-B: those of the populations that do not move
+// along x. The others straddle a line that the next wavefront or block also reads, and a
+// nontemporal line is gone by then (us per step, all nontemporal / those / none: FP32 4096^2 186.0
+// / 183.4 / 192.4, 8192^2 740 / 730 / 763, FP64 8192 x 4096 793 / 783 / 808, BF16 8192^2 417 / 387
+// / 391). AA: all in FP32 and FP64, none of 16-bit storage.
+template <class S, int PH, bool STREAM, int DX>
+constexpr bool kLoadNT = STREAM && (PH == PH_AB ? DX == 0 : sizeof(S) != 2);
+
 struct RowRes {
   __amdgpu_buffer_rsrc_t r;
 };
@@ -299,7 +307,7 @@ k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
       constexpr int slot = (PH == PH_AA_ODD) ? opp(i) : i;
       constexpr int dx = shift ? -cx(i) : 0;
       constexpr int dy = shift ? -cy(i) : 0;
-      gs[n][i] = ld_raw<S, STREAM && sizeof(S) != 2>(at<S>(sr[dy + 1] + slot * psb, rp[n].template of<dx>()));
+      gs[n][i] = ld_raw<S, kLoadNT<S, PH, STREAM, dx>>(at<S>(sr[dy + 1] + slot * psb, rp[n].template of<dx>()));
     });
   }
 
