@@ -456,7 +456,8 @@ lbm_status lbm_init(const lbm_params* p, void* d_workspace, size_t workspace_byt
     d.contig = p->pattern == LBM_AB;
     const int64_t population_bytes =
         int64_t(lbm::Q) * d.pitch * d.ny * int64_t(storage_size(p->storage)) * (d.contig ? 2 : 1);
-    d.stream = population_bytes >= (d.contig ? lbm::kStreamBytesAB : lbm::kStreamBytesAA);
+    const bool padded = !d.contig && d.pitch != d.nx;
+    d.stream = population_bytes < (padded ? lbm::kStreamBytesPadded : lbm::kStreamBytes) ? 0 : padded ? 1 : 2;
     d.xcd = population_bytes <= (storage_size(p->storage) == 2 ? lbm::kXcdBytes16 : lbm::kXcdBytes);
     dispatch_int(p->storage, [&](auto eng) {
       decltype(eng)::plan(d, p->two_step, plan.stride, false);

@@ -26,7 +26,7 @@ struct RunDesc {
   int adj_rb;        // AA: row blocks of the two-step adjoint kernel; 0: one reverse step per launch
   int walls;         // 1: solid bounce-back columns at x = 0 and x = nx - 1 (A-B only)
   int xcd;           // 1: the single-step kernel's blocks run in XCD order (see kXcdBytes)
-  int stream;        // 1: the single-step kernel's accesses bypass the caches (see kAuxStoreWT)
+  int stream;        // the single-step kernel's cache policy (STREAM_OFF, _ON, _ALL)
   // A-B: how several forward (march, tile) and reverse (adj_*) steps are launched; steps = 0
   // where a kernel does not apply or is not the fastest.
   MarchPlan march, adj_march;
@@ -34,11 +34,13 @@ struct RunDesc {
 };
 
 // Where a run's population buffers (both of A-B, the one of AA) stop fitting the 256 MB last-level
-// cache well enough for plain accesses to win, us per step plain/streaming on uniform fields: A-B
-// FP32 302 MB 40/48, 319 MB 48/53, 355 MB 61/58, FP16 325 MB 61/58, FP64 332 MB 56/54; AA FP32
-// 350 MB 120/146, BF16 302 MB 87/98, FP64 295 MB 87/105, 382 MB 131/123. A-B's write-once streams
-// evict each other earlier than AA's reads and writes of the same lines.
-constexpr int64_t kStreamBytesAB = int64_t(304) << 20, kStreamBytesAA = int64_t(352) << 20;
+// cache well enough for plain accesses to win, us per step plain/streaming: A-B FP32 302 MB 46/48,
+// 381 MB 67/62, FP64 324 MB 57/54; AA on rows without padding FP32 326 MB 105/104, 340 MB 111/104,
+// FP64 302 MB 92/93, 321 MB 103/102, FP16 302 MB 96/98, 321 MB 118/117. AA's padding lanes keep
+// to their own slots while the rest of the group shifts, so padded rows write parts of lines, which
+// the caches put together: FP32 358 MB 127/163, 392 MB 140/154, FP64 381 MB 131/122, FP16 348 MB
+// 133/133.
+constexpr int64_t kStreamBytes = int64_t(304) << 20, kStreamBytesPadded = int64_t(352) << 20;
 // Up to here the step's blocks run in XCD order, which keeps a row's neighbours of the previous
 // step in the same L2: AA FP32 1000^2 11.7 -> 10.4 us, 2700^2 (267 MB) 68 -> 61, A-B FP32 1700^2
 // (212 MB) 27.1 -> 25.2, 2048^2 (302 MB) 40 -> 44. 16-bit storage, whose steps are bound by their

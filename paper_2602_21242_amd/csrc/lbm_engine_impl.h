@@ -417,7 +417,7 @@ int step_threads(const RunDesc& d, int phase, int npt) {
   return best;
 }
 
-template <class S, int MODEL, int NPT, bool STREAM>
+template <class S, int MODEL, int NPT, int STREAM>
 hipError_t launch_step_w(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st) {
   using T = typename StorageTraits<S>::T;
   const int threads = step_threads<S>(d, phase, NPT);
@@ -443,8 +443,11 @@ hipError_t launch_step_w(const RunDesc& d, int phase, const void* src, void* dst
 
 template <class S, int MODEL, int NPT>
 hipError_t launch_step_n(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st) {
-  return d.stream ? launch_step_w<S, MODEL, NPT, true>(d, phase, src, dst, rec, st)
-                  : launch_step_w<S, MODEL, NPT, false>(d, phase, src, dst, rec, st);
+  // STREAM_ALL differs for AA's 16-bit loads alone.
+  if constexpr (sizeof(S) == 2)
+    if (d.stream == STREAM_ALL && phase != PH_AB) return launch_step_w<S, MODEL, NPT, STREAM_ALL>(d, phase, src, dst, rec, st);
+  return d.stream ? launch_step_w<S, MODEL, NPT, STREAM_ON>(d, phase, src, dst, rec, st)
+                  : launch_step_w<S, MODEL, NPT, STREAM_OFF>(d, phase, src, dst, rec, st);
 }
 
 // Nodes per thread of the step kernel. Two or four nodes per thread put more loads in flight

@@ -148,15 +148,17 @@ constexpr int kAuxNT = 2;                // cache-policy operand of a nontempora
 // us, 1000^2 15.3 -> 10.5 us (uniform fields; 84 -> 62 us in a Taylor-Green run, XCD order
 // included).
 constexpr int kAuxStoreWT = kAuxNT | 16;
-template <bool STREAM> constexpr int kAuxStore = STREAM ? kAuxStoreWT : 0;
-
+template <int STREAM> constexpr int kAuxStore = STREAM ? kAuxStoreWT : 0;
 // Which loads of a streaming step are nontemporal. A-B: those of the populations that do not move
 // along x. The others straddle a line that the next wavefront or block also reads, and a
 // nontemporal line is gone by then (us per step, all nontemporal / those / none: FP32 4096^2 186.0
 // / 183.4 / 192.4, 8192^2 740 / 730 / 763, FP64 8192 x 4096 793 / 783 / 808, BF16 8192^2 417 / 387
-// / 391). AA: all in FP32 and FP64, none of 16-bit storage.
-template <class S, int PH, bool STREAM, int DX>
-constexpr bool kLoadNT = STREAM && (PH == PH_AB ? DX == 0 : sizeof(S) != 2);
+// / 391). AA: all in FP32 and FP64; of 16-bit storage on rows without padding (STREAM_ALL: FP16
+// 8192^2 384, plain 410), not on padded ones, whose padding lanes load parts of lines (5200^2 215,
+// 190).
+enum { STREAM_OFF = 0, STREAM_ON = 1, STREAM_ALL = 2 };
+template <class S, int PH, int STREAM, int DX>
+constexpr bool kLoadNT = STREAM != STREAM_OFF && (PH == PH_AB ? DX == 0 : sizeof(S) != 2 || STREAM == STREAM_ALL);
 
 struct RowRes {
   __amdgpu_buffer_rsrc_t r;
@@ -270,7 +272,7 @@ __device__ __forceinline__ int first_group(int& y, int& lane, bool xcd, int thre
 // solid (fullway bounce-back, the isothermal shocktube of Sec. 5): a wall node pulls its populations
 // like any node and, instead of colliding, sends each back the way it came, g*_i = g_opp(i) (exact
 // in the shifted storage since w_i = w_opp(i)).
-template <class S, int MODEL, int PH, bool REC, int NPT, bool STREAM, bool WALLS = false>
+template <class S, int MODEL, int PH, bool REC, int NPT, int STREAM, bool WALLS = false>
 __global__ void __launch_bounds__((PH == PH_AB ? kStepBlock<S> : kBlock))
 k_step(const S* src, S* dst, Geo geo, Coef<typename StorageTraits<S>::T> k,
        typename StorageTraits<S>::T* rec, int64_t rec_rs) {

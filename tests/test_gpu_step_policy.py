@@ -50,3 +50,14 @@ def test_walls_on_boxes_beyond_the_cache(storage, nx, ny):
     assert torch.equal(a, b.populations())
     free = _run(nx, ny, "partial", storage, "ab", 3, f0)
     assert torch.equal(a[:, :, 4:-4], free[:, :, 4:-4])
+
+
+@pytest.mark.parametrize("storage,nx,ny", [("f32", 3072, 3000), ("f32", 3100, 3300), ("f64", 2112, 2200),
+                                           ("f16", 4224, 4224), ("f16", 4500, 4520), ("bf16", 4224, 4224),
+                                           ("bf16", 4700, 4400)])
+def test_aa_beyond_the_cache_matches_ab(storage, nx, ny):
+    """AA in place, on rows with and without padding whose buffer bypasses the caches, against A-B:
+    both phases and the step after them."""
+    import torch
+    f0 = _state(nx, ny)
+    assert torch.equal(_run(nx, ny, "complete", storage, "aa", 3, f0), _run(nx, ny, "complete", storage, "ab", 3, f0))
