@@ -240,8 +240,7 @@ lbm_status launch_steps(lbm_ctx* c, int64_t ns, int64_t t, const void* src, void
       e = E::step(c->d, ph, src, dst, rec, c->stream);
     } else {
       const int64_t slot = int64_t(c->plan.rec_slot_bytes / sizeof(T));
-      e = c->d.tile.steps > 0 ? E::tile(c->d, int(ns), src, dst, static_cast<T*>(rec), slot, c->stream)
-                              : E::march(c->d, int(ns), src, dst, static_cast<T*>(rec), slot, c->stream);
+      e = E::steps(c->d, int(ns), src, dst, static_cast<T*>(rec), slot, c->stream);
     }
     if (e != hipSuccess) return fail(LBM_ERR_HIP, std::string("step kernel launch: ") + hipGetErrorString(e));
     return LBM_OK;
@@ -284,6 +283,14 @@ void note_capture(lbm_ctx* c) {
     decltype(eng)::plan(c->d, c->p.two_step, c->plan.stride, true);
     return 0;
   });
+}
+
+bool shares_evenly(const lbm_ctx* c) { return int64_t(c->d.nx) * c->d.ny < lbm::kEvenNodes; }
+
+// Steps of the next forward launch when m lie ahead.
+int64_t forward_steps(const lbm_ctx* c, int64_t m) {
+  const int64_t ns = lbm::steps_ahead(m, c->d.march.steps, c->d.tile.steps, shares_evenly(c));
+  return ns == 2 && c->d.two.single ? 1 : ns;
 }
 
 bool is_small(const lbm_ctx* c) { return int64_t(c->d.pitch) * c->d.ny <= kGraphMaxPositions; }
@@ -347,7 +354,7 @@ lbm_status sweep(lbm_ctx* c, int* out_b) {
       void* const other = c->p.pattern == LBM_AB ? c->ws + c->plan.pop_off[1 - c->cur] : slot;
       const void* src = c->ckpt(k);
       for (int64_t t = t0; t < t1;) {
-        const int64_t ns = lbm::steps_ahead(t1 - t, d.march.steps, d.tile.steps);
+        const int64_t ns = forward_steps(c, t1 - t);
         void* const dst = src == slot ? other : slot;
         st = launch_steps(c, ns, t, src, dst, c->rec_slot(t - t0));
         if (st != LBM_OK) return st;
@@ -508,10 +515,10 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
         int64_t ns;
         if (c->captured) {
           if (odd < 0) odd = int((lbm_steps_per_launch(c) == 2 ? (n - k + 1) / 2 : n - k) & 1);
-          ns = lbm::steps_ahead_parity(n - k, c->d.march.steps, c->d.tile.steps, odd);
+          ns = lbm::steps_ahead_parity(n - k, c->d.march.steps, c->d.tile.steps, odd, shares_evenly(c));
           odd ^= 1;
         } else {
-          ns = lbm::steps_ahead(n - k, c->d.march.steps, c->d.tile.steps);
+          ns = forward_steps(c, n - k);
         }
         s = do_steps(c, ns, nullptr);
         if (s != LBM_OK) return s;
@@ -528,7 +535,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
       // the state into the next checkpoint's slot (at t = N there is none).
       const int64_t seg_end = std::min((seg + 1) * c->plan.stride, N);
       const bool keep = c->time >= t_last;
-      const int64_t ns = lbm::steps_ahead(std::min(n - k, seg_end - c->time), c->d.march.steps, c->d.tile.steps);
+      const int64_t ns = forward_steps(c, std::min(n - k, seg_end - c->time));
       void* rec = keep ? c->rec_slot(c->time - t_last) : nullptr;
       s = c->time + ns == seg_end && seg_end < N ? steps_into_ckpt(c, ns, seg + 1, rec) : do_steps(c, ns, rec);
       if (s != LBM_OK) return s;

@@ -31,6 +31,8 @@ struct RunDesc {
   // where a kernel does not apply or is not the fastest.
   MarchPlan march, adj_march;
   TilePlan tile, adj_tile;
+  TwoPlan two;  // forward launches of two steps
+  int two_rb;   // not 0: the pair kernel takes them (unless recording), over that many row blocks
 };
 
 // Where a run's population buffers (both of A-B, the one of AA) stop fitting the 256 MB last-level
@@ -59,12 +61,10 @@ template <class S>
 struct Engine {
   using T = typename StorageTraits<S>::T;
   static hipError_t step(const RunDesc& d, int phase, const void* src, void* dst, void* rec, hipStream_t st);
-  // ns A-B steps in one launch, out of place, by the marching or the tile kernel of the run's
+  // ns >= 2 A-B steps in one launch, out of place, by the marching or the tile kernel of the run's
   // plan; rec, when not null, receives the moments of step s at rec + s * rec_slot.
-  static hipError_t march(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
+  static hipError_t steps(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
                           hipStream_t st);
-  static hipError_t tile(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
-                         hipStream_t st);
   // Fills the run's plans for the current device (mode: lbm_params.two_step; segment: steps of a
   // recorded run's checkpoint segments, 0: no recording). captured: no plan of single steps alone
   // where lbm_steps_per_launch reports 2 (see lbm_ctx::captured).

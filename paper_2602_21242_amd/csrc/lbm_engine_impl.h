@@ -5,6 +5,7 @@
 
 #include "lbm_engine.h"
 #include "lbm_march.h"
+#include "lbm_pair.h"
 #include "lbm_step.h"
 #include "lbm_tile.h"
 
@@ -502,18 +503,19 @@ inline MarchGeo march_geo(const RunDesc& d, const MarchPlan& p) {
   g.ncol = p.ncol;
   g.w = p.w;
   g.xlast = p.xlast;
+  g.halo = p.halo;
   g.nrb = p.nrb;
   return g;
 }
 inline dim3 march_grid(const MarchPlan& p) { return dim3(unsigned((p.ncol + p.waves - 1) / p.waves) * unsigned(p.nrb)); }
 
 template <class S, int MODEL, bool REC>
-hipError_t launch_march(const RunDesc& d, int ns, const S* src, S* dst,
+hipError_t launch_march(const RunDesc& d, const MarchPlan& p, int ns, const S* src, S* dst,
                         const MarchRec<typename StorageTraits<S>::T>& rec, hipStream_t st) {
   using T = typename StorageTraits<S>::T;
-  const MarchGeo g = march_geo(d, d.march);
+  const MarchGeo g = march_geo(d, p);
   const Coef<T> k = make_coef<T>(d);
-  const dim3 grid = march_grid(d.march), block(unsigned(d.march.waves * kLanes));
+  const dim3 grid = march_grid(p), block(unsigned(p.waves * kLanes));
   switch (ns) {
     case 2: hipLaunchKernelGGL((k_march<S, MODEL, 2, REC>), grid, block, 0, st, src, dst, g, k, rec); break;
     case 3: hipLaunchKernelGGL((k_march<S, MODEL, 3, REC>), grid, block, 0, st, src, dst, g, k, rec); break;
@@ -521,19 +523,6 @@ hipError_t launch_march(const RunDesc& d, int ns, const S* src, S* dst,
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-template <class S>
-hipError_t Engine<S>::march(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
-                            hipStream_t st) {
-  if (!d.contig || d.walls || ns > d.march.steps) return hipErrorInvalidValue;
-  MarchRec<T> r{};
-  for (int s = 0; rec && s < ns; ++s) r.p[s] = rec + s * rec_slot;
-  return with_model(d.model, [&](auto m) {
-    constexpr int MODEL = decltype(m)::value;
-    return rec ? launch_march<S, MODEL, true>(d, ns, static_cast<const S*>(src), static_cast<S*>(dst), r, st)
-               : launch_march<S, MODEL, false>(d, ns, static_cast<const S*>(src), static_cast<S*>(dst), r, st);
-  });
 }
 
 template <class S>
@@ -600,16 +589,37 @@ hipError_t launch_tile(const RunDesc& d, const TilePlan& p, int ns, hipStream_t 
 }
 
 template <class S>
-hipError_t Engine<S>::tile(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
-                           hipStream_t st) {
-  if (!d.contig || ns > d.tile.steps || (d.walls && rec)) return hipErrorInvalidValue;
+hipError_t Engine<S>::steps(const RunDesc& d, int ns, const void* src, void* dst, T* rec, int64_t rec_slot,
+                            hipStream_t st) {
+  const bool two = ns == 2 && (d.two.march.steps || d.two.tile.steps);
+  const MarchPlan& mp = two ? d.two.march : d.march;
+  const TilePlan& tp = two ? d.two.tile : d.tile;
+  if (!d.contig || (d.walls && rec) || ns > std::max(mp.steps, tp.steps)) return hipErrorInvalidValue;
   const S* s = static_cast<const S*>(src);
   S* o = static_cast<S*>(dst);
+  if constexpr (sizeof(S) >= 4) {
+    if (ns == 2 && d.two_rb && !rec) {
+      const Geo g = make_geo(d, 1);
+      const dim3 grid(unsigned(d.nx / kPairNodes), unsigned(d.two_rb)), block(kPairNodes + kLanes);
+      return with_model(d.model, [&](auto m) {
+        constexpr int MODEL = decltype(m)::value;
+        if (d.stream) hipLaunchKernelGGL((k_pair<S, MODEL, STREAM_ON>), grid, block, 0, st, s, o, g, make_coef<T>(d));
+        else hipLaunchKernelGGL((k_pair<S, MODEL, STREAM_OFF>), grid, block, 0, st, s, o, g, make_coef<T>(d));
+        return hipGetLastError();
+      });
+    }
+  }
   return with_model(d.model, [&](auto m) {
     constexpr int MODEL = decltype(m)::value;
-    if (d.walls) return launch_tile<S, MODEL, TILE_WALLS>(d, d.tile, ns, st, s, o, rec, rec_slot);
-    if (rec) return launch_tile<S, MODEL, TILE_REC>(d, d.tile, ns, st, s, o, rec, rec_slot);
-    return launch_tile<S, MODEL, TILE_STEP>(d, d.tile, ns, st, s, o, rec, rec_slot);
+    if (tp.steps) {
+      if (d.walls) return launch_tile<S, MODEL, TILE_WALLS>(d, tp, ns, st, s, o, rec, rec_slot);
+      if (rec) return launch_tile<S, MODEL, TILE_REC>(d, tp, ns, st, s, o, rec, rec_slot);
+      return launch_tile<S, MODEL, TILE_STEP>(d, tp, ns, st, s, o, rec, rec_slot);
+    }
+    if (d.walls) return hipErrorInvalidValue;
+    MarchRec<T> r{};
+    for (int k = 0; rec && k < ns; ++k) r.p[k] = rec + k * rec_slot;
+    return rec ? launch_march<S, MODEL, true>(d, mp, ns, s, o, r, st) : launch_march<S, MODEL, false>(d, mp, ns, s, o, r, st);
   });
 }
 
@@ -661,7 +671,7 @@ inline int plan_row_blocks(const RunDesc& d, int mode, bool tall, int cus) {
 }
 
 template <class S>
-void plan_steps(RunDesc& d, int cus, bool force_march, bool no_single, int64_t horizon) {
+void plan_steps(RunDesc& d, int cus, bool force_march, bool no_single, int row_blocks, int64_t horizon) {
   using T = typename StorageTraits<S>::T;
   // The tile kernel addresses a whole buffer with 32-bit byte offsets.
   const bool tiles = d.rs * d.ny * int64_t(sizeof(T)) < (int64_t(1) << 31);
@@ -676,6 +686,12 @@ void plan_steps(RunDesc& d, int cus, bool force_march, bool no_single, int64_t h
   if (!d.walls) d.march = plan_march(d.nx, d.ny, MarchNodes<S>::value, kMarchHalo, kMarchMax, kMarchWaves, cus, horizon, cm);
   if (tiles) d.tile = plan_tile(d.nx, d.ny, cus, horizon, cm);
   choose(d.march, d.tile, single_step_us(d.nx, d.ny, cus, cm));
+  // Launches of two steps: the pair kernel (see lbm_pair.h) or a plan of their own.
+  const bool pair = row_blocks > 0 && d.nx % kPairNodes == 0 && (sizeof(S) == 4 || (sizeof(S) == 8 && (d.stream || d.tile.steps)));
+  d.two_rb = pair ? row_blocks : 0;
+  d.two = {};
+  if ((d.march.steps || d.tile.steps) && !(d.tile.wrapx && d.tile.wrapy) && !force_march && !d.two_rb)
+    d.two = plan_two(d.nx, d.ny, MarchNodes<S>::value, kMarchWaves, cus, !d.walls, d.tile, cm);
   if (horizon > 0) {
     const CostModel ca = cost_model(int(sizeof(T)), d.model == M_BGK, true);
     d.adj_march = plan_march(d.nx, d.ny, kMarchAdjointNodes, kMarchHalo, kMarchMax, kMarchWaves, cus, horizon, ca);
@@ -690,7 +706,8 @@ void Engine<S>::plan(RunDesc& d, int mode, int64_t segment, bool captured) {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     return;
-  const bool pair = mode >= 0 && !d.walls && plan_row_blocks(d, mode, FuseTall<S>::value, cus) > 0;
+  const int row_blocks = mode >= 0 && !d.walls ? plan_row_blocks(d, mode, FuseTall<S>::value, cus) : 0;
+  const bool pair = row_blocks > 0;
   d.pair = d.contig && pair;
   if (mode < 0) return;
   if (!d.contig) {
@@ -700,7 +717,7 @@ void Engine<S>::plan(RunDesc& d, int mode, int64_t segment, bool captured) {
   // mode 1 takes the marching kernel on every grid of whole pairs (the documented rule), mode 0
   // whatever the cost model finds fastest.
   const bool force = mode == 1 && d.nx % kLanes == 0 && (d.pitch / kLanes) % kFuseGroups == 0;
-  plan_steps<S>(d, cus, force, captured && pair, segment);
+  plan_steps<S>(d, cus, force, captured && pair, row_blocks, segment);
 }
 
 // f(std::bool_constant<contiguous rows>).

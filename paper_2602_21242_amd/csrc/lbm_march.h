@@ -14,7 +14,7 @@
 // steps.
 //
 // The strip's edge nodes lose their neighbours, one column per side and step, so a wavefront
-// stores the 64 NPL - 2 kMarchHalo nodes in its middle, and a row block recomputes NS - 1 rows
+// stores the 64 NPL - 2 halo nodes in its middle (halo: kMarchHalo, two for launches of two steps), and a row block recomputes NS - 1 rows
 // of step 1 on either side. Measured on MI355X (complete model, us per launch of 4 steps, us per
 // launch of 2 steps of the LDS-staged pair kernel this replaces): FP32 4096^2 300 / 205, 8192^2
 // 1102 / 830; FP64 4096^2 531 / 418. The FP32 kernel issues a vector instruction in nearly every
@@ -30,7 +30,7 @@
 namespace lbm {
 
 constexpr int kMarchMax = 4;    // steps per launch
-constexpr int kMarchHalo = 4;   // nodes at either edge of a strip that are not stored
+constexpr int kMarchHalo = 4;   // nodes at either edge of a strip that are not stored (two steps: 2)
 constexpr int kMarchWaves = 4;  // strips per block on grids that fill the chip
 static_assert(kMarchHalo >= kMarchMax, "a step invalidates one column per side");
 
@@ -46,7 +46,7 @@ constexpr int kMarchAdjointNodes = 1;
 struct MarchGeo {
   int nx, ny, ps;
   int64_t rs, rec_rs;
-  int ncol, w, xlast, nrb;
+  int ncol, w, xlast, halo, nrb;
 };
 
 template <class T>
@@ -157,7 +157,7 @@ __device__ __forceinline__ Strip strip_of(const MarchGeo& g, int& xw) {
   s.active = col < g.ncol;
   s.lane = int(threadIdx.x % kLanes);
   const int x0 = col == g.ncol - 1 ? g.xlast : col * g.w;
-  s.x = x0 - kMarchHalo + NPL * s.lane;
+  s.x = x0 - g.halo + NPL * s.lane;
   xw = s.x % g.nx;
   if (xw < 0) xw += g.nx;
   s.store = s.x >= x0 && s.x < x0 + g.w && s.x < g.nx;

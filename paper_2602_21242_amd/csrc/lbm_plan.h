@@ -13,7 +13,7 @@ namespace lbm {
 
 struct MarchPlan {
   int steps = 0;  // per launch; 0: the kernel does not apply
-  int ncol = 0, w = 0, xlast = 0, nrb = 0, waves = 0;
+  int ncol = 0, w = 0, xlast = 0, halo = 0, nrb = 0, waves = 0;
   double us_per_step = 1e30;
 };
 
@@ -50,9 +50,12 @@ struct CostModel {
   double march_memory = 0;          // bytes per us, the halos of the reverse march included
   double single_launch = 0;         // single step: dispatch, first loads, last stores
   double single_issue = 0;          // and the share of a SIMD's cycles it issues in
+  double tile_line = 0;             // bytes that a tile's row reads or writes besides its own
+  bool tile_uneven = false;         // launches too short for uneven shares of blocks to even out
   int regs[kTileConfigCount] = {};  // vector registers of the tile kernel's instances
   int max_cells = 0;                // largest instance that does not spill
 };
+constexpr int64_t kEvenNodes = int64_t(1) << 16;  // tiles share steps evenly below
 constexpr double kTileLaunch = 4.2;
 constexpr double kTileStep = 0.11;     // a step's barrier and LDS latency
 constexpr double kTileRound = 0.8;     // a further round of blocks on the same compute unit
@@ -90,6 +93,7 @@ inline CostModel cost_model(int bytes, bool bgk, bool adjoint, bool bf16 = false
 // Strips of w stored nodes out of `span` (see MarchGeo). False where no strip width works.
 inline bool march_strips(int nx, int span, int halo, bool pairs, MarchPlan& p) {
   const int most = span - 2 * halo;
+  p.halo = halo;
   if (!pairs || nx % 2 == 0) {
     p.w = most;
     p.ncol = (nx + most - 1) / most;
@@ -111,9 +115,13 @@ inline bool march_strips(int nx, int span, int halo, bool pairs, MarchPlan& p) {
 }
 
 // Steps of the next launch when m steps lie ahead. Tiles share them evenly among the launches
-// they need; the marching kernel takes as many as it can without leaving a single one.
-inline int64_t steps_ahead(int64_t m, int march, int tile) {
+// they need, except that on grids too large for the launches to count (even = false) a single step
+// left over is a launch of its own: a plan's region for five steps computes as much for three
+// (1024^2 FP32, 6 steps as 3 + 3 61 us, as 5 + 1 53). The marching kernel takes as many as it can
+// without leaving a single one.
+inline int64_t steps_ahead(int64_t m, int march, int tile, bool even = true) {
   if (tile > 0) {
+    if (!even && m > tile && m % tile == 1) return tile;
     const int64_t launches = (m + tile - 1) / tile;
     return (m + launches - 1) / launches;
   }
@@ -124,8 +132,8 @@ inline int64_t steps_ahead(int64_t m, int march, int tile) {
 // The same where the launches that are left have to be odd or even in number: the call then ends
 // in the buffer it started from, or in the other one, whatever the plan. march or tile >= 2; one
 // step cannot take an even number of launches.
-inline int64_t steps_ahead_parity(int64_t m, int march, int tile, bool odd) {
-  const int64_t ns = steps_ahead(m, march, tile);
+inline int64_t steps_ahead_parity(int64_t m, int march, int tile, bool odd, bool even = true) {
+  const int64_t ns = steps_ahead(m, march, tile, even);
   return ns > 1 && m - ns == int64_t(odd) ? ns - 1 : ns;
 }
 
@@ -137,8 +145,10 @@ inline int64_t steps_ahead_parity(int64_t m, int march, int tile, bool odd) {
 // 284; FP64 2024^2 40.3 with one wavefront, 38.5 with two; FP32 2048^2 24.4 with three steps, 22.8
 // with four; FP32 LBGK 4096^2, bound by memory, 63.6 with one wavefront per SIMD, 72.3 with three.
 // horizon: steps come in runs of that many (0: many).
+// gain: fewer, longer row blocks and fuller blocks unless others take less than that share of the
+// time.
 inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, int max_waves, int cus, int64_t horizon,
-                            const CostModel& cm) {
+                            const CostModel& cm, double gain = 0.99) {
   MarchPlan best;
   MarchPlan p;
   if (!march_strips(nx, 64 * npl, halo, npl == 2, p)) return best;
@@ -172,8 +182,7 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
           for (int64_t m = horizon; m > 0; m -= steps_ahead(m, steps, 0)) us += launch(steps_ahead(m, steps, 0));
           us /= double(horizon);
         }
-        // Fewer, longer row blocks unless more of them gain a hundredth.
-        if (us < best.us_per_step * 0.99) {
+        if (us < best.us_per_step * gain) {
           best = p;
           best.steps = steps;
           best.nrb = int(nrb);
@@ -186,11 +195,31 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
   return best;
 }
 
+// Time of a launch of ns steps on tiles of tw x th nodes by instance c.
+inline double tile_launch_us(int nx, int ny, int cus, int c, int tw, int th, int wx, int wy, int ns, double memory,
+                             const CostModel& cm) {
+  const int cells = kTileConfigs[c].threads * kTileConfigs[c].nodes, h = ns - 1;
+  const double rw = tw + (wx ? 0 : 2 * h), rh = th + (wy ? 0 : 2 * h);
+  // Wavefronts of the block (the region shrinks by a row on both sides per step), blocks per
+  // compute unit, and how many of them it holds at once.
+  const double wv = std::ceil(rw * (wy ? rh : rh - h) / 64.0);
+  const double share = double((nx + tw - 1) / tw) * ((ny + th - 1) / th) / cus, blocks = std::ceil(share);
+  const int by_regs = 512 / cm.regs[c] * 4 * 64 / kTileConfigs[c].threads;
+  const int fit = std::max(1, std::min(int(160 * 1024 / (cm.bytes / 2 * (cells + 2))), by_regs));
+  const double rounds = std::ceil(blocks / fit);
+  const double per = std::max(std::ceil(wv / 4), wv / 4 * (blocks > 2 && !cm.tile_uneven ? share : blocks));
+  const double wait = blocks <= 1 ? kTileAlone : fit == 1 ? kTileSerial : 1.0;
+  const double region = rw * rh / (double(tw) * th);
+  const double line = cm.tile_line / (cm.bytes / 18.0);  // in nodes
+  const double mem = double(nx) * ny *
+                     (cm.bytes / 2 * (1 + line / tw + region * (1 + line / rw)) + ns * cm.rec_bytes * region) / memory;
+  return kTileLaunch + mem + (rounds - 1) * kTileRound + ns * (kTileStep * rounds + cm.tile_wave * per * wait);
+}
+
 // Tile shape, instance and steps per launch of least time per step.
 inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostModel& cm) {
   TilePlan best;
   const int steps_try[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 16, 24, 32, 48, 64};
-  const double lds_per_cell = cm.bytes / 2;
   // Records of a segment that do not stay in the last-level cache come from memory, and the
   // marching kernel reads fewer of them twice (gradients, tiles -> march: FP32 1536^2 50 steps 3819
   // -> 3514 us, 1024^2 500 steps 18.2 -> 17.1 ms; in the cache, 1024^2 100 steps: 3440 against
@@ -240,19 +269,7 @@ inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostMo
         th = (ny + nty - 1) / nty;
         const double rw = tw + (wx ? 0 : 2 * h), rh = th + (wy ? 0 : 2 * h);
         if (rw * rh > cells) continue;
-        // Wavefronts of the block (the region shrinks by a row on both sides per step), blocks per
-        // compute unit, and how many of them it holds at once.
-        const double wv = std::ceil(rw * (wy ? rh : rh - h) / 64.0);
-        const double share = double(ntx) * nty / cus, blocks = std::ceil(share);
-        const int by_regs = 512 / cm.regs[c] * 4 * 64 / kTileConfigs[c].threads;
-        const int fit = std::max(1, std::min(int(160 * 1024 / (lds_per_cell * (cells + 2))), by_regs));
-        const double rounds = std::ceil(blocks / fit);
-        const double per = std::max(std::ceil(wv / 4), wv / 4 * (blocks > 2 ? share : blocks));
-        const double wait = blocks <= 1 ? kTileAlone : fit == 1 ? kTileSerial : 1.0;
-        const double region = rw * rh / (double(tw) * th);
-        const double mem = double(nx) * ny * (cm.bytes / 2 * (1 + region) + ns * cm.rec_bytes * region) / memory;
-        const double us = (kTileLaunch + mem + (rounds - 1) * kTileRound +
-                           ns * (kTileStep * rounds + cm.tile_wave * per * wait)) * double(launches) / double(m);
+        const double us = tile_launch_us(nx, ny, cus, c, tw, th, wx, wy, ns, memory, cm) * double(launches) / double(m);
         if (us < best.us_per_step * 0.999) {
           best.steps = ns;
           best.cfg = c;
@@ -268,6 +285,44 @@ inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostMo
   // One block that holds the whole box needs no surroundings: any number of steps.
   if (best.wrapx && best.wrapy) best.steps = kTileWholeSteps;
   return best;
+}
+
+// Launches of exactly two steps (calls of two, and what longer ones leave over) where the pair
+// kernel does not take them: the plan of many steps has tiles for deeper surroundings, and marches
+// of 16-bit storage lose two columns per side instead of four. steps = 0 in both and not single: the
+// plan of many steps serves as well (to 7 %, which is what the estimates are good for). us per call
+// of two by the plan of many steps / by this: FP32 700^2 14.2 / 11.7, 1000^2 24.8 / 17.4; FP16 512^2
+// 9.6 / 8.4, 1024^2 21.1 / 18.3, 2048^2 55.6 / 51.8; BF16 768^2 14.9 / 12.7, 2048^2 44.7 / 40.5.
+struct TwoPlan {
+  MarchPlan march;
+  TilePlan tile;
+  bool single = false;  // two launches of one step are faster
+};
+inline double single_step_us(int nx, int ny, int cus, const CostModel& cm);
+inline TwoPlan plan_two(int nx, int ny, int npl, int max_waves, int cus, bool march, const TilePlan& many, const CostModel& cost) {
+  TwoPlan p;
+  const bool half = cost.bytes < 72.0;
+  if (!many.steps && !half) return p;
+  CostModel cm = cost;
+  cm.tile_line = 64.0;
+  cm.tile_uneven = true;
+  // Fitted to calls of two steps from 128^2 to 1448^2.
+  const double scale = double(nx) * ny * cm.bytes < 0.8 * kCacheBytes ? 0.85 : 1.0;
+  double now = 1e30;
+  if (many.steps) {
+    now = 0.5 * scale * tile_launch_us(nx, ny, cus, many.cfg, many.tw, many.th, many.wrapx, many.wrapy, 2, cm.tile_memory, cm);
+    p.tile = plan_tile(nx, ny, cus, 2, cm);
+    p.tile.us_per_step *= scale;
+  }
+  if (march) p.march = plan_march(nx, ny, npl, 2, 2, max_waves, cus, 2, cm);
+  // 16-bit steps are bound by their instructions, of which surroundings cost more than estimated.
+  const double single = std::max(3.3, (half ? 0.95 : 1.05) * single_step_us(nx, ny, cus, cm));
+  const double best = std::min({p.march.us_per_step, p.tile.us_per_step, single});
+  const bool worth = best < 0.93 * now;
+  p.single = worth && single == best;
+  if (!worth || p.single || p.march.us_per_step != best) p.march.steps = 0;
+  if (!worth || p.single || p.march.steps || p.tile.us_per_step != best) p.tile.steps = 0;
+  return p;
 }
 
 // Time of a launch of one step.
