@@ -90,6 +90,13 @@ inline CostModel cost_model(int bytes, bool bgk, bool adjoint, bool bf16 = false
   return c;
 }
 
+// ceil of a small non-negative number, without the call into libm that std::ceil is here: lbm_init
+// plans in 3 us of host time instead of 8 (with recording 5 instead of 20).
+inline double up(double x) {
+  const double f = double(int64_t(x));
+  return f < x ? f + 1 : f;
+}
+
 // Strips of w stored nodes out of `span` (see MarchGeo). False where no strip width works.
 inline bool march_strips(int nx, int span, int halo, bool pairs, MarchPlan& p) {
   const int most = span - 2 * halo;
@@ -160,7 +167,8 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
       const int64_t nrb = std::min<int64_t>(std::max<int64_t>(1, slots / cols), ny);
       const int64_t rows = (ny + nrb - 1) / nrb;
       const int64_t rounds = (cols * nrb * waves + int64_t(cus) * 4 - 1) / (int64_t(cus) * 4);
-      auto launch = [&](int64_t steps) {
+      // Time of a launch; `least` where that already exceeds `limit`.
+      auto launch = [&](int64_t steps, double limit) {
         const double share = cm.march_spread && rounds > 2 ? double(cols * nrb * waves) / (cus * 4.0) : double(rounds);
         const double rate = cm.march_many - (cm.march_many - cm.march_alone) / double(rounds);
         const double issue = share * double(steps * (rows + steps - 1)) * npl * cm.wave / rate * (waves > 1 ? 1.01 : 1.0);
@@ -168,6 +176,8 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
         // delay each other (a norm of order 6), while reverse steps hide one behind the other.
         if (cm.rec_bytes == 0) {
           const double mem = double(nx) * ny * cm.bytes / (rounds < 2 ? cm.march_memory_alone : cm.march_memory);
+          const double least = cm.march_launch + std::max({2.0, issue, mem});
+          if (least >= limit) return least;
           const double i3 = issue * issue * issue, m3 = mem * mem * mem;
           return cm.march_launch + std::max(2.0, std::cbrt(std::sqrt(i3 * i3 + m3 * m3)));
         }
@@ -175,12 +185,19 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
         const double mem = double(nx) * ny * (cm.bytes / 2 * (1 + halo_reads) + steps * cm.rec_bytes * halo_reads);
         return cm.march_launch + std::max(issue, mem / cm.march_memory);
       };
+      double by_steps[8] = {};
       for (int steps = 2; steps <= max_steps; ++steps) {
-        double us = launch(steps) / steps;
+        double us;
         if (horizon > 0 && horizon < 64) {
           us = 0;
-          for (int64_t m = horizon; m > 0; m -= steps_ahead(m, steps, 0)) us += launch(steps_ahead(m, steps, 0));
+          for (int64_t m = horizon, ns; m > 0; m -= ns) {
+            ns = steps_ahead(m, steps, 0);
+            if (!(by_steps[ns] > 0)) by_steps[ns] = launch(ns, 1e30);
+            us += by_steps[ns];
+          }
           us /= double(horizon);
+        } else {
+          us = launch(steps, best.us_per_step * gain * steps) / steps;
         }
         if (us < best.us_per_step * gain) {
           best = p;
@@ -195,19 +212,25 @@ inline MarchPlan plan_march(int nx, int ny, int npl, int halo, int max_steps, in
   return best;
 }
 
-// Time of a launch of ns steps on tiles of tw x th nodes by instance c.
-inline double tile_launch_us(int nx, int ny, int cus, int c, int tw, int th, int wx, int wy, int ns, double memory,
-                             const CostModel& cm) {
-  const int cells = kTileConfigs[c].threads * kTileConfigs[c].nodes, h = ns - 1;
+// Blocks of instance c that a compute unit holds at once.
+inline int tile_fit(int c, const CostModel& cm) {
+  const int by_regs = 512 / cm.regs[c] * 4 * 64 / kTileConfigs[c].threads;
+  const int cells = kTileConfigs[c].threads * kTileConfigs[c].nodes;
+  return std::max(1, std::min(int(160 * 1024 / (cm.bytes / 2 * (cells + 2))), by_regs));
+}
+
+// Time of a launch of ns steps on `tiles` tiles of tw x th nodes, `fit` of them at once on a compute
+// unit.
+inline double tile_launch_us(int nx, int ny, int cus, int fit, int tiles, int tw, int th, int wx, int wy, int ns,
+                             double memory, const CostModel& cm) {
+  const int h = ns - 1;
   const double rw = tw + (wx ? 0 : 2 * h), rh = th + (wy ? 0 : 2 * h);
   // Wavefronts of the block (the region shrinks by a row on both sides per step), blocks per
-  // compute unit, and how many of them it holds at once.
-  const double wv = std::ceil(rw * (wy ? rh : rh - h) / 64.0);
-  const double share = double((nx + tw - 1) / tw) * ((ny + th - 1) / th) / cus, blocks = std::ceil(share);
-  const int by_regs = 512 / cm.regs[c] * 4 * 64 / kTileConfigs[c].threads;
-  const int fit = std::max(1, std::min(int(160 * 1024 / (cm.bytes / 2 * (cells + 2))), by_regs));
-  const double rounds = std::ceil(blocks / fit);
-  const double per = std::max(std::ceil(wv / 4), wv / 4 * (blocks > 2 && !cm.tile_uneven ? share : blocks));
+  // compute unit.
+  const double wv = up(rw * (wy ? rh : rh - h) / 64.0);
+  const double share = double(tiles) / cus, blocks = up(share);
+  const double rounds = up(blocks / fit);
+  const double per = std::max(up(wv / 4), wv / 4 * (blocks > 2 && !cm.tile_uneven ? share : blocks));
   const double wait = blocks <= 1 ? kTileAlone : fit == 1 ? kTileSerial : 1.0;
   const double region = rw * rh / (double(tw) * th);
   const double line = cm.tile_line / (cm.bytes / 18.0);  // in nodes
@@ -231,6 +254,7 @@ inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostMo
     if (cells > cm.max_cells) continue;
     int last = 0;  // a short horizon makes several of steps_try the same
     const double side = std::sqrt(double(cells));
+    const int fit = tile_fit(c, cm);
     for (int ns : steps_try) {
       int64_t launches = 1, m = ns;
       if (horizon > 0 && horizon < 64) {
@@ -241,6 +265,11 @@ inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostMo
         last = ns;
       }
       const int h = ns - 1;
+      // No tiles of this many steps can be faster than a launch, its accesses, barriers and
+      // collisions of the stored nodes alone.
+      const double least = kTileLaunch + double(nx) * ny * (cm.bytes + ns * cm.rec_bytes) / memory +
+                           ns * (kTileStep + cm.tile_wave * double(nx) * ny / (256.0 * cus));
+      if (least * double(launches) / double(m) >= best.us_per_step * 0.999) continue;
       for (int shape = 0; shape < 9; ++shape) {
         // Shapes: the whole width (0), the whole height (1), else regions of several widths.
         int tw, th, wx = 0, wy = 0;
@@ -267,9 +296,10 @@ inline TilePlan plan_tile(int nx, int ny, int cus, int64_t horizon, const CostMo
         const int ntx = (nx + tw - 1) / tw, nty = (ny + th - 1) / th;
         tw = (nx + ntx - 1) / ntx;
         th = (ny + nty - 1) / nty;
+        const int tiles = ntx * nty;
         const double rw = tw + (wx ? 0 : 2 * h), rh = th + (wy ? 0 : 2 * h);
         if (rw * rh > cells) continue;
-        const double us = tile_launch_us(nx, ny, cus, c, tw, th, wx, wy, ns, memory, cm) * double(launches) / double(m);
+        const double us = tile_launch_us(nx, ny, cus, fit, tiles, tw, th, wx, wy, ns, memory, cm) * double(launches) / double(m);
         if (us < best.us_per_step * 0.999) {
           best.steps = ns;
           best.cfg = c;
@@ -310,7 +340,8 @@ inline TwoPlan plan_two(int nx, int ny, int npl, int max_waves, int cus, bool ma
   const double scale = double(nx) * ny * cm.bytes < 0.8 * kCacheBytes ? 0.85 : 1.0;
   double now = 1e30;
   if (many.steps) {
-    now = 0.5 * scale * tile_launch_us(nx, ny, cus, many.cfg, many.tw, many.th, many.wrapx, many.wrapy, 2, cm.tile_memory, cm);
+    now = 0.5 * scale * tile_launch_us(nx, ny, cus, tile_fit(many.cfg, cm), (nx + many.tw - 1) / many.tw * ((ny + many.th - 1) / many.th),
+                                         many.tw, many.th, many.wrapx, many.wrapy, 2, cm.tile_memory, cm);
     p.tile = plan_tile(nx, ny, cus, 2, cm);
     p.tile.us_per_step *= scale;
   }
