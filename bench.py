@@ -102,18 +102,12 @@ def make_sim(w, model, storage, pattern, fields, **kw):
                       pattern=pattern, **kw)
 
 
-def launch_steps(sim, nx, ny):
-    """Steps of one launch of lbm_step(n) for a run of many steps, complete model, on MI355X (the
-    cost model's choice on grids of 4096^2 and more; other grids: 1 where steps_per_launch is 1,
-    else 2 as a lower bound)."""
+def next_launch(sim, steps=1 << 20):
+    """(kernel, steps) of a launch of lbm_step(n) for a run of many steps."""
     from paper_2602_21242_amd import capi
-    if sim.steps_per_launch == 1:
-        return 1
-    if nx * ny < 4096 * 4096:
-        return 2
-    if sim.params.storage in (capi.LBM_F64, capi.LBM_F32):
-        return 4
-    return 3 if nx * ny >= 8192 * 8192 else 2
+    status, kernel, n = capi.lbm_next_launch(sim._ctx, steps)
+    capi.check(status, "lbm_next_launch")
+    return ("k_step", "k_march", "k_tile", "k_pair")[kernel], n
 
 
 def spin_up(sim, seconds):
@@ -319,7 +313,7 @@ def main():
     # same configuration, with no pause between the spin-up, the warm-up and the timed steps.
     sim = make_sim(w, args.model, args.storage, args.pattern, fields)
     spin = make_sim(w, args.model, args.storage, args.pattern, fields)
-    spl = 1 if args.single_step else launch_steps(sim, w.nx, w.ny)
+    name, spl = next_launch(sim, 1 if args.single_step else 1 << 20)
     ms = timer(sim, args.steps, args.warmup, spin=spin, spin_s=args.spin_up)
     del spin
     inv = sim.invariants(allow_nonfinite=True)
@@ -335,7 +329,7 @@ def main():
         f"(cold {cold_ms:.4f} ms/step, {nodes / (cold_ms * 1e-3) / 1e9:.2f} GLUPS), "
         f"{achieved:.0f} GB/s algorithmic at {ALG_BYTES[args.storage]} B per node and launch")
     traffic = load_traffic(w.name, args.model, args.storage, args.pattern)
-    kernel = (f"k_march<{args.storage},{args.model},{spl}>" if spl > 1 else f"k_step<{args.storage},{args.model},{args.pattern}>")
+    kernel = f"{name}<{args.storage},{args.model},{spl if spl > 1 else args.pattern}>"
     roofline = {"bound": "hbm" if spl == 1 else "vector issue", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kernel, "steps_per_launch": spl,
                 "alg_bytes_per_node_launch": ALG_BYTES[args.storage],
@@ -370,7 +364,7 @@ def main():
                                    ("uc", "aa"), ("partial", "aa")):
                 log(f"[bench] variant tg4096 {model} f32 {pattern}")
                 s = make_sim(w, model, "f32", pattern, fields)
-                sp = launch_steps(s, w.nx, w.ny)
+                _, sp = next_launch(s)
                 m = time_steady(s, steps_v)
                 res[f"tg4096/{model}/f32/{pattern}"] = {
                     "ms_per_step": m, "GLUPS": nodes / (m * 1e-3) / 1e9, "steps_per_launch": sp,
@@ -399,7 +393,7 @@ def main():
             for storage in ("f64", "f32", "f16", "bf16"):
                 log(f"[bench] variant turb8192 complete {storage} ab")
                 s = make_sim(wt, "complete", storage, "ab", tf)
-                sp = launch_steps(s, wt.nx, wt.ny)
+                _, sp = next_launch(s)
                 m = time_steady(s, 200)
                 ent = {"ms_per_step": m, "GLUPS": nt / (m * 1e-3) / 1e9, "steps_per_launch": sp,
                        "hbm_frac_per_update": ALG_BYTES[storage] * nt / (m * 1e-3) / 1e9 / HBM_PEAK_GBS}

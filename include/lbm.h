@@ -97,8 +97,9 @@ typedef struct {
                             nothing */
   int64_t record_steps;  /* 0: no adjoint; N > 0: checkpoint the first N steps for lbm_adjoint */
   int32_t two_step;      /* A-B: several steps per kernel launch. 0: as many as are fastest for the
-                            grid, type and model; 1: the kernel that marches up the rows wherever
-                            lbm_steps_per_launch documents 2, else as 0; -1: one step per launch.
+                            grid, type and model; 1: the kernels that walk up the rows (marching,
+                            pair) wherever lbm_steps_per_launch is 2, else as 0; -1: one step per
+                            launch.
                             AA: two reverse steps per launch of the adjoint, by the same values */
   int32_t walls;         /* 0: doubly periodic. 1: the columns x = 0 and x = nx - 1 are solid
                             nodes with fullway bounce-back (the isothermal shocktube, Sec. 5):
@@ -201,16 +202,30 @@ lbm_status lbm_adjoint_populations(lbm_ctx* ctx, const void* d_fbarN, void* d_fb
 /* Completed time steps n, or -1 for a NULL context. */
 int64_t lbm_time(const lbm_ctx* ctx);
 
-/* 2 on grids of at least two steps per kernel launch in pairs of rows, else 1 (-1 for a NULL
- * context): the A-B pattern (every storage type and model), no walls, nx a multiple of 512, more
- * than 2^15 storage positions and two_step >= 0; with two_step = 0 also only where the grid gives
- * at least three quarters of the device's compute units a block of 2 or more rows x 512 columns
- * (roughly (nx/512) floor(ny/2) >= 3 CUs/4). It classifies the grid and is not the length of a
- * launch: with two_step >= 0 lbm_step takes 2 to 4 steps per launch on large A-B grids, more on
- * small ones, up to all of a call's (at most 4096) on boxes that one block holds. A launch never
- * passes over a checkpoint time of a recorded run. Results do not depend on it: several steps in
- * one launch are bit-identical to single steps. */
+/* The unit in which lbm_step counts the launches of a captured call: 2 or 1 (-1 for a NULL
+ * context). 2 for the A-B pattern (every storage type and model), no walls, nx a multiple of 512,
+ * more than 2^15 storage positions and two_step >= 0; with two_step = 0 also only where the grid
+ * gives at least three quarters of the device's compute units a block of 2 or more rows x 512
+ * columns (roughly (nx/512) floor(ny/2) >= 3 CUs/4). It depends on the grid alone; how many steps a
+ * launch really takes is lbm_next_launch's answer. */
 int32_t lbm_steps_per_launch(const lbm_ctx* ctx);
+
+/* The kernels that lbm_step and lbm_adjoint* launch (lbm_next_launch). */
+typedef enum {
+  LBM_KERNEL_STEP = 0,  /* one step */
+  LBM_KERNEL_MARCH = 1, /* 2 to 4 steps (A-B), wavefronts marching up strips of columns */
+  LBM_KERNEL_TILE = 2,  /* 2 to 4096 steps (A-B), tiles of the box kept in LDS */
+  LBM_KERNEL_PAIR = 3   /* 2 steps: forward A-B without recording, reverse AA; rows staged in LDS */
+} lbm_kernel;
+
+/* The kernel and the number of steps of the first launch for n >= 1 steps: of lbm_step outside the
+ * recorded window (reverse = 0), or of the reverse sweep with n steps left in a checkpoint segment
+ * (reverse = 1, record_steps > 0). Host side only. Results do not depend on it: several steps in
+ * one launch are bit-identical to single steps. A launch never passes over a checkpoint time of a
+ * recorded run; inside the window lbm_step takes the steps left in the segment for n. A context
+ * that has been captured may take one step less (see lbm_step), and short AA and single-step runs
+ * replay 64 launches at a time. */
+lbm_status lbm_next_launch(const lbm_ctx* ctx, int64_t n, int32_t reverse, lbm_kernel* kernel, int64_t* steps);
 
 const char* lbm_status_string(lbm_status s);
 

@@ -14,6 +14,7 @@ LBM_ERR_HIP, LBM_ERR_NONFINITE, LBM_ERR_STATE = 4, 5, 6
 LBM_BGK, LBM_OREG_UC, LBM_OREG_PARTIAL, LBM_OREG_COMPLETE = 0, 1, 2, 3
 LBM_F64, LBM_F32, LBM_BF16, LBM_F16 = 0, 1, 2, 3
 LBM_AB, LBM_AA = 0, 1
+LBM_KERNEL_STEP, LBM_KERNEL_MARCH, LBM_KERNEL_TILE, LBM_KERNEL_PAIR = 0, 1, 2, 3
 
 MODELS = {"bgk": LBM_BGK, "uc": LBM_OREG_UC, "partial": LBM_OREG_PARTIAL, "complete": LBM_OREG_COMPLETE}
 DTYPES = {"f64": LBM_F64, "f32": LBM_F32, "bf16": LBM_BF16, "f16": LBM_F16}
@@ -73,6 +74,9 @@ def lib():
         L.lbm_time.argtypes = [_vp]
         L.lbm_steps_per_launch.restype = ctypes.c_int32
         L.lbm_steps_per_launch.argtypes = [_vp]
+        L.lbm_next_launch.restype = st
+        L.lbm_next_launch.argtypes = [_vp, ctypes.c_int64, ctypes.c_int32, ctypes.POINTER(ctypes.c_int),
+                                      ctypes.POINTER(ctypes.c_int64)]
         L.lbm_status_string.restype = ctypes.c_char_p
         L.lbm_status_string.argtypes = [ctypes.c_int]
         L.lbm_last_error.restype = ctypes.c_char_p
@@ -162,6 +166,13 @@ def lbm_time(ctx):
 
 def lbm_steps_per_launch(ctx):
     return lib().lbm_steps_per_launch(ctx)
+
+
+def lbm_next_launch(ctx, n, reverse=False):
+    """(status, kernel, steps) of the first launch for n steps."""
+    kernel, steps = ctypes.c_int(-1), ctypes.c_int64(0)
+    s = lib().lbm_next_launch(ctx, int(n), int(reverse), ctypes.byref(kernel), ctypes.byref(steps))
+    return s, kernel.value, steps.value
 
 
 def lbm_status_string(s):

@@ -293,6 +293,24 @@ int64_t forward_steps(const lbm_ctx* c, int64_t m) {
   return ns == 2 && c->d.two.single ? 1 : ns;
 }
 
+// Kernel of a forward launch of ns >= 2 steps that records nothing (the rule of Engine::steps).
+lbm_kernel forward_kernel(const lbm_ctx* c, int64_t ns) {
+  const lbm::RunDesc& d = c->d;
+  if (ns == 2 && d.two_rb) return LBM_KERNEL_PAIR;
+  if (ns == 2 && d.two.march.steps) return LBM_KERNEL_MARCH;
+  return (ns == 2 && d.two.tile.steps) || d.tile.steps ? LBM_KERNEL_TILE : LBM_KERNEL_MARCH;
+}
+
+// Steps of the next reverse launch when m lie ahead in the segment, and its kernel.
+int64_t reverse_steps(const lbm_ctx* c, int64_t m) {
+  if (c->p.pattern == LBM_AB) return lbm::steps_ahead(m, c->d.adj_march.steps, c->d.adj_tile.steps);
+  return c->d.adj_rb > 0 && m >= 2 ? 2 : 1;
+}
+lbm_kernel reverse_kernel(const lbm_ctx* c) {
+  if (c->p.pattern != LBM_AB) return LBM_KERNEL_PAIR;
+  return c->d.adj_tile.steps ? LBM_KERNEL_TILE : LBM_KERNEL_MARCH;
+}
+
 bool is_small(const lbm_ctx* c) { return int64_t(c->d.pitch) * c->d.ny <= kGraphMaxPositions; }
 
 // The executable graph of kGraphSteps steps from the current buffer index (A-B) or phase
@@ -365,8 +383,7 @@ lbm_status sweep(lbm_ctx* c, int* out_b) {
     // Reverse steps t = t1 - 1 .. t0, several per launch (t, t - 1, ...) where the plan says so.
     for (int64_t t = t1 - 1; t >= t0;) {
       const int64_t m = t - t0 + 1;
-      const int64_t ns = c->p.pattern == LBM_AB ? lbm::steps_ahead(m, d.adj_march.steps, d.adj_tile.steps)
-                                                : (d.adj_rb > 0 && m >= 2 ? 2 : 1);
+      const int64_t ns = reverse_steps(c, m);
       st = dispatch(c->p.storage, [&](auto eng) -> lbm_status {
         using E = decltype(eng);
         using T = typename E::T;
@@ -741,6 +758,19 @@ lbm_status lbm_adjoint_populations(lbm_ctx* c, const void* d_fbarN, void* d_fbar
 int32_t lbm_steps_per_launch(const lbm_ctx* c) {
   if (!c) return -1;
   return (!is_small(c) && c->d.pair) ? 2 : 1;
+}
+
+lbm_status lbm_next_launch(const lbm_ctx* c, int64_t n, int32_t reverse, lbm_kernel* kernel, int64_t* steps) {
+  return guarded([&]() -> lbm_status {
+    lbm_status s = check_ctx(c);
+    if (s != LBM_OK) return s;
+    if (n < 1) return fail(LBM_ERR_INVALID_ARGUMENT, "n must be >= 1");
+    if (!kernel || !steps) return fail(LBM_ERR_INVALID_ARGUMENT, "output is NULL");
+    if (reverse && c->p.record_steps <= 0) return fail(LBM_ERR_STATE, "context was created with record_steps = 0");
+    *steps = reverse ? reverse_steps(c, n) : forward_steps(c, n);
+    *kernel = *steps == 1 ? LBM_KERNEL_STEP : reverse ? reverse_kernel(c) : forward_kernel(c, *steps);
+    return LBM_OK;
+  });
 }
 
 int64_t lbm_time(const lbm_ctx* c) { return c ? c->time : -1; }

@@ -21,9 +21,10 @@ class Simulation:
     adjoint() (sqrt(N) checkpoints by default, or every ckpt_stride steps; the forward run
     keeps the last segment's moments, so ckpt_stride >= record_steps needs no recomputation
     at record_steps x 5 x 4 (FP64: x 8) bytes per node). two_step: 0 runs
-    as many steps per launch as are fastest for the grid, 1 prefers the marching kernel on the
-    grids of steps_per_launch 2, -1 one step per launch (results are bit-identical). walls: solid bounce-back columns at x = 0
-    and x = nx - 1 (A-B pattern, no recording).
+    as many steps per launch as are fastest for the grid, 1 prefers the kernels that walk up the
+    rows (marching, pair) on the grids of steps_per_launch 2, -1 one step per launch (results are
+    bit-identical). walls: solid bounce-back columns at x = 0 and x = nx - 1 (A-B pattern, no
+    recording).
     """
 
     def __init__(self, nx, ny, theta, nu, ux, uy, rho=None, rho0=1.0, model="complete", storage="f32",
@@ -80,8 +81,9 @@ class Simulation:
 
     @property
     def steps_per_launch(self):
-        """2 on A-B grids of whole blocks of 512 columns large enough for the device, else 1 (the
-        launches themselves take 2 to 4 steps on large grids and more on small ones)."""
+        """2 on A-B grids of whole blocks of 512 columns large enough for the device, else 1: the unit
+        in which the launches of a captured call are counted (capi.lbm_next_launch says how many
+        steps a launch takes)."""
         return capi.lbm_steps_per_launch(self._ctx)
 
     @property
