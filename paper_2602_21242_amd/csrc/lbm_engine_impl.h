@@ -582,7 +582,11 @@ hipError_t launch_tile(const RunDesc& d, const TilePlan& p, int ns, hipStream_t 
     case 0: go(k_tile<S, MODEL, 256, 1, KIND>, args...); break;
     case 1: go(k_tile<S, MODEL, 512, 1, KIND>, args...); break;
     case 2: go(k_tile<S, MODEL, 1024, 1, KIND>, args...); break;
-    case 3: go(k_tile<S, MODEL, 1024, 2, KIND>, args...); break;
+    case 3:
+      // Reverse FP64 tiles have no registers for two nodes per thread (CostModel::max_cells).
+      if constexpr (KIND == TILE_ADJOINT && sizeof(S) == 8) return hipErrorInvalidValue;
+      else go(k_tile<S, MODEL, 1024, 2, KIND>, args...);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

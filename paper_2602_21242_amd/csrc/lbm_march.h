@@ -14,15 +14,15 @@
 // steps.
 //
 // The strip's edge nodes lose their neighbours, one column per side and step, so a wavefront
-// stores the 64 NPL - 2 halo nodes in its middle (halo: kMarchHalo, two for launches of two steps), and a row block recomputes NS - 1 rows
-// of step 1 on either side. Measured on MI355X (complete model, us per launch of 4 steps, us per
-// launch of 2 steps of the LDS-staged pair kernel this replaces): FP32 4096^2 300 / 205, 8192^2
-// 1102 / 830; FP64 4096^2 531 / 418. The FP32 kernel issues a vector instruction in nearly every
-// slot (142 per node and step; 39.3e12 lane operations per second allow 277 GLUPS, reached
-// without the halo), so it is bound by the collision's arithmetic and 1/NS of the traffic.
-// Fewer steps leave it bound by memory (4096^2: 3 steps 298, 2 steps 300-327 us per launch), more
-// need more than 256 registers. Two nodes per lane halve the halo's share and the DPP shifts of
-// one (4096^2 345 us); FP64 has registers for one.
+// stores the 64 NPL - 2 halo nodes in its middle (halo: kMarchHalo, two in the plan for launches of
+// two steps), and a row block recomputes NS - 1 rows of step 1 on either side. Measured on MI355X
+// (complete model, us per launch of four steps, per two steps of the LDS-staged pair kernel of
+// lbm_pair.h): FP32 4096^2 300 / 197, 8192^2 1102 / 802; FP64 4096^2 531 / 405. The FP32 kernel is
+// bound by its instructions: 139 vector instructions per computed node and step, 85 274 per
+// wavefront with the surroundings (128 columns for 120 stored, 77 rows for 71), 676 000 clocks per
+// SIMD at 4096^2, which at 2.4 GHz is 93 % of the launch's time. Fewer steps leave it bound by memory (4096^2: 3
+// steps 280, 2 steps 239-284 us per launch), more need more than 256 registers. Two nodes per lane
+// halve the halo's share and the DPP shifts of one (4096^2 345 us); FP64 has registers for one.
 #pragma once
 
 #include "lbm_step.h"
@@ -166,7 +166,8 @@ __device__ __forceinline__ Strip strip_of(const MarchGeo& g, int& xw) {
   return s;
 }
 
-// Row r of a periodic column of ny rows, r within [-kMarchMax, ny + kMarchMax).
+// Row r of a periodic column of ny rows, r within [-2 (kMarchMax - 1), ny + kMarchMax) (the reverse
+// march reads the records of s rows further down).
 __device__ __forceinline__ int wrap_row(int r, int ny) {
   while (r < 0) r += ny;
   while (r >= ny) r -= ny;

@@ -147,7 +147,8 @@ inline int64_t steps_ahead_parity(int64_t m, int march, int tile, bool odd, bool
 // Row blocks and steps per launch of least time per step. A SIMD works through its share of the
 // strips' row blocks; a block of h rows costs steps * (h + steps - 1) collisions, and more
 // wavefronts per SIMD fill more of each other's waits. Fitted to 300 launches from 1000^2 to
-// 8192^2 (7 to 9 % off in the mean, the picked plan within 4 % of the fastest one): FP16 8192^2
+// 8192^2 (7 to 9 % off in the mean, the picked plan within 4 % of the fastest one; the largest FP32
+// grids are estimated too slow, 89 us per step for 76 at 4096^2 and 328 for 288 at 8192^2): FP16 8192^2
 // 388 us per step with two wavefronts per SIMD and two steps, 326 with six and three; BF16 340 and
 // 284; FP64 2024^2 40.3 with one wavefront, 38.5 with two; FP32 2048^2 24.4 with three steps, 22.8
 // with four; FP32 LBGK 4096^2, bound by memory, 63.6 with one wavefront per SIMD, 72.3 with three.
