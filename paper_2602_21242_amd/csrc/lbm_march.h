@@ -19,10 +19,12 @@
 // (complete model, us per launch of four steps, per two steps of the LDS-staged pair kernel of
 // lbm_pair.h): FP32 4096^2 300 / 197, 8192^2 1102 / 802; FP64 4096^2 531 / 405. The FP32 kernel is
 // bound by its instructions: 139 vector instructions per computed node and step, 85 274 per
-// wavefront with the surroundings (128 columns for 120 stored, 77 rows for 71), 676 000 clocks per
-// SIMD at 4096^2, which at 2.4 GHz is 93 % of the launch's time. Fewer steps leave it bound by memory (4096^2: 3
-// steps 280, 2 steps 239-284 us per launch), more need more than 256 registers. Two nodes per lane
-// halve the halo's share and the DPP shifts of one (4096^2 345 us); FP64 has registers for one.
+// wavefront with the surroundings (128 columns for 120 stored, 77 rows for 71), which at 4096^2 are
+// 676 000 clocks per SIMD, as many as the launch takes (310 us at the 2.16 GHz that the chip runs at
+// then). FP64 fills 0.72 of its issue slots (1.94 GHz), FP16 0.97 (2.34 GHz). Fewer steps leave FP32
+// bound by memory (4096^2: 3 steps 280, 2 steps 239-284 us per launch), more need more than 256
+// registers. Two nodes per lane halve the halo's share and the DPP shifts of one (4096^2 345 us);
+// FP64 has registers for one.
 #pragma once
 
 #include "lbm_step.h"
