@@ -46,3 +46,22 @@ def test_pair_kernel(nx, ny, storage, model):
         out.append(sim.populations(dtype=torch.float32 if storage == "f32" else torch.float64))
         sim.close()
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("nx,ny", [(384, 384), (513, 200), (700, 700), (1000, 600), (2041, 1200), (1024, 1500)])
+def test_recorded_segments_of_two_steps(nx, ny, storage):
+    """Forward and recomputed launches that end at checkpoints two steps apart, with records."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nx + ny)
+    f0 = (1.0 + 0.1 * (2.0 * torch.rand(9, ny, nx, generator=g, device="cuda", dtype=torch.float64) - 1.0)) / 9.0
+    w = torch.randn(9, ny, nx, generator=g, device="cuda", dtype=torch.float64)
+    got = []
+    for ts in (0, -1):
+        sim = gpu_sim(nx, ny, 0.4, 0.05, "complete", storage, "ab", two_step=ts, record_steps=7, ckpt_stride=2)
+        sim.set_populations(f0)
+        sim.step(7)
+        got.append((sim.populations(), sim.adjoint_populations(w)))
+        sim.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
