@@ -420,8 +420,8 @@ __device__ __forceinline__ void collide(const T g[Q], T out[Q], const Coef<T>& k
 //   sums over c                4.1e-6,  0.4e-6    -5.7e-5 to  8.6e-5
 // Root mean square error of the gradient of 400 steps of a shear layer at 333 x 190 against FP64:
 // 1.2e-7, one by one 4.6e-6, sums over c 4.7e-6. It costs 4 vector instructions and, with the nine
-// fbs held to the end, 8 to 18 registers (8 reverse steps of 1024^2 140 -> 143 us, of 4096^2 1632
-// -> 1641).
+// fbs held to the end, 8 to 18 registers (8 reverse steps of 1024^2 140.1 -> 140.6 us, of 4096^2
+// 1637 -> 1643).
 template <class T, int MODEL>
 __device__ __forceinline__ void collide_vjp(const T fbs[Q], const T rec[NREC], const Coef<T>& k, T fbar[Q]) {
 #pragma clang fp contract(off)

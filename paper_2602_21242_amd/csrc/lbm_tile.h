@@ -39,30 +39,34 @@ struct TileGeo {
 };
 
 // A region's cells: one population after the other, one spare cell at either end (the odd steps'
-// neighbours of the first and last cell).
-template <class S, int CELLS>
+// neighbours of the first and last cell). own: see kTileWaves.
+template <class S, int CELLS, bool PARK>
 struct TileCells {
   S c[Q][CELLS + 2];
+  int own[PARK ? CELLS + 2 : 1];
 };
 
 // Least wavefronts per SIMD that the registers have to allow. FP32 reverse tiles of one node per
-// thread want 70 registers, which leaves a compute unit one block of 1024 threads; held to 64 (one
-// spilled) it takes two: 8 reverse steps of 1024^2 in one segment 155.8 -> 142.8 us.
-template <class S, int M, int KIND>
-constexpr int kTileWaves = KIND == TILE_ADJOINT && sizeof(S) == 4 && M == 1 ? 8 : 1;
+// thread want 70 registers, which leaves a compute unit one block of 1024 threads; held to 64 it
+// takes two: 8 reverse steps of 1024^2 in one segment 155.8 -> 140.6 us. They then keep what the
+// last step alone needs (own) in LDS. Spilled to scratch memory instead, the one register costs
+// each launch 0.7 us (142.6). Smaller blocks need no bound.
+template <class S, int NT, int M, int KIND>
+constexpr int kTileWaves = KIND == TILE_ADJOINT && sizeof(S) == 4 && M == 1 && NT == 1024 ? 8 : 1;
 
 // KIND TILE_STEP / TILE_WALLS: ns forward steps (with the bounce-back columns of k_step);
 // TILE_REC: step s also writes its moments to rec + s rec_slot; TILE_ADJOINT: ns reverse steps
 // on fbar (S is the compute type), reverse step s with the moments at rec - s rec_slot.
 template <class S, int MODEL, int NT, int M, int KIND>
-__global__ void __launch_bounds__(NT, (kTileWaves<S, M, KIND>))
+__global__ void __launch_bounds__(NT, (kTileWaves<S, NT, M, KIND>))
 k_tile(const S* __restrict__ src, S* __restrict__ dst, TileGeo g, Coef<typename StorageTraits<S>::T> k,
        typename StorageTraits<S>::T* rec, int64_t rec_slot) {
   using T = typename StorageTraits<S>::T;
   using Tr = StorageTraits<S>;
   constexpr bool ADJ = KIND == TILE_ADJOINT;
   constexpr int D = ADJ ? -1 : 1;  // inputs come from x - D c
-  __shared__ TileCells<S, NT * M> lds;
+  constexpr bool PARK = kTileWaves<S, NT, M, KIND> > 1;  // own waits in LDS for the last step
+  __shared__ TileCells<S, NT * M, PARK> lds;
   const int n_cells = g.rw * g.rh;
   const int tx0 = (int(blockIdx.x) % g.ntx) * g.tw, ty0 = (int(blockIdx.x) / g.ntx) * g.th;
   const size_t srcb = size_t(g.rs) * g.ny * sizeof(S), recb = size_t(g.rec_rs) * g.ny * sizeof(T);
@@ -107,6 +111,7 @@ k_tile(const S* __restrict__ src, S* __restrict__ dst, TileGeo g, Coef<typename 
       for (int j = 0; j < NREC; ++j)
         rv[m][j] = ldb<T, false>(rr, j * g.ps * int(sizeof(T)), uint32_t(rpos[m]) * uint32_t(sizeof(T)));
     }
+    if constexpr (PARK) lds.own[n + 1] = own[m];
   }
   for (int s = 0; s < g.ns; ++s) {
     const int lo = g.wrapy ? 0 : s * g.rw, hi = g.wrapy ? n_cells : n_cells - s * g.rw;
@@ -156,6 +161,7 @@ k_tile(const S* __restrict__ src, S* __restrict__ dst, TileGeo g, Coef<typename 
         for (int i = 0; i < Q; ++i) out[i] = wall[m] ? g9[m][opp(i)] : out[i];
       }
       if (last) {
+        if constexpr (PARK) own[m] = lds.own[c];
         if (own[m] >= 0) {
 #pragma unroll
           for (int i = 0; i < Q; ++i)
